@@ -1,6 +1,7 @@
 // Streaming kernels around the matrix-core GEMMs of the scoring path: feature transform, layer-1
 // candidate term, weight packing, the shared per-tensor encoder, score assembly and argmax.
 #include "internal.hpp"
+#include <type_traits>
 
 namespace ab {
 
@@ -466,39 +467,115 @@ __global__ __launch_bounds__(256) void finish_select_wave_kernel(const FinishArg
     }
 }
 
-// Plain argmax over stored rows (C <= 1024, a multiple of 4, 16-byte aligned rows): sixteen lanes per
-// scenario, four scenarios per wavefront, all of a lane's 16-byte loads issued up front; the lanes of a
-// row of sixteen combine through four DPP exchanges (no LDS).
-template <int NLOAD>
-__global__ __launch_bounds__(256) void select_rows16_kernel(const FinishArgs a, int64_t S)
+// Optimization Trigger (Section 3.3): argmax of a stored score row, relative gain over the configuration in
+// use, and the two threshold tests; IEEE single precision throughout.
+struct TriggerArgs {
+    const float *scores; int64_t row_stride; int32_t C;
+    const int32_t *cur_idx; const float *observed;
+    float gain_threshold, error_threshold;
+    int32_t *best_idx; float *gain; uint8_t *reconf; uint8_t *adapt;
+};
+// (bv, bi) = the row's best, vc = the score in use (NaN where the current index is outside the row)
+__device__ __forceinline__ void trigger_write(const TriggerArgs &a, int64_t s, float bv, int bi, float vc, bool cur_ok, float obs)
 {
+    const bool has_best = bi != AB_NONE;
+    a.best_idx[s] = has_best ? bi : -1;
+    const float nan = __uint_as_float(0x7fc00000u);
+    const float g = has_best && cur_ok ? (bv - vc) / fabsf(vc) : nan;
+    if (a.gain) a.gain[s] = g;
+    a.reconf[s] = (uint8_t)(g >= a.gain_threshold);
+    if (a.adapt) {
+        const float e = a.observed && cur_ok ? fabsf(vc - obs) / fabsf(obs) : nan;
+        a.adapt[s] = (uint8_t)(e > a.error_threshold);
+    }
+}
+
+// Decision on stored rows of at most 1024 columns: the plain argmax (FinishArgs) or the trigger (TriggerArgs).
+// Bound by reading the rows once, so a wavefront takes four rows (sixteen lanes each) and issues all of a lane's
+// loads before it looks at the first value; the lanes of a row of sixteen combine through four DPP exchanges (no
+// LDS, no barrier).  VEC: rows are 16-byte aligned and a multiple of four columns, a lane loads 16 bytes at a
+// time; otherwise 4 bytes (sixteen adjacent lanes still read 64 contiguous bytes).  What the trigger reads besides
+// the row (index in use, its score, the observed speed) is asked for in front of the row and hides behind it.
+// Measured at 65536 x 256: trigger 54.2 -> 14.4 us a call (a work-group per row and a barrier
+// before), argmax 12.5 us a call; argmax of rows without 16-byte alignment 21.8 -> 17.7 us (a wavefront per row before).
+template <int NLOAD, bool VEC, typename Args>
+__global__ __launch_bounds__(256) void decide_rows16_kernel(const Args a, int64_t S)
+{
+    constexpr bool TRIGGER = std::is_same<Args, TriggerArgs>::value;
     const int l16 = threadIdx.x & 15;
     const int64_t s = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     const bool live = s < S;
-    const float *p = a.partial + (live ? s : 0) * a.row_stride;
+    const int64_t sr = live ? s : 0;
+    const float *p;
+    int ci = 0;
+    float obs = 0.f;
+    if constexpr (TRIGGER) {
+        p = a.scores + sr * a.row_stride;
+        ci = a.cur_idx[sr];
+        if (a.observed) obs = a.observed[sr];
+    } else {
+        p = a.partial + sr * a.row_stride;
+    }
     f32x4 x[NLOAD];
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
-        const int c = (i * 16 + l16) * 4;
-        x[i] = (live && c < a.C) ? __builtin_nontemporal_load((const f32x4 *)(p + c))
-                                 : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        if constexpr (VEC) {
+            const int c = (i * 16 + l16) * 4;
+            x[i] = (live && c < a.C) ? __builtin_nontemporal_load((const f32x4 *)(p + c))
+                                     : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int c = i * 64 + e * 16 + l16;
+                x[i][e] = (live && c < a.C) ? __builtin_nontemporal_load(p + c) : -INFINITY;
+            }
+        }
+    }
+    bool cur_ok = false;
+    float vc = __uint_as_float(0x7fc00000u);
+    if constexpr (TRIGGER) {
+        cur_ok = ci >= 0 && ci < a.C;
+        if (cur_ok) vc = p[ci];
     }
     float bv = -INFINITY;
     int bi = AB_NONE;
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
-        const int c = (i * 16 + l16) * 4;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) if (c < a.C) amax_take(bv, bi, x[i][e], c + e);
+        for (int e = 0; e < 4; ++e) {
+            const int c = VEC ? (i * 16 + l16) * 4 + e : i * 64 + e * 16 + l16;
+            if (c < a.C) amax_take(bv, bi, x[i][e], c);
+        }
     }
     amax_dpp<0xB1>(bv, bi);      // lanes ^ 1   (quad_perm 1,0,3,2)
     amax_dpp<0x4E>(bv, bi);      // lanes ^ 2   (quad_perm 2,3,0,1)
     amax_dpp<0x141>(bv, bi);     // the other quad of the half row (row_half_mirror)
     amax_dpp<0x140>(bv, bi);     // the other half of the row (row_mirror)
     if (live && l16 == 0) {
-        a.best_idx[s] = (bi == AB_NONE) ? -1 : bi;
-        if (a.best_score) a.best_score[s] = (bi == AB_NONE) ? __uint_as_float(0x7fc00000u) : bv;
+        if constexpr (TRIGGER) {
+            trigger_write(a, s, bv, bi, vc, cur_ok, obs);
+        } else {
+            a.best_idx[s] = (bi == AB_NONE) ? -1 : bi;
+            if (a.best_score) a.best_score[s] = (bi == AB_NONE) ? __uint_as_float(0x7fc00000u) : bv;
+        }
     }
+}
+
+template <typename Args>
+static void launch_decide_rows16(const Args &a, const float *rows, int64_t row_stride, int64_t S, hipStream_t st)
+{
+    const unsigned blocks = (unsigned)((S + 15) / 16);
+    const bool vec = a.C % 4 == 0 && row_stride % 4 == 0 && ((uintptr_t)rows & 15) == 0;
+    auto go = [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        if (vec) decide_rows16_kernel<N, true, Args><<<blocks, 256, 0, st>>>(a, S);
+        else     decide_rows16_kernel<N, false, Args><<<blocks, 256, 0, st>>>(a, S);
+    };
+    if (a.C <= 64) go(std::integral_constant<int, 1>{});
+    else if (a.C <= 128) go(std::integral_constant<int, 2>{});
+    else if (a.C <= 256) go(std::integral_constant<int, 4>{});
+    else if (a.C <= 512) go(std::integral_constant<int, 8>{});
+    else go(std::integral_constant<int, 16>{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -722,15 +799,7 @@ __global__ __launch_bounds__(1024) void score_tiny_kernel(const TinyArgs a)
     }
 }
 
-// Optimization Trigger (Section 3.3): argmax of a stored score row, relative gain over the configuration in
-// use, and the two threshold tests.  One work-group per scenario; IEEE single precision throughout.
-struct TriggerArgs {
-    const float *scores; int64_t row_stride; int32_t C;
-    const int32_t *cur_idx; const float *observed;
-    float gain_threshold, error_threshold;
-    int32_t *best_idx; float *gain; uint8_t *reconf; uint8_t *adapt;
-};
-
+// The trigger on rows of more than 1024 columns: one work-group per scenario.
 __global__ __launch_bounds__(256) void trigger_kernel(const TriggerArgs a)
 {
     const int64_t s = blockIdx.x;
@@ -746,21 +815,9 @@ __global__ __launch_bounds__(256) void trigger_kernel(const TriggerArgs a)
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 4; ++w) amax_take(bv, bi, sv[w], si[w]);
-        const bool has_best = bi != AB_NONE;
-        a.best_idx[s] = has_best ? bi : -1;
         const int ci = a.cur_idx[s];
         const bool cur_ok = ci >= 0 && ci < a.C;
-        const float nan = __uint_as_float(0x7fc00000u);
-        const float vc = cur_ok ? p[ci] : nan;
-        float g = nan;
-        if (has_best && cur_ok) g = (bv - vc) / fabsf(vc);
-        if (a.gain) a.gain[s] = g;
-        a.reconf[s] = (uint8_t)(g >= a.gain_threshold);
-        if (a.adapt) {
-            float e = nan;
-            if (a.observed && cur_ok) e = fabsf(vc - a.observed[s]) / fabsf(a.observed[s]);
-            a.adapt[s] = (uint8_t)(e > a.error_threshold);
-        }
+        trigger_write(a, s, bv, bi, cur_ok ? p[ci] : __uint_as_float(0x7fc00000u), cur_ok, a.observed ? a.observed[s] : 0.f);
     }
 }
 
@@ -1085,12 +1142,8 @@ hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride
     a.partial = partial; a.nt = nt; a.row_stride = row_stride; a.b_out = b_out; a.scores = scores;
     a.score_stride = score_stride; a.best_idx = best_idx; a.best_score = best_score; a.C = C;
     const unsigned wave_blocks = (unsigned)((S + 3) / 4);
-    if (C <= 1024 && nt == 1 && !b_out && !scores && best_idx && C % 4 == 0 && row_stride % 4 == 0 &&
-        ((uintptr_t)partial & 15) == 0) {
-        const unsigned blocks = (unsigned)((S + 15) / 16);
-        if (C <= 256) select_rows16_kernel<4><<<blocks, 256, 0, st>>>(a, S);
-        else if (C <= 512) select_rows16_kernel<8><<<blocks, 256, 0, st>>>(a, S);
-        else select_rows16_kernel<16><<<blocks, 256, 0, st>>>(a, S);
+    if (C <= 1024 && nt == 1 && !b_out && !scores && best_idx) {
+        launch_decide_rows16(a, partial, row_stride, S, st);
     } else if (C <= 1024 && nt == 1)
         finish_select_wave_kernel<1><<<wave_blocks, 256, 0, st>>>(a, S);
     else if (C <= 1024 && nt == 2 && ((uintptr_t)partial & 7) == 0)
@@ -1250,7 +1303,8 @@ hipError_t launch_trigger(const float *scores, int64_t S, int C, int64_t row_str
 {
     if (S == 0) return hipSuccess;
     TriggerArgs a{scores, row_stride, C, cur_idx, observed, gain_threshold, error_threshold, best_idx, gain, reconf, adapt};
-    trigger_kernel<<<(unsigned)S, 256, 0, st>>>(a);
+    if (C <= 1024) launch_decide_rows16(a, scores, row_stride, S, st);
+    else trigger_kernel<<<(unsigned)S, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 

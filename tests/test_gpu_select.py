@@ -96,3 +96,28 @@ def test_trigger_matches_oracle_bit_for_bit():
     ab.ab_trigger(sc, torch.zeros(4, dtype=torch.int32, device=DEV), best, rec)
     torch.cuda.synchronize()
     assert best.tolist() == [1, 1, 0, 0] and rec.tolist() == [1, 0, 0, 0]
+
+
+@pytest.mark.parametrize("Cn,stride", [(1, 3), (63, 63), (64, 64), (65, 66), (128, 132), (255, 255), (256, 257), (512, 512),
+                                       (513, 515), (1023, 1023), (1024, 1024), (1025, 1025)])
+def test_trigger_row_layouts(Cn, stride):
+    """Edges of the row-length classes, both load widths, the work-group form above 1024 columns; a last wavefront with
+    one live row.  The arithmetic is IEEE single precision on both sides, so the comparison is exact."""
+    rng = np.random.default_rng(Cn * 7 + stride)
+    S = 33
+    sc = (1.0 + 0.2 * rng.standard_normal((S, stride))).astype(np.float32)
+    sc[:, Cn:] = 1e9
+    sc[1, :Cn] = np.nan
+    sc[2, :Cn] = 1.0
+    cur = rng.integers(-1, Cn + 1, S).astype(np.int32)
+    obs = (1.0 + 0.2 * rng.standard_normal(S)).astype(np.float32)
+    t = lambda a: torch.from_numpy(a).to(DEV)
+    best = torch.full((S,), -9, dtype=torch.int32, device=DEV)
+    gain = torch.zeros(S, dtype=torch.float32, device=DEV)
+    rec, ad = (torch.full((S,), 7, dtype=torch.uint8, device=DEV) for _ in range(2))
+    ab.ab_trigger(t(sc), t(cur), best, rec, observed=t(obs), gain=gain, adapt=ad, C_=Cn, row_stride=stride)
+    torch.cuda.synchronize()
+    rb, rg, rr, ra = orc.trigger(sc[:, :Cn].copy(), cur, obs)
+    g = gain.cpu().numpy()
+    assert (best.cpu().numpy() == rb).all() and ((g == rg) | (np.isnan(g) & np.isnan(rg))).all()
+    assert (rec.cpu().numpy().astype(bool) == rr).all() and (ad.cpu().numpy().astype(bool) == ra).all()
