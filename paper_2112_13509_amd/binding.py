@@ -1,12 +1,15 @@
-"""Thin ctypes binding of ``libautobyte.so`` (see ``include/autobyte.h``).
+"""Thin binding of ``libautobyte.so`` (see ``include/autobyte.h``).
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  PyTorch is
-used for device memory and streams.  There is no fallback: if the library is missing, or a tensor
-is not a contiguous ROCm tensor of the expected dtype, the call raises.
+used for device memory and streams.  The structures are ctypes; the entry points that a program calls
+per step check and convert their tensors in ``_native.so`` (``csrc/native.cpp``).  There is no
+fallback: if a library is missing, or a tensor is not a contiguous ROCm tensor of the expected dtype,
+the call raises.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import List, Optional, Sequence, Tuple
 
@@ -18,6 +21,7 @@ AB_MAX_STATS, AB_MAX_SCALARS, AB_MAX_HIDDEN, AB_MAX_LAYERS = 16, 40, 8, 12
 
 # AUTOBYTE_LIB: an already built variant of the library (the host-sanitizer run of the argument-check tests uses it)
 _LIB_PATH = os.environ.get("AUTOBYTE_LIB") or os.path.join(os.path.dirname(os.path.abspath(__file__)), "libautobyte.so")
+_NATIVE_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_native.so")
 _lib = None
 
 
@@ -211,22 +215,25 @@ def desc_from_workload(wl) -> ab_model_desc:
                      n_outputs=int(wl.W[-1].shape[0]), loss_kind=getattr(wl, "loss_kind", "mse"))
 
 
-def _ptr(t: Optional[torch.Tensor], dtype, what: str) -> Optional[int]:
-    if t is None:
-        return None
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
-        raise TypeError("%s must be a tensor on the GPU" % what)
-    if t.dtype != dtype:
-        raise TypeError("%s must have dtype %s, got %s" % (what, dtype, t.dtype))
-    if not t.is_contiguous():
-        raise TypeError("%s must be contiguous" % what)
-    return t.data_ptr()
+_native_mod = None
 
 
-def _stream_handle(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+def _native():
+    """The marshalling module, bound to the loaded library's entry points (once)."""
+    global _native_mod
+    if _native_mod is None:
+        lib = load()
+        if not os.path.exists(_NATIVE_PATH):
+            raise RuntimeError("_native.so is missing: run `python paper_2112_13509_amd/build.py` "
+                               "(or __graft_entry__.build()) first; there is no fallback path")
+        spec = importlib.util.spec_from_file_location(__package__ + "._native", _NATIVE_PATH)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.bind(*(C.cast(f, _vp).value for f in (
+            lib.ab_score_candidates, lib.ab_score_candidates_v, lib.ab_score_candidates_static, lib.ab_select_best,
+            lib.ab_trigger, lib.ab_online_update_tail, lib.ab_replay_mix)))
+        _native_mod = mod
+    return _native_mod
 
 
 class Params:
@@ -293,52 +300,11 @@ def ab_score_candidates(desc: ab_model_desc, params: Params, dyn: torch.Tensor, 
     ``layers_of`` (int32 [S], encoder models only): how many of the L padded layers each scenario really has.
     ``partition_bytes`` [P] and ``credit_mult`` [Q] are shared by all scenarios; given as [S, P] and [S, Q]
     every scenario brings its own grid."""
-    lib = load()
-    S = int(dyn.shape[0])
-    if layers_of is not None and layers_of.numel() != S:
-        raise ValueError("layers_of must have one entry per scenario")
-    st = ab_stats(_ptr(dyn, torch.float32, "dyn"), _ptr(scalars, torch.float32, "scalars"), S,
-                  _ptr(layers_of, torch.int32, "layers_of"))
-    per_scenario = partition_bytes.dim() == 2
-    if per_scenario and (credit_mult.dim() != 2 or partition_bytes.shape[0] != S or credit_mult.shape[0] != S):
-        raise ValueError("per-scenario grids must be [S, P] and [S, Q]")
-    P, Q = int(partition_bytes.shape[-1]), int(credit_mult.shape[-1])
-    gr = ab_grid(_ptr(partition_bytes, torch.float32, "partition_bytes"), P,
-                 _ptr(credit_mult, torch.float32, "credit_mult"), Q, 1 if per_scenario else 0)
-    if dyn.numel() != S * desc.n_layers * desc.n_stats or scalars.numel() != S * desc.n_scalars:
-        raise ValueError("dyn / scalars do not match the description")
-    for t, n, what in ((scores, S * P * Q, "scores"), (best_idx, S, "best_idx"), (best_score, S, "best_score")):
-        if t is not None and t.numel() != n:
-            raise ValueError("%s has %d elements, expected %d" % (what, t.numel(), n))
-    n_out = max(1, int(desc.n_outputs))
-    if v_best is not None and v_best.numel() != S * n_out:
-        raise ValueError("v_best has %d elements, expected %d" % (v_best.numel(), S * n_out))
-    if static_scratch:
-        if workspace is not None or v_best is not None:
-            raise ValueError("the static-scratch form takes neither a workspace nor v_best")
-        rc = lib.ab_score_candidates_static(C.byref(desc), C.byref(params.c), C.byref(st), C.byref(gr),
-                                            _ptr(scores, torch.float32, "scores"),
-                                            _ptr(best_idx, torch.int32, "best_idx"),
-                                            _ptr(best_score, torch.float32, "best_score"), _stream_handle(stream))
-        if check and rc != 0:
-            raise AutoByteError(rc, "ab_score_candidates_static")
-        return rc
-    ws_ptr = _ptr(workspace, torch.uint8, "workspace")
-    if v_best is not None:
-        rc = lib.ab_score_candidates_v(C.byref(desc), C.byref(params.c), C.byref(st), C.byref(gr),
-                                       _ptr(scores, torch.float32, "scores"), _ptr(best_idx, torch.int32, "best_idx"),
-                                       _ptr(best_score, torch.float32, "best_score"),
-                                       _ptr(v_best, torch.float32, "v_best"), ws_ptr,
-                                       0 if workspace is None else workspace.numel(), _stream_handle(stream))
-        if check and rc != 0:
-            raise AutoByteError(rc, "ab_score_candidates_v")
-        return rc
-    rc = lib.ab_score_candidates(C.byref(desc), C.byref(params.c), C.byref(st), C.byref(gr),
-                                 _ptr(scores, torch.float32, "scores"), _ptr(best_idx, torch.int32, "best_idx"),
-                                 _ptr(best_score, torch.float32, "best_score"), ws_ptr,
-                                 0 if workspace is None else workspace.numel(), _stream_handle(stream))
-    if check and rc != 0:
-        raise AutoByteError(rc, "ab_score_candidates")
+    rc = (_native_mod or _native()).score(desc, params.c, dyn, scalars, partition_bytes, credit_mult, scores, best_idx,
+                                          best_score, workspace, stream, layers_of, static_scratch, v_best)
+    if rc and check:
+        raise AutoByteError(rc, "ab_score_candidates_static" if static_scratch else
+                            "ab_score_candidates" if v_best is None else "ab_score_candidates_v")
     return rc
 
 
@@ -360,18 +326,8 @@ def ab_select_best(scores: torch.Tensor, best_idx: torch.Tensor, best_score: Opt
                    C_: Optional[int] = None, row_stride: Optional[int] = None, stream=None,
                    check: bool = True) -> int:
     """Per-row argmax of ``scores`` [S, row_stride] over the first ``C_`` columns."""
-    lib = load()
-    if scores.dim() != 2:
-        raise ValueError("scores must be 2-D")
-    S = int(scores.shape[0])
-    row_stride = int(scores.shape[1]) if row_stride is None else int(row_stride)
-    C_ = row_stride if C_ is None else int(C_)
-    if best_idx.numel() != S or (best_score is not None and best_score.numel() != S):
-        raise ValueError("best_idx / best_score must have one element per row")
-    rc = lib.ab_select_best(_ptr(scores, torch.float32, "scores"), S, C_, row_stride,
-                            _ptr(best_idx, torch.int32, "best_idx"),
-                            _ptr(best_score, torch.float32, "best_score"), _stream_handle(stream))
-    if check and rc != 0:
+    rc = (_native_mod or _native()).select(scores, best_idx, best_score, C_, row_stride, stream)
+    if rc and check:
         raise AutoByteError(rc, "ab_select_best")
     return rc
 
@@ -382,22 +338,9 @@ def ab_trigger(scores: torch.Tensor, current_idx: torch.Tensor, best_idx: torch.
                gain_threshold: float = 0.05, error_threshold: float = 0.10, C_: Optional[int] = None,
                row_stride: Optional[int] = None, stream=None, check: bool = True) -> int:
     """Choice plus the Optimization Trigger's two threshold tests on ``scores`` [S, row_stride]."""
-    lib = load()
-    if scores.dim() != 2:
-        raise ValueError("scores must be 2-D")
-    S = int(scores.shape[0])
-    row_stride = int(scores.shape[1]) if row_stride is None else int(row_stride)
-    C_ = row_stride if C_ is None else int(C_)
-    for t, what in ((current_idx, "current_idx"), (best_idx, "best_idx"), (reconfigure, "reconfigure"),
-                    (observed, "observed"), (gain, "gain"), (adapt, "adapt")):
-        if t is not None and t.numel() != S:
-            raise ValueError("%s must have one element per row" % what)
-    rc = lib.ab_trigger(_ptr(scores, torch.float32, "scores"), S, C_, row_stride,
-                        _ptr(current_idx, torch.int32, "current_idx"), _ptr(observed, torch.float32, "observed"),
-                        gain_threshold, error_threshold, _ptr(best_idx, torch.int32, "best_idx"),
-                        _ptr(gain, torch.float32, "gain"), _ptr(reconfigure, torch.uint8, "reconfigure"),
-                        _ptr(adapt, torch.uint8, "adapt"), _stream_handle(stream))
-    if check and rc != 0:
+    rc = (_native_mod or _native()).trigger(scores, current_idx, best_idx, reconfigure, observed, gain, adapt,
+                                            gain_threshold, error_threshold, C_, row_stride, stream)
+    if rc and check:
         raise AutoByteError(rc, "ab_trigger")
     return rc
 
@@ -407,19 +350,9 @@ def ab_online_update(desc: ab_model_desc, params: Params, x_raw: torch.Tensor, t
                      loss_out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                      stream=None, check: bool = True) -> int:
     """Enqueue one forward + backward + Adam step on the rows of ``x_raw`` [B, F]."""
-    lib = load()
-    B = int(x_raw.shape[0])
-    F = desc.n_layers * desc.n_stats + desc.n_scalars + 2
-    if x_raw.numel() != B * F or target.numel() != B * max(1, int(desc.n_outputs)):
-        raise ValueError("x_raw must be [B, %d] and target [B, n_outputs]" % F)
-    if params.step is None:
-        raise ValueError("params were not created with trainable=True")
-    rc = lib.ab_online_update(C.byref(desc), C.byref(params.c), _ptr(x_raw, torch.float32, "x_raw"),
-                              _ptr(target, torch.float32, "target"), B, lr, beta1, beta2, eps,
-                              _ptr(loss_out, torch.float32, "loss_out"),
-                              _ptr(workspace, torch.uint8, "workspace"),
-                              0 if workspace is None else workspace.numel(), _stream_handle(stream))
-    if check and rc != 0:
+    rc = (_native_mod or _native()).update(desc, params.c, params.step is not None, x_raw, target, 0, lr, beta1, beta2, eps,
+                                           loss_out, workspace, stream)
+    if rc and check:
         raise AutoByteError(rc, "ab_online_update")
     return rc
 
@@ -429,19 +362,9 @@ def ab_online_update_tail(desc: ab_model_desc, params: Params, x_raw: torch.Tens
                           eps: float = 1e-8, loss_out: Optional[torch.Tensor] = None,
                           workspace: Optional[torch.Tensor] = None, stream=None, check: bool = True) -> int:
     """The online step with scorer layers below ``first_trainable`` frozen."""
-    lib = load()
-    B = int(x_raw.shape[0])
-    F = desc.n_layers * desc.n_stats + desc.n_scalars + 2
-    if x_raw.numel() != B * F or target.numel() != B * max(1, int(desc.n_outputs)):
-        raise ValueError("x_raw must be [B, %d] and target [B, n_outputs]" % F)
-    if params.step is None:
-        raise ValueError("params were not created with trainable=True")
-    rc = lib.ab_online_update_tail(C.byref(desc), C.byref(params.c), _ptr(x_raw, torch.float32, "x_raw"),
-                                   _ptr(target, torch.float32, "target"), B, int(first_trainable),
-                                   lr, beta1, beta2, eps, _ptr(loss_out, torch.float32, "loss_out"),
-                                   _ptr(workspace, torch.uint8, "workspace"),
-                                   0 if workspace is None else workspace.numel(), _stream_handle(stream))
-    if check and rc != 0:
+    rc = (_native_mod or _native()).update(desc, params.c, params.step is not None, x_raw, target, first_trainable, lr, beta1,
+                                           beta2, eps, loss_out, workspace, stream)
+    if rc and check:
         raise AutoByteError(rc, "ab_online_update_tail")
     return rc
 
@@ -450,23 +373,7 @@ def ab_replay_mix(x_new: Optional[torch.Tensor], target_new: Optional[torch.Tens
                   target_old: Optional[torch.Tensor], pick: torch.Tensor, x_out: torch.Tensor,
                   target_out: torch.Tensor, stream=None, check: bool = True) -> int:
     """Gather a minibatch from a pool of new rows (pick >= 0) and a pool of old rows (pick < 0: row -pick-1)."""
-    lib = load()
-    B, F = int(x_out.shape[0]), int(x_out.shape[1])
-    n_new = 0 if x_new is None else int(x_new.shape[0])
-    n_old = 0 if x_old is None else int(x_old.shape[0])
-    for t_ in (x_new, x_old):
-        if t_ is not None and int(t_.shape[1]) != F:
-            raise ValueError("pools and output must have the same row width")
-    if pick.numel() != B or target_out.numel() % B != 0:
-        raise ValueError("pick must have one entry and target_out n_outputs entries per output row")
-    n_out = target_out.numel() // B
-    for t_, n_ in ((target_new, n_new), (target_old, n_old)):
-        if t_ is not None and t_.numel() != n_ * n_out:
-            raise ValueError("pool targets must have %d entries per row" % n_out)
-    rc = lib.ab_replay_mix(_ptr(x_new, torch.float32, "x_new"), _ptr(target_new, torch.float32, "target_new"), n_new,
-                           _ptr(x_old, torch.float32, "x_old"), _ptr(target_old, torch.float32, "target_old"), n_old,
-                           _ptr(pick, torch.int32, "pick"), B, F, n_out, _ptr(x_out, torch.float32, "x_out"),
-                           _ptr(target_out, torch.float32, "target_out"), _stream_handle(stream))
-    if check and rc != 0:
+    rc = (_native_mod or _native()).replay_mix(x_new, target_new, x_old, target_old, pick, x_out, target_out, stream)
+    if rc and check:
         raise AutoByteError(rc, "ab_replay_mix")
     return rc

@@ -1,4 +1,4 @@
-"""Builds ``libautobyte.so`` (HIP, gfx950) next to this file.  Run as a script or call :func:`build`."""
+"""Builds ``libautobyte.so`` (HIP, gfx950) and ``_native.so`` next to this file.  Run as a script or call :func:`build`."""
 from __future__ import annotations
 
 import os
@@ -29,11 +29,34 @@ def _compile(src: str, objdir: str, extra=(), suffix: str = ".o") -> str:
     return obj
 
 
+def build_native() -> str:
+    """``_native.so``: the argument marshalling of binding.py (host code only; needs torch's headers)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    out = os.path.join(HERE, "_native.so")
+    tmp = out + ".tmp%d" % os.getpid()
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += ["-isystem" + i for i in inc] + [os.path.join(CSRC, "native.cpp"), "-o", tmp]
+    cmd += ["-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError("g++ failed on native.cpp")
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=5) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
+        native = ex.submit(build_native)
         objs = list(ex.map(lambda s: _compile(s, objdir), SOURCES))
+        native.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     res = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs,
                          capture_output=True, text=True)
