@@ -52,11 +52,13 @@ static ab_status check_desc(const ab_model_desc *d)
     return AB_OK;
 }
 
+enum { BIG_TILE = 1, BIG_SPAN = 2 };    // gemm_big.hip; gemm_span.hip (row tiles that span scenarios)
+
 struct ScorePlan {
     int dtype, Fs, F, Kp, D, base;
     int H[AB_MAX_HIDDEN];
     int tile[AB_MAX_HIDDEN];      // tile of hidden GEMM k (k >= 1)
-    int big[AB_MAX_HIDDEN];       // hidden GEMM k runs on the 256x256 bf16 kernel
+    int big[AB_MAX_HIDDEN];       // hidden GEMM k runs on a 256x256 bf16 kernel: BIG_TILE, BIG_SPAN, or 0
     int tile_a;                   // tile of the scenario-term GEMM
     int nt_last;
     int64_t chunk_scen, chunk_rows;
@@ -92,8 +94,13 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
     p->tile_a = pick_tile(S, p->H[0]);
     for (int k = 1; k < p->D; ++k) {
         p->tile[k] = pick_tile(p->chunk_rows, p->H[k]);
-        p->big[k] = p->dtype == AB_BF16 && p->H[k] % 256 == 0 && (k > 1 || C % 256 == 0) &&
-                    ((p->chunk_rows + 255) / 256) * (p->H[k] / 256) >= 64;   // (measured crossover against the generic tiles)
+        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 ||
+            ((p->chunk_rows + 255) / 256) * (p->H[k] / 256) < 64)            // (measured crossover against the generic tiles)
+            continue;
+        // the generating kernel of gemm_big.hip has one scenario per row tile; what it fetches a tile ahead needs three
+        // slabs of 64 inputs to be sure to have arrived, so two slabs go to the other one as well
+        if (k > 1 || (C % 256 == 0 && p->H[0] != 128)) p->big[k] = BIG_TILE;
+        else if (gemm_span_shape(C, p->H[0], p->H[k])) p->big[k] = BIG_SPAN;
     }
     p->nt_last = 1;
     if (p->D >= 2) {
@@ -343,7 +350,9 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                                      : (last ? "gemm_hidden_last" : "gemm_hidden_mid"),
                               2.0 * rows * p.H[k] * p.H[k - 1], 0, st);
                 const int amode = k == 1 ? AMODE_GEN : AMODE_LOAD, epi = last ? EPI_SCORE : EPI_STORE;
-                if (p.big[k] && gemm_big_supported(dt, amode, epi, g))
+                if (p.big[k] == BIG_SPAN)
+                    AB_HIP(launch_gemm_span(epi, g, st));
+                else if (p.big[k] && gemm_big_supported(dt, amode, epi, g))
                     AB_HIP(launch_gemm_big(amode, epi, g, st));
                 else if (p.big[k])
                     return AB_ERR_UNSUPPORTED;     // cannot happen: the plan checked the same conditions

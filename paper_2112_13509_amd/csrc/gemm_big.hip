@@ -21,32 +21,10 @@
 //     Waits on the DMA use exact vmcnt counts (loads retire in issue order), never a full drain.
 //   - Stores go through an LDS staging tile (row stride 528 bytes) and leave as 16-byte, fully
 //     coalesced writes.
-#include "internal.hpp"
+#include "stream_util.hpp"
 #include <type_traits>
 
 namespace ab {
-
-typedef __attribute__((address_space(3))) void lds_void;
-typedef const __attribute__((address_space(1))) void global_void;
-typedef float f32x8_unaligned __attribute__((ext_vector_type(8), aligned(4)));
-
-typedef __attribute__((address_space(4))) f32x8_unaligned const_f32x8;   // read-only for the whole launch: scalar loads
-// Eight consecutive floats at a wave-uniform address, fetched through the scalar cache into scalar registers.
-__device__ __forceinline__ f32x8_unaligned scalar_load8(const float *p)
-{
-    f32x8_unaligned v = *(const const_f32x8 *)(uintptr_t)p;
-    asm volatile("" : "+s"(v));
-    return v;
-}
-
-// 64 lanes x 16 bytes; lane l's data lands at lds_uniform_dst + 16*l.  STREAM marks the access
-// non-temporal: activation panels and outputs pass through L2 once per XCD and should not push the
-// weight matrix (re-read by every tile) out of it.
-template <bool STREAM>
-__device__ __forceinline__ void dma16(const void *gsrc, void *lds_uniform_dst)
-{
-    __builtin_amdgcn_global_load_lds((global_void *)gsrc, (lds_void *)lds_uniform_dst, 16, 0, STREAM ? 2 : 0);
-}
 
 template <int AMODE, int EPI>
 __global__ __launch_bounds__(512) void gemm_big_kernel(const GemmArgs g)
@@ -189,16 +167,6 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const GemmArgs g)
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     acc[jn][im], 0, 0, 0);
     };
-
-    // Scheduling hints: keep the source order of the phases (fence) and, inside a phase, alternate one
-    // matrix instruction with one LDS fragment read so the reads for the next quarter are issued under
-    // the current quarter's matrix work instead of being sunk in front of their first use.
-#define AB_FENCE() __builtin_amdgcn_sched_barrier(0)
-#define AB_MFMA_DS_PAIR() do { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); \
-                               __builtin_amdgcn_sched_group_barrier(0x100, 1, 0); } while (0)
-#define AB_INTERLEAVE_6() do { AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); \
-                               AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); \
-                               __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); } while (0)
 
     // ---- prologue.  Issue order fixes what a vmcnt(n) wait leaves outstanding (loads retire in order).
     if constexpr (AMODE == AMODE_LOAD) {
@@ -348,19 +316,6 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const GemmArgs g)
 //   - bias (and output weights) are read through the scalar cache in the epilogue, so no ordinary
 //     vector load has to be waited for while slab fetches are in flight.
 //
-// LDS stores the compiler does not see as such: it orders every LDS store it knows of behind all
-// global->LDS DMA in flight (a full vmcnt drain), which the staging writes of the epilogue must not do;
-// the stage they go to has been retired by the barrier before.  LDS operations of a wavefront execute
-// in order, so the reads that follow see the data.
-__device__ __forceinline__ void lds_write8(void *p, uint2 v)
-{
-    asm volatile("ds_write_b64 %0, %1" ::"v"((uint32_t)(uintptr_t)(lds_void *)p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void lds_write4(void *p, float v)
-{
-    asm volatile("ds_write_b32 %0, %1" ::"v"((uint32_t)(uintptr_t)(lds_void *)p), "v"(v) : "memory");
-}
-
 template <int EPI, bool COL_REGS>
 __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
 {
@@ -530,16 +485,6 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
                 }
             }
     };
-
-    // Scheduling inside a quarter that also issues slab fetches: 8 matrix instructions, 6 fragment reads and
-    // 2 (or 4) DMA requests, spread evenly.
-#define AB_MFMA_VMEM_PAIR() do { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); \
-                                 __builtin_amdgcn_sched_group_barrier(0x010, 1, 0); } while (0)
-#define AB_INTERLEAVE_6_V2() do { AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); \
-                                  AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_DS_PAIR(); } while (0)
-#define AB_INTERLEAVE_6_V4() do { __builtin_amdgcn_sched_group_barrier(0x100, 2, 0); \
-                                  AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); \
-                                  AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); } while (0)
 
     // Order of the memory operations of a wavefront (loads and stores retire in order).  The quarters are
     // straight-line code on purpose: a branch around matrix instructions makes the compiler copy accumulators.
@@ -749,16 +694,7 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
 //   - memory operations of a wavefront: W(j+2) x4 in the last quarter of slab j; at a tile border
 //     the stores x16 and the vector fetch x3 follow.  Inside a tile the wait before a slab's barrier
 //     is therefore for everything, at a tile's first slab 19 operations may stay in flight.
-// Needs K <= 1024 (vector area) and at least two slabs.
-__device__ __forceinline__ void lds_write16(void *p, i32x4 v)
-{
-    asm volatile("ds_write_b128 %0, %1" ::"v"((uint32_t)(uintptr_t)(lds_void *)p), "v"(v) : "memory");
-}
-__device__ __forceinline__ void dma4(const void *gsrc, void *lds_uniform_dst)   // 64 lanes x 4 bytes
-{
-    __builtin_amdgcn_global_load_lds((global_void *)gsrc, (lds_void *)lds_uniform_dst, 4, 0, 0);
-}
-
+// Needs K <= 1024 (vector area) and at least three slabs.
 template <int EPI, bool COL_REGS, bool SHARE>
 __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
 {
@@ -1230,9 +1166,10 @@ hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st)
         return epi == EPI_STORE ? launch_big_one<AMODE_LOAD, EPI_STORE>(g, st)
                                 : launch_big_one<AMODE_LOAD, EPI_SCORE>(g, st);
     }
-    // generated operand: the streaming kernel needs the bias, the vector area bounds K, two slabs at least,
-    // 32-bit row arithmetic and 4-byte DMA sources
-    if (g.bias && g.K <= 1024 && g.K >= 128 && g.M < (1LL << 31))
+    // generated operand: the streaming kernel needs the bias, the vector area bounds K, 32-bit row arithmetic, 4-byte
+    // DMA sources and three slabs (its wait at a tile's first slab leaves the next tile's vectors in flight, and with
+    // two slabs the next one would already read them)
+    if (g.bias && g.K <= 1024 && g.K >= 192 && g.M < (1LL << 31))
         return epi == EPI_STORE ? launch_stream_gen<EPI_STORE>(g, st) : launch_stream_gen<EPI_SCORE>(g, st);
     return epi == EPI_STORE ? launch_big_one<AMODE_GEN, EPI_STORE>(g, st)
                             : launch_big_one<AMODE_GEN, EPI_SCORE>(g, st);

@@ -68,6 +68,10 @@ hipError_t launch_gemm(int dtype, int tile, int amode, int epi, GemmArgs g, hipS
 bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g);
 hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st);
 
+// The same product with a generated operand whose row tiles span scenarios (gemm_span.hip).
+bool gemm_span_shape(int32_t C, int H_in, int H_out);
+hipError_t launch_gemm_span(int epi, GemmArgs g, hipStream_t st);
+
 hipError_t launch_encode_stats(int dtype, const ab_model_desc *d, const float *dyn, const float *scal,
                                void *xs, int64_t S, int ld, int col0, int with_stats, hipStream_t st);
 hipError_t launch_prep_layer1(int dtype, const ab_model_desc *d, const void *W1, const float *b1, int F, int Fs,
