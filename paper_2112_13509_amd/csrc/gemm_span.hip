@@ -20,7 +20,7 @@
 //
 // Bound by the matrix cores.  Before this kernel these shapes took the generic 256 x 256 tile, whose operand loads are
 // waited for one by one: 198135 rows x 1024 x 1024 (777 scenarios x 255 candidates) took 1237 us a launch, about 390 us
-here; the whole pass of that network (three hidden products) 1872 -> 1026 us, others of these shapes 1.2 - 2.3 times faster.
+// here; the whole pass of that network (three hidden products) 1872 -> 1026 us, others of these shapes 1.2 - 2.3 times faster.
 #include "stream_util.hpp"
 #include <type_traits>
 
