@@ -1,13 +1,17 @@
 // Online adaptation step (Section 3.2 "Offline training online adapting"; loss of Eq. 2 as mean
 // squared error): forward with saved activations, exact back-propagation, Adam.
 //
-// Every matrix product is brought to the K-contiguous form of gemm_core.hpp by keeping transposed
+// Two forms.  The row-block form (update_rows.hip) takes the networks whose weights fit an XCD's L2: a work-group carries
+// a block of batch rows through all layers and back, one launch makes all weight gradients.  The layer-by-layer form below
+// takes the others.
+//
+// In the latter every matrix product is brought to the K-contiguous form of gemm_core.hpp by keeping transposed
 // copies next to the row-major ones (written by the producing kernel's epilogue):
 //   forward   h_k      = relu(h_{k-1} W_k^T + b_k)          A = h_{k-1} [B, in],   B-op = W_k [out, in]
 //   dW_k      = d_k^T h_{k-1}                               A = d_k^T [out, B],    B-op = h_{k-1}^T [in, B]   (split over B)
 //   d_{k-1}   = (d_k W_k) * [h_{k-1} > 0]                   A = d_k [B, out],      B-op = W_k^T [in, out]
 // The batch dimension is padded to a multiple of 64 in the transposed buffers (zero columns).
-#include "internal.hpp"
+#include "update_rows.hpp"
 #include <string.h>
 
 namespace ab {
@@ -27,6 +31,8 @@ struct UpdatePlan {
     size_t off_wt[AB_MAX_HIDDEN], off_h[AB_MAX_HIDDEN], off_ht[AB_MAX_HIDDEN];
     size_t off_d[AB_MAX_HIDDEN], off_dt[AB_MAX_HIDDEN], off_gw[AB_MAX_HIDDEN], off_gb[AB_MAX_HIDDEN];
     size_t total;
+    bool rows;                          // row-block form
+    int grad_tile, rows_splits;         // its gradient launch: tile width, batch split
 };
 
 static int update_tile(int64_t M, int N)
@@ -49,14 +55,44 @@ static void plan_update(const ab_model_desc *d, int64_t B, UpdatePlan *p)
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     p->off_scal = take(64);
+    RowsArgs shape;
+    memset(&shape, 0, sizeof(shape));
+    shape.D = p->D; shape.n_out = p->n_out;
+    int64_t tiles64 = 0;
+    for (int k = 0; k < p->D; ++k) {
+        p->H[k] = d->hidden[k];
+        p->in_w[k] = (k == 0) ? p->Kp : d->hidden[k - 1];
+        shape.l[k].in = p->in_w[k]; shape.l[k].out = p->H[k];
+        tiles64 += (int64_t)(p->H[k] / 64) * (p->in_w[k] / 64);
+    }
+    p->rows = update_rows_supported(shape, p->dtype);
+    if (p->rows) {
+        // eight splits, one per XCD, unless the batch is shorter; 128-wide tiles once they occupy the chip
+        const int64_t slabs = p->Bp / 64;
+        p->rows_splits = 8;
+        while (p->rows_splits > slabs) p->rows_splits /= 2;
+        p->grad_tile = tiles64 * p->rows_splits >= 512 ? 128 : 64;
+        p->off_x = take((size_t)p->Bp * p->Kp * es);
+        p->off_dout = take((size_t)p->Bp * p->n_out * 4);
+        p->off_lossrow = take((size_t)p->Bp * 4);
+        p->off_wt[0] = take((size_t)p->H[0] * p->Kp * es);
+        for (int k = 0; k < p->D; ++k) {
+            p->off_h[k] = take((size_t)p->Bp * p->H[k] * es);
+            p->off_d[k] = take((size_t)p->Bp * p->H[k] * es);
+            p->off_gw[k] = take((size_t)p->rows_splits * p->H[k] * p->in_w[k] * 4);
+            p->off_gb[k] = take((size_t)p->rows_splits * p->H[k] * 4);
+        }
+        p->off_gwout = take((size_t)p->rows_splits * p->n_out * p->H[p->D - 1] * 4);
+        p->off_gbout = take((size_t)AB_MAX_OUTPUTS * 4);
+        p->total = off;
+        return;
+    }
     p->off_x = take((size_t)B * p->Kp * es);
     p->off_xt = take((size_t)p->Kp * p->Bp * es);
     p->off_yhat = take((size_t)B * p->n_out * 4);
     p->off_dout = take((size_t)p->Bp * p->n_out * 4);
     p->off_lossrow = take((size_t)p->Bp * 4);
     for (int k = 0; k < p->D; ++k) {
-        p->H[k] = d->hidden[k];
-        p->in_w[k] = (k == 0) ? p->Kp : d->hidden[k - 1];
         const int tiles = (p->H[k] / 64) * (p->in_w[k] / 64);
         const int slabs = (int)(p->Bp / slab_k(p->dtype));
         int s = 512 / tiles;
@@ -415,9 +451,9 @@ __device__ __forceinline__ void bias_grad_block(const BiasGradArgs &a, unsigned 
 // thread transforms one pair of columns for eight rows (so it looks its two transforms up once), writes the
 // row-major pairs, and parks the values in LDS, from which the transposed tile leaves as 32- or 64-byte
 // pieces of a row of x_t.  Rows at and beyond B of the tile are written as zeros into x_t (ld_t is the batch
-// rounded up to 64).
+// rounded up to 64) and, up to x_rows, into x.
 struct EncodeRowsArgs {
-    const float *x_raw; void *x; void *x_t; int64_t B, ld_t; int32_t F, ld, col_tiles;
+    const float *x_raw; void *x; void *x_t; int64_t B, ld_t, x_rows; int32_t F, ld, col_tiles;
     int32_t n_stat, n_stats_per_layer, n_scal;
     ab_enc enc_stat[AB_MAX_STATS];
     ab_enc enc_scal[AB_MAX_SCALARS];
@@ -457,10 +493,13 @@ __device__ __forceinline__ void encode_rows_block(const EncodeRowsArgs &a, unsig
         if (row < a.B) {
             if (j0 < a.F) v0 = phi(raw0[i], e[0]);
             if (j0 + 1 < a.F) v1 = phi(raw1[i], e[1]);
+        }
+        if (row < a.x_rows) {
             const int64_t o = row * a.ld + j0;
             if constexpr (sizeof(T) == 2) ((uint32_t *)a.x)[o >> 1] = pack_bf16x2(v0, v1);
             else ((f32x2 *)a.x)[o >> 1] = f32x2{v0, v1};
         }
+        if (!a.x_t) continue;
         if constexpr (sizeof(T) == 2) {
             const uint32_t pk = pack_bf16x2(v0, v1);
             ((uint16_t *)tile)[(2 * cp) * LD_TILE + rl] = (uint16_t)(pk & 0xffffu);
@@ -470,8 +509,8 @@ __device__ __forceinline__ void encode_rows_block(const EncodeRowsArgs &a, unsig
             ((float *)tile)[(2 * cp + 1) * LD_TILE + rl] = v1;
         }
     }
-    __syncthreads();
     if (!a.x_t) return;
+    __syncthreads();
     const int col = t >> 2, rc = (t & 3) * 16;
     const int64_t o = (int64_t)(c0 + col) * a.ld_t + r0 + rc;
     if constexpr (sizeof(T) == 2) {
@@ -597,6 +636,46 @@ __global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a)
 }
 
 template <typename T>
+static ab_status launch_adam(const UpdatePlan &p, ab_params *prm, const float *scal, float lr, float beta1, float beta2,
+                             float eps, unsigned char *ws, int k0, hipStream_t st)
+{
+    const int D = p.D;
+    const double esz = (double)elem_size(p.dtype);
+    float *gw_out = (float *)(ws + p.off_gwout), *gb_out = (float *)(ws + p.off_gbout);
+    AdamArgs a;
+    memset(&a, 0, sizeof(a));
+    int64_t start = 0;
+    auto add = [&](float *w, float *m, float *v, void *wc, const float *g, int rows, int cols, int ldg,
+                   int splits, int64_t stride) {
+        AdamArgs::Tn &t = a.tn[a.n++];
+        t.w = w; t.m = m; t.v = v; t.w_compute = wc; t.g = g; t.rows = rows; t.cols = cols; t.ldg = ldg;
+        t.splits = splits; t.split_stride = stride;
+        // widest vector that divides the row length and the gradient rows' pitch and that every pointer is aligned to
+        const uintptr_t ptrs = (uintptr_t)w | (uintptr_t)m | (uintptr_t)v | (uintptr_t)g | (uintptr_t)wc;
+        t.vw = (cols % 4 == 0 && ldg % 4 == 0 && stride % 4 == 0 && ptrs % 16 == 0) ? 4
+             : (cols % 2 == 0 && ldg % 2 == 0 && stride % 2 == 0 && ptrs % 8 == 0) ? 2 : 1;
+        t.start = start; start += (int64_t)rows * cols / t.vw;
+    };
+    for (int k = k0; k < D; ++k) {
+        const int cols = (k == 0) ? p.F : p.H[k - 1];
+        add(prm->W_master[k], prm->adam_mW[k], prm->adam_vW[k], (void *)prm->W[k], (float *)(ws + p.off_gw[k]),
+            p.H[k], cols, p.in_w[k], p.rows ? p.rows_splits : p.splits[k], (int64_t)p.H[k] * p.in_w[k]);
+        add(prm->b[k], prm->adam_mb[k], prm->adam_vb[k], nullptr, (float *)(ws + p.off_gb[k]), 1, p.H[k], p.H[k],
+            p.rows ? p.rows_splits : 1, p.H[k]);
+    }
+    add(prm->W_master[D], prm->adam_mW[D], prm->adam_vW[D], (void *)prm->W[D], gw_out, p.n_out, p.H[D - 1], p.H[D - 1],
+        p.rows ? p.rows_splits : 1, (int64_t)p.n_out * p.H[D - 1]);
+    add(prm->b[D], prm->adam_mb[D], prm->adam_vb[D], nullptr, gb_out, 1, p.n_out, p.n_out, 1, 0);
+    a.total = start; a.scal = scal; a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps;
+    double n_param = 0.0;
+    for (int i = 0; i < a.n; ++i) n_param += (double)a.tn[i].rows * a.tn[i].cols;
+    TraceScope ts("upd_adam", n_param * (28.0 + esz), 1, st);
+    adam_kernel<T><<<(unsigned)((start + 255) / 256), 256, 0, st>>>(a);
+    AB_HIP(hipGetLastError());
+    return AB_OK;
+}
+
+template <typename T>
 static ab_status run_update(const ab_model_desc *d, ab_params *prm, const UpdatePlan &p, const float *x_raw,
                             const float *target, float lr, float beta1, float beta2, float eps,
                             float *loss_out, unsigned char *ws, int k0, hipStream_t st)
@@ -613,7 +692,7 @@ static ab_status run_update(const ab_model_desc *d, ab_params *prm, const Update
     {   // launch 1: rows -> x, x^T; padded copy of W_1, transposed hidden weights, zero padding; step counter
         EncodeRowsArgs e;
         memset(&e, 0, sizeof(e));
-        e.x_raw = x_raw; e.x = x; e.x_t = xt; e.B = B; e.ld_t = Bp; e.F = p.F; e.ld = p.Kp; e.col_tiles = p.Kp / 64;
+        e.x_raw = x_raw; e.x = x; e.x_t = p.rows ? nullptr : xt; e.B = B; e.ld_t = Bp; e.x_rows = p.rows ? Bp : B; e.F = p.F; e.ld = p.Kp; e.col_tiles = p.Kp / 64;
         e.n_stat = d->n_layers * d->n_stats; e.n_stats_per_layer = d->n_stats; e.n_scal = d->n_scalars;
         for (int i = 0; i < AB_MAX_STATS; ++i) e.enc_stat[i] = d->enc_stat[i];
         for (int i = 0; i < AB_MAX_SCALARS; ++i) e.enc_scal[i] = d->enc_scalar[i];
@@ -630,10 +709,10 @@ static ab_status run_update(const ab_model_desc *d, ab_params *prm, const Update
             j.kind = kind; j.start = start; start += n;
         };
         add(JOB_PAD_COPY, prm->W[0], ws + p.off_wt[0], p.H[0], p.F, p.F, p.Kp, (int64_t)p.H[0] * p.Kp);
-        for (int k = (k0 > 0 ? k0 + 1 : 1); k < D; ++k)      // W_k^T is the operand of the delta of layer k - 1
+        for (int k = (k0 > 0 ? k0 + 1 : 1); k < D && !p.rows; ++k)      // W_k^T is the operand of the delta of layer k - 1
             add(JOB_TRANSPOSE, prm->W[k], ws + p.off_wt[k], p.H[k], p.H[k - 1], p.H[k - 1], p.H[k],
                 (int64_t)p.H[k] * p.H[k - 1]);
-        if (Bp > B) {                                        // (x^T gets its zero columns from the row transform)
+        if (Bp > B && !p.rows) {                             // (x^T gets its zero columns from the row transform)
             for (int k = 0; k < D; ++k) {
                 add(JOB_ZERO_COLS, nullptr, ws + p.off_ht[k], p.H[k], (int)B, 0, (int)Bp, (int64_t)p.H[k] * (Bp - B));
                 add(JOB_ZERO_COLS, nullptr, ws + p.off_dt[k], p.H[k], (int)B, 0, (int)Bp, (int64_t)p.H[k] * (Bp - B));
@@ -681,6 +760,43 @@ static ab_status run_update(const ab_model_desc *d, ab_params *prm, const Update
         adam_kernel<T><<<(unsigned)((a.total + 255) / 256), 256, 0, st>>>(a);
         AB_HIP(hipGetLastError());
         return AB_OK;
+    }
+    if (p.rows) {
+        double flops = 0.0, grad_flops = 0.0;
+        RowsArgs a;
+        memset(&a, 0, sizeof(a));
+        a.x = x; a.D = D; a.k0 = k0; a.n_out = p.n_out; a.loss_kind = d->loss_kind; a.B = B;
+        GradsArgs gr;
+        memset(&gr, 0, sizeof(gr));
+        int tiles = 0;
+        for (int k = 0; k < D; ++k) {
+            a.l[k].W = k == 0 ? (const void *)(ws + p.off_wt[0]) : prm->W[k]; a.l[k].b = prm->b[k];
+            a.l[k].h = ws + p.off_h[k]; a.l[k].d = ws + p.off_d[k];
+            a.l[k].in = p.in_w[k]; a.l[k].out = p.H[k];
+            flops += 2.0 * B * p.H[k] * p.in_w[k] * (k > k0 ? 2 : 1);
+            if (k < k0) continue;
+            GradsArgs::L &l = gr.l[gr.n++];
+            l.d = ws + p.off_d[k]; l.h_in = k == 0 ? x : (const void *)(ws + p.off_h[k - 1]);
+            l.gw = (float *)(ws + p.off_gw[k]); l.gb = (float *)(ws + p.off_gb[k]);
+            l.H = p.H[k]; l.in_w = p.in_w[k]; l.start = tiles;
+            tiles += (p.H[k] + p.grad_tile - 1) / p.grad_tile * ((p.in_w[k] + p.grad_tile - 1) / p.grad_tile);
+            grad_flops += 2.0 * B * p.H[k] * p.in_w[k];
+        }
+        a.w_out = prm->W[D]; a.b_out = prm->b[D]; a.target = target; a.dout = dout; a.lossrow = (float *)(ws + p.off_lossrow);
+        gr.splits = p.rows_splits; gr.B = B; gr.Bp = Bp; gr.h_last = ws + p.off_h[D - 1]; gr.dout = dout; gr.lossrow = a.lossrow;
+        gr.gw_out = gw_out; gr.gb_out = gb_out; gr.loss_out = loss_out; gr.H_last = p.H[D - 1]; gr.n_out = p.n_out;
+        gr.out_splits = p.rows_splits;
+        gr.n_out_blocks = (unsigned)(p.H[D - 1] / 64 * gr.out_splits);
+        gr.n_tile_blocks = (unsigned)(tiles * p.rows_splits);
+        {
+            TraceScope ts("upd_gemm_rows", flops, 0, st);
+            AB_HIP(launch_update_rows(dt, a, st));
+        }
+        {
+            TraceScope ts("upd_gemm_grads", grad_flops, 0, st);
+            AB_HIP(launch_update_grads(dt, p.grad_tile, gr, st));
+        }
+        return launch_adam<T>(p, prm, scal, lr, beta1, beta2, eps, ws, k0, st);
     }
     // forward
     for (int k = 0; k < D; ++k) {
@@ -799,37 +915,7 @@ static ab_status run_update(const ab_model_desc *d, ab_params *prm, const Update
         }
         AB_HIP(launch_group(gr, "upd_gemm_dw_bias"));
     }
-    {
-        AdamArgs a;
-        memset(&a, 0, sizeof(a));
-        int64_t start = 0;
-        auto add = [&](float *w, float *m, float *v, void *wc, const float *g, int rows, int cols, int ldg,
-                       int splits, int64_t stride) {
-            AdamArgs::Tn &t = a.tn[a.n++];
-            t.w = w; t.m = m; t.v = v; t.w_compute = wc; t.g = g; t.rows = rows; t.cols = cols; t.ldg = ldg;
-            t.splits = splits; t.split_stride = stride;
-            // widest vector that divides the row length and the gradient rows' pitch and that every pointer is aligned to
-            const uintptr_t ptrs = (uintptr_t)w | (uintptr_t)m | (uintptr_t)v | (uintptr_t)g | (uintptr_t)wc;
-            t.vw = (cols % 4 == 0 && ldg % 4 == 0 && stride % 4 == 0 && ptrs % 16 == 0) ? 4
-                 : (cols % 2 == 0 && ldg % 2 == 0 && stride % 2 == 0 && ptrs % 8 == 0) ? 2 : 1;
-            t.start = start; start += (int64_t)rows * cols / t.vw;
-        };
-        for (int k = k0; k < D; ++k) {
-            const int cols = (k == 0) ? p.F : p.H[k - 1];
-            add(prm->W_master[k], prm->adam_mW[k], prm->adam_vW[k], (void *)prm->W[k], (float *)(ws + p.off_gw[k]),
-                p.H[k], cols, p.in_w[k], p.splits[k], (int64_t)p.H[k] * p.in_w[k]);
-            add(prm->b[k], prm->adam_mb[k], prm->adam_vb[k], nullptr, (float *)(ws + p.off_gb[k]), 1, p.H[k], p.H[k], 1, 0);
-        }
-        add(prm->W_master[D], prm->adam_mW[D], prm->adam_vW[D], (void *)prm->W[D], gw_out, p.n_out, p.H[D - 1], p.H[D - 1], 1, 0);
-        add(prm->b[D], prm->adam_mb[D], prm->adam_vb[D], nullptr, gb_out, 1, p.n_out, p.n_out, 1, 0);
-        a.total = start; a.scal = scal; a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.eps = eps;
-        double n_param = 0.0;
-        for (int i = 0; i < a.n; ++i) n_param += (double)a.tn[i].rows * a.tn[i].cols;
-        TraceScope ts("upd_adam", n_param * (28.0 + esz), 1, st);
-        adam_kernel<T><<<(unsigned)((start + 255) / 256), 256, 0, st>>>(a);
-        AB_HIP(hipGetLastError());
-    }
-    return AB_OK;
+    return launch_adam<T>(p, prm, scal, lr, beta1, beta2, eps, ws, k0, st);
 }
 
 // Minibatch assembled from two pools of raw rows (fresh observations and the offline set): one wavefront per
