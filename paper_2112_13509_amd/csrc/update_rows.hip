@@ -11,7 +11,6 @@
 // registers take 13 us, their 16 rows at a power-of-two pitch fall on few L2 channels).
 #include "update_rows.hpp"
 #include "stream_util.hpp"
-#include <type_traits>
 
 namespace ab {
 
@@ -47,17 +46,40 @@ __device__ __forceinline__ f32x4 mma16(const i32x4 &w, const i32x4 &x, f32x4 acc
 }
 
 // Four bf16 down a column: sixteen lanes read 4 rows x 16 columns (8 bytes each), lane i ends with column i.  Written out,
-// with the wait left to the caller (lds_wait), because the compiler drains all global->LDS transfers in front of the builtin.
+// because the compiler drains all global->LDS transfers in front of the builtin; the reads of a block and their wait are one
+// statement, so that no register of theirs can be touched while a read is on its way.
+// v[i] = the four rows at p[i], w[i] = those OFF bytes on.
 template <int OFF>
-__device__ __forceinline__ void lds_read_tr(uint2 &v, const unsigned char *p)
+__device__ __forceinline__ void lds_read_tr_4x2(uint2 (&v)[4], uint2 (&w)[4], const unsigned char *const (&p)[4])
 {
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"((uint32_t)(uintptr_t)(lds_void *)p), "i"(OFF));
+    auto at = [](const unsigned char *q) { return (uint32_t)(uintptr_t)(lds_void *)q; };
+    asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %4, %8 offset:%12\n\t"
+                 "ds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %5, %9 offset:%12\n\t"
+                 "ds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %6, %10 offset:%12\n\t"
+                 "ds_read_b64_tr_b16 %3, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(at(p[0])), "v"(at(p[1])), "v"(at(p[2])), "v"(at(p[3])), "i"(OFF) : "memory");
 }
-// At most N of the LDS reads issued so far may be outstanding from here on; the values named are usable behind it.
-template <int N>
-__device__ __forceinline__ void lds_wait(uint2 &a, uint2 &b, uint2 &c, uint2 &d)
+// v[i][...] = the four rows at p[i], those 4, 16 and 20 rows of ROWB bytes on.
+template <int ROWB>
+__device__ __forceinline__ void lds_read_tr_4x4(uint2 (&v)[4][4], const unsigned char *const (&p)[4])
 {
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(N));
+    auto at = [](const unsigned char *q) { return (uint32_t)(uintptr_t)(lds_void *)q; };
+    asm volatile("ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %16 offset:%20\n\t"
+                 "ds_read_b64_tr_b16 %2, %16 offset:%21\n\tds_read_b64_tr_b16 %3, %16 offset:%22\n\t"
+                 "ds_read_b64_tr_b16 %4, %17\n\tds_read_b64_tr_b16 %5, %17 offset:%20\n\t"
+                 "ds_read_b64_tr_b16 %6, %17 offset:%21\n\tds_read_b64_tr_b16 %7, %17 offset:%22\n\t"
+                 "ds_read_b64_tr_b16 %8, %18\n\tds_read_b64_tr_b16 %9, %18 offset:%20\n\t"
+                 "ds_read_b64_tr_b16 %10, %18 offset:%21\n\tds_read_b64_tr_b16 %11, %18 offset:%22\n\t"
+                 "ds_read_b64_tr_b16 %12, %19\n\tds_read_b64_tr_b16 %13, %19 offset:%20\n\t"
+                 "ds_read_b64_tr_b16 %14, %19 offset:%21\n\tds_read_b64_tr_b16 %15, %19 offset:%22\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[0][2]), "=&v"(v[0][3]), "=&v"(v[1][0]), "=&v"(v[1][1]),
+                   "=&v"(v[1][2]), "=&v"(v[1][3]), "=&v"(v[2][0]), "=&v"(v[2][1]), "=&v"(v[2][2]), "=&v"(v[2][3]),
+                   "=&v"(v[3][0]), "=&v"(v[3][1]), "=&v"(v[3][2]), "=&v"(v[3][3])
+                 : "v"(at(p[0])), "v"(at(p[1])), "v"(at(p[2])), "v"(at(p[3])), "i"(4 * ROWB), "i"(16 * ROWB), "i"(20 * ROWB)
+                 : "memory");
 }
 __device__ __forceinline__ i32x4 join(const uint2 &lo, const uint2 &hi) { return i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y}; }
 
@@ -381,14 +403,11 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
                         // lane i of a group of sixteen asks for row 8 g + (i >> 2) (then + 4), columns 4 (i & 3) .. + 3 of the block
                         const int row = 8 * g + (r >> 2);
                         uint2 lo[4], hi[4];
+                        const unsigned char *p[4];
 #pragma unroll
-                        for (int nb = 0; nb < 4; ++nb) {
-                            const unsigned char *p = u + row * 128 + (((nb * 2 + ((r & 3) >> 1)) ^ ((r >> 2) << 1)) << 4) + (r & 1) * 8;
-                            lds_read_tr<0>(lo[nb], p);
-                            lds_read_tr<512>(hi[nb], p);
-                        }
-                        lds_wait<0>(lo[0], lo[1], lo[2], lo[3]);
-                        lds_wait<0>(hi[0], hi[1], hi[2], hi[3]);
+                        for (int nb = 0; nb < 4; ++nb)
+                            p[nb] = u + row * 128 + (((nb * 2 + ((r & 3) >> 1)) ^ ((r >> 2) << 1)) << 4) + (r & 1) * 8;
+                        lds_read_tr_4x2<512>(lo, hi, p);
 #pragma unroll
                         for (int nb = 0; nb < 4; ++nb) w[nb] = join(lo[nb], hi[nb]);
                     } else {
@@ -679,37 +698,29 @@ __global__ __launch_bounds__(256, W == 128 ? 2 : 3) void update_grads_kernel(con
             fetch(s + ST - 1, stage == 0 ? ST - 1 : stage - 1);
             const unsigned char *sa = smem + stage * STAGE, *sb = sa + 8192;
             if constexpr (ES == 2) {
-                // sixteen reads a slab, four per pair of 32-column blocks and K step; the products follow as they return
-                constexpr int KS = BK / 16;
-                uint2 ra[KS][MB][2], rb[KS][MB][2];
-                auto step = [&](auto ks_tag) {
-                    constexpr int ks = decltype(ks_tag)::value;
+                // sixteen reads a slab: K steps 2 q and 2 q + 1 of a block of 32 columns are the four of one address
+                constexpr int KQ = BK / 32;
+                static_assert(KQ * MB == 2, "four addresses a slab");
+                uint2 f[4][4];
+                const unsigned char *p[4];
+#pragma unroll
+                for (int q = 0; q < KQ; ++q)
 #pragma unroll
                     for (int i = 0; i < MB; ++i) {
-                        lds_read_tr<ks * 16 * ROWB>(ra[ks][i][0], sa + o_a[i]);
-                        lds_read_tr<(ks * 16 + 4) * ROWB>(ra[ks][i][1], sa + o_a[i]);
-                        lds_read_tr<ks * 16 * ROWB>(rb[ks][i][0], sb + o_b[i]);
-                        lds_read_tr<(ks * 16 + 4) * ROWB>(rb[ks][i][1], sb + o_b[i]);
+                        p[q * MB + i] = sa + o_a[i] + q * 32 * ROWB;
+                        p[2 + q * MB + i] = sb + o_b[i] + q * 32 * ROWB;
                     }
-                };
-                auto mul = [&](auto ks_tag) {
-                    constexpr int ks = decltype(ks_tag)::value, LEFT = (KS - 1 - ks) * 4 * MB;
+                lds_read_tr_4x4<ROWB>(f, p);
 #pragma unroll
-                    for (int i = 0; i < MB; ++i) lds_wait<LEFT>(ra[ks][i][0], ra[ks][i][1], rb[ks][i][0], rb[ks][i][1]);
+                for (int ks = 0; ks < 2 * KQ; ++ks)
 #pragma unroll
                     for (int i = 0; i < MB; ++i)
 #pragma unroll
-                        for (int j = 0; j < MB; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, join(ra[ks][i][0], ra[ks][i][1])),
-                                                                                __builtin_bit_cast(bf16x8, join(rb[ks][j][0], rb[ks][j][1])), acc[i][j], 0, 0, 0);
-                };
-                using std::integral_constant;
-                step(integral_constant<int, 0>{});
-                step(integral_constant<int, 1>{});
-                if constexpr (KS == 4) { step(integral_constant<int, 2>{}); step(integral_constant<int, 3>{}); }
-                mul(integral_constant<int, 0>{});
-                mul(integral_constant<int, 1>{});
-                if constexpr (KS == 4) { mul(integral_constant<int, 2>{}); mul(integral_constant<int, 3>{}); }
+                        for (int j = 0; j < MB; ++j) {
+                            const uint2 *fa = f[(ks >> 1) * MB + i] + 2 * (ks & 1), *fb = f[2 + (ks >> 1) * MB + j] + 2 * (ks & 1);
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, join(fa[0], fa[1])),
+                                                                                __builtin_bit_cast(bf16x8, join(fb[0], fb[1])), acc[i][j], 0, 0, 0);
+                        }
             } else {
 #pragma unroll
                 for (int ks = 0; ks < BK / 2; ++ks) {
