@@ -54,6 +54,7 @@ hipError_t launch_gemm(int dtype, int tile, int amode, int epi, GemmArgs g, hipS
     if (g.N <= 0 || g.N % edge != 0 || g.K <= 0 || g.K % slab_k(dtype) != 0) return hipErrorInvalidValue;
     g.m_tiles = (g.M + edge - 1) / edge;
     g.n_tiles = g.N / edge;
+    if (tile == TILE_SLIM) return launch_gemm_slim(dtype, amode, epi, g, st);
     if (dtype == AB_BF16) {
         switch (tile) {
         case TILE_SMALL: return launch_tile<bf16_t, 1>(amode, epi, g, st);

@@ -55,14 +55,18 @@ inline hipError_t compute_units(int *cus)
     return e;
 }
 
-enum { TILE_SMALL = 0, TILE_MID = 1, TILE_BIG = 2 };   // 64x64, 128x128, 256x256 work-group tiles
+enum { TILE_SMALL = 0, TILE_MID = 1, TILE_BIG = 2, TILE_SLIM = 3 };   // 64x64, 128x128, 256x256 work-group tiles; 32x32 (gemm_slim.hip)
 
-static inline int tile_edge(int tile) { return 64 << tile; }
+static inline int tile_edge(int tile) { return tile == TILE_SLIM ? 32 : 64 << tile; }
 static inline int slab_k(int dtype) { return dtype == AB_BF16 ? 64 : 32; }
 static inline size_t elem_size(int dtype) { return dtype == AB_BF16 ? 2 : 4; }
 
 // Fills m_tiles / n_tiles from M, N and the tile, then launches.  N must be a multiple of the tile edge.
 hipError_t launch_gemm(int dtype, int tile, int amode, int epi, GemmArgs g, hipStream_t st);
+
+// Products of a fraction of the chip's work (gemm_slim.hip): EPI_STORE or EPI_SCORE, with a bias; tile counts filled.
+// A generated operand is taken in its factored form, whichever amode names it.
+hipError_t launch_gemm_slim(int dtype, int amode, int epi, const GemmArgs &g, hipStream_t st);
 
 // The 256x256 bf16 kernel (gemm_big.hip): EPI_STORE (bf16 out) or EPI_SCORE, AMODE_LOAD or AMODE_GEN.
 bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g);

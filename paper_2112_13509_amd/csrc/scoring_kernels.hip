@@ -373,6 +373,7 @@ struct FinishArgs {
     float *scores; int64_t score_stride;                     // NULL: do not store
     int32_t *best_idx; float *best_score;                    // may be NULL
     int32_t C;
+    int32_t vec;                                             // `partial` is 16-byte aligned
 };
 
 __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
@@ -384,16 +385,33 @@ __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
     int bi = AB_NONE;
     for (int c0 = threadIdx.x; c0 < a.C; c0 += 1024) {      // four candidates per thread at a time, loads together
         float v[4];
+        if (a.nt % 8 == 0 && a.vec) {                        // sixteen partial sums a candidate and more: eight per round trip
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int c = c0 + 256 * u;
-            v[u] = c < a.C ? p[(int64_t)c * a.nt] : 0.f;
-        }
-        for (int t = 1; t < a.nt; ++t) {
+            for (int u = 0; u < 4; ++u) v[u] = 0.f;
+            for (int t = 0; t < a.nt; t += 8) {
+                f32x4 x[4][2];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        x[u][h] = c0 + 256 * u < a.C ? *(const f32x4 *)(p + (int64_t)(c0 + 256 * u) * a.nt + t + 4 * h) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) v[u] += (x[u][h][0] + x[u][h][1]) + (x[u][h][2] + x[u][h][3]);
+            }
+        } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = c0 + 256 * u;
-                if (c < a.C) v[u] += p[(int64_t)c * a.nt + t];
+                v[u] = c < a.C ? p[(int64_t)c * a.nt] : 0.f;
+            }
+            for (int t = 1; t < a.nt; ++t) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int c = c0 + 256 * u;
+                    if (c < a.C) v[u] += p[(int64_t)c * a.nt + t];
+                }
             }
         }
 #pragma unroll
@@ -1141,6 +1159,7 @@ hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride
     FinishArgs a;
     a.partial = partial; a.nt = nt; a.row_stride = row_stride; a.b_out = b_out; a.scores = scores;
     a.score_stride = score_stride; a.best_idx = best_idx; a.best_score = best_score; a.C = C;
+    a.vec = ((uintptr_t)partial & 15) == 0 && row_stride * nt % 4 == 0;
     const unsigned wave_blocks = (unsigned)((S + 3) / 4);
     if (C <= 1024 && nt == 1 && !b_out && !scores && best_idx) {
         launch_decide_rows16(a, partial, row_stride, S, st);
