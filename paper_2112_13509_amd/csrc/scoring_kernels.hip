@@ -296,20 +296,41 @@ __global__ __launch_bounds__(256) void output_v_kernel(const OutputVArgs a)
 #pragma unroll
     for (int o = 0; o < AB_MAX_OUTPUTS; ++o) acc[o] = 0.f;
     const float xp = a.h_last ? 0.f : a.xp_sel[s], xc = a.h_last ? 0.f : a.xc_sel[s];
-    for (int j = lane; j < a.H; j += 64) {
-        float h;
-        if (a.h_last) h = a.h_last[s * a.H + j];
-        else {
-            h = relu_keep_nan(fmaf(a.wc[j], xc, fmaf(a.wp[j], xp, a.a_term[s * a.H + j])));   // (the last hidden
-        }                                                       // activation stays fp32 in the scoring pass too)
+    // a lane takes eight adjacent units; everything it reads of eight outputs is requested before the first product
+    // (one round trip per 512 units; V of 300 scenarios, 512 units, 8 outputs: 4.6 us a launch, 12.1 with a unit a lane and step)
+    for (int j = lane * 8; j < a.H; j += 512) {
+        float h[8];
 #pragma unroll
-        for (int o = 0; o < AB_MAX_OUTPUTS; ++o) {
-            if (o < a.n_out) {
-                float w;
-                if constexpr (sizeof(T) == 2) w = bf16_bits_to_f32(((const uint16_t *)a.W)[(int64_t)o * a.H + j]);
-                else w = ((const float *)a.W)[(int64_t)o * a.H + j];
-                acc[o] = fmaf(w, h, acc[o]);
+        for (int q = 0; q < 2; ++q) {
+            f32x4 v;
+            if (a.h_last) v = *(const f32x4 *)(a.h_last + s * a.H + j + 4 * q);
+            else {                                           // (the last hidden activation stays fp32 in the scoring pass too)
+                const f32x4 at = *(const f32x4 *)(a.a_term + s * a.H + j + 4 * q);
+                const f32x4 wp = *(const f32x4 *)(a.wp + j + 4 * q), wc = *(const f32x4 *)(a.wc + j + 4 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = relu_keep_nan(fmaf(wc[e], xc, fmaf(wp[e], xp, at[e])));
             }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[4 * q + e] = v[e];
+        }
+#pragma unroll
+        for (int o0 = 0; o0 < AB_MAX_OUTPUTS; o0 += 8) {
+            if (o0 >= a.n_out) break;
+            i32x4 w[8][sizeof(T) / 2];
+#pragma unroll
+            for (int o = 0; o < 8; ++o)
+#pragma unroll
+                for (int q = 0; q < (int)sizeof(T) / 2; ++q)
+                    w[o][q] = *(const i32x4 *)((const T *)a.W + (int64_t)min(o0 + o, a.n_out - 1) * a.H + j + 4 * q);
+#pragma unroll
+            for (int o = 0; o < 8; ++o)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float x;
+                    if constexpr (sizeof(T) == 2) x = __uint_as_float(e & 1 ? (uint32_t)w[o][0][e >> 1] & 0xffff0000u : (uint32_t)w[o][0][e >> 1] << 16);
+                    else x = __uint_as_float((uint32_t)w[o][e >> 2][e & 3]);
+                    acc[o0 + o] = fmaf(x, h[e], acc[o0 + o]);
+                }
         }
     }
     const bool none = a.best_idx[s] < 0;
