@@ -890,16 +890,17 @@ __global__ __launch_bounds__(256) void score_single_hidden_kernel(const ScoreD1A
 // Shared per-tensor encoder (Section 3.1 "Meta network architecture": the layer-wise statistics are
 // embedded into a fixed-dimension feature space so that models with different layer counts can be
 // handled).  A work-group takes scenarios blockIdx.x, blockIdx.x + gridDim.x, ... (two work-groups per CU):
-//   e[l] = relu(W_b relu(W_a phi(stat[l]) + b_a) + b_b)   (K -> 128 on the vector ALUs, 128 -> 128 on
-//   the matrix cores), pooled[s] = mean_l e[l], written as the first 128 columns of the scenario row.
-// W_b (bf16, 32 KB) is staged once per work-group in LDS.  After that the four wavefronts work on
-// their own 32-tensor blocks without meeting, each block's raw statistics fetched while the block before
-// is computed: a wavefront transforms its block's statistics, runs
-// the first layer (a lane owns two of the 128 units, weights in registers), parks the bf16 result in
-// its private 8 KB of LDS, multiplies it with W_b (32 matrix instructions) and adds relu(. + b_b) of the
-// valid tensors to per-lane column sums.  One reduction over the wavefronts at the end.
-// LDS rows are 256 bytes; 16-byte chunk c of row r sits at position c ^ (r & 15).
-// Both layers' products use bf16 operands with fp32 accumulation.
+//   e[l] = relu(W_b relu(W_a phi(stat[l]) + b_a) + b_b)   (K -> 128 -> 128), pooled[s] = mean_l e[l], written as the
+//   first 128 columns of the scenario row.
+// The four wavefronts work on their own 32-tensor blocks without meeting, each block's raw statistics fetched while the
+// block before is computed; one reduction over the wavefronts at a scenario's end.  Both layers run on the matrix cores
+// and the hidden row never leaves the registers: the first layer is taken transposed (32 x 32 x 2 in fp32: rows = units,
+// columns = tensors, the bias as initial sums), so a lane ends with units 8 g + 4 half + 0..3 of its tensor, and the
+// second product (bf16 operands, fp32 sums) simply numbers its summed index that way: K step q of lane half h is units
+// 16 q + 4 h + 0..3 and 16 q + 8 + 4 h + 0..3, which is how W_b's chunks are laid out in LDS (bf16, 32 KB, once per
+// work-group; 16-byte chunk c of row r at c ^ (r & 15)).  Bound by the matrix cores (1536 clocks a block: 512 + 1024); with
+// the first layer on the vector ALUs (2700 clocks a block there) and its rows through LDS a batch of 8192 scenarios of
+// 200 - 400 tensors took 235 us, now 145 us.
 // ------------------------------------------------------------------------------------------------
 struct TensorEncArgs {
     const float *dyn; int32_t L, K;
@@ -911,15 +912,11 @@ struct TensorEncArgs {
     ab_enc enc_stat[AB_MAX_ENCODER_STATS];
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void tensor_encoder_kernel(const TensorEncArgs a)
+template <typename T, int KS>                                // KS: pairs of statistics (K <= 2 KS)
+__global__ __launch_bounds__(256, 2) void tensor_encoder_kernel(const TensorEncArgs a)
 {
     constexpr int H = 128;
-    __shared__ __attribute__((aligned(16))) unsigned char wb_s[H * 256];        // W_b, bf16, swizzled rows
-    __shared__ __attribute__((aligned(16))) unsigned char hbuf[4][32 * 256];    // per wavefront: 32 tensors x 128 bf16
-    __shared__ __attribute__((aligned(16))) float xin[4][32 * AB_MAX_ENCODER_STATS];    // per wavefront: transformed statistics
-    __shared__ __attribute__((aligned(16))) float wa_s[H * AB_MAX_ENCODER_STATS];       // [unit][AB_MAX_ENCODER_STATS], zero padded
-    __shared__ float ba_s[H];
+    __shared__ __attribute__((aligned(16))) unsigned char wb_s[H * 256];
     __shared__ float red[4][H];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, half = lane >> 5, l31 = lane & 31;
     auto layers = [&](int64_t sc) {                        // a scenario's own layer count
@@ -928,55 +925,48 @@ __global__ __launch_bounds__(256) void tensor_encoder_kernel(const TensorEncArgs
         return n;
     };
 
-    for (int i = t; i < H * AB_MAX_ENCODER_STATS; i += 256) {
-        const int o = i / AB_MAX_ENCODER_STATS, k = i % AB_MAX_ENCODER_STATS;
-        wa_s[i] = (k < a.K) ? load_as_f32<T>(a.Wa, o * a.K + k) : 0.f;
-    }
-    if (t < H) ba_s[t] = a.ba[t];
-    for (int i = t; i < H * 16; i += 256) {                 // 16-byte chunks of W_b
-        const int n = i >> 4, c = i & 15;
-        i32x4 v;
+    for (int i = t; i < H * 16; i += 256) {                 // chunk c = 2 q + h of row n
+        const int n = i >> 4, c = i & 15, u = (c >> 1) * 16 + (c & 1) * 4;
+        uint2 lo, hi;
         if constexpr (sizeof(T) == 2) {
-            v = *(const i32x4 *)((const uint16_t *)a.Wb + n * H + c * 8);
+            lo = *(const uint2 *)((const uint16_t *)a.Wb + n * H + u);
+            hi = *(const uint2 *)((const uint16_t *)a.Wb + n * H + u + 8);
         } else {
-            const float *w = (const float *)a.Wb + n * H + c * 8;
-            v.x = (int)pack_bf16x2(w[0], w[1]); v.y = (int)pack_bf16x2(w[2], w[3]);
-            v.z = (int)pack_bf16x2(w[4], w[5]); v.w = (int)pack_bf16x2(w[6], w[7]);
+            const float *w = (const float *)a.Wb + n * H + u;
+            lo = uint2{pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
+            hi = uint2{pack_bf16x2(w[8], w[9]), pack_bf16x2(w[10], w[11])};
         }
-        *(i32x4 *)(wb_s + n * 256 + ((c ^ (n & 15)) << 4)) = v;
+        *(i32x4 *)(wb_s + n * 256 + ((c ^ (n & 15)) << 4)) = i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y};
+    }
+
+    float bb[4], colsum[4] = {0.f, 0.f, 0.f, 0.f}, wa[4][KS];
+    f32x16 ba[4];                                          // first layer's bias where its result has the units
+#pragma unroll
+    for (int jn = 0; jn < 4; ++jn) {
+        bb[jn] = a.bb[jn * 32 + l31];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) ba[jn][r] = a.ba[jn * 32 + (r >> 2) * 8 + half * 4 + (r & 3)];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) wa[jn][k] = 2 * k + half < a.K ? load_as_f32<T>(a.Wa, (jn * 32 + l31) * a.K + 2 * k + half) : 0.f;
     }
     __syncthreads();
 
-    float bb[4], colsum[4] = {0.f, 0.f, 0.f, 0.f};
+    // this lane's statistics of a block: 2 k + half of tensor l31
+    ab_enc my_enc[KS];
 #pragma unroll
-    for (int jn = 0; jn < 4; ++jn) bb[jn] = a.bb[jn * 32 + l31];
-    unsigned char *hb = hbuf[wave];
-    float *xw = xin[wave];
-    float wa0[AB_MAX_ENCODER_STATS], wa1[AB_MAX_ENCODER_STATS];             // first layer: rows 2*lane and 2*lane+1 of W_a
-#pragma unroll
-    for (int k = 0; k < AB_MAX_ENCODER_STATS; ++k) {
-        wa0[k] = wa_s[(2 * lane) * AB_MAX_ENCODER_STATS + k];
-        wa1[k] = wa_s[(2 * lane + 1) * AB_MAX_ENCODER_STATS + k];
-    }
-    const float ba0 = ba_s[2 * lane], ba1 = ba_s[2 * lane + 1];
-
-    // this lane's slots of a block's statistics: element i = lane + 64 j of [32 tensors][AB_MAX_ENCODER_STATS], i.e.
-    // tensor (lane >> 3) + 8 j, statistic lane & 7 (the same statistic for all four: one transform)
-    const int my_k = lane & (AB_MAX_ENCODER_STATS - 1);
-    const ab_enc my_enc = a.enc_stat[my_k];
-    auto fetch_raw = [&](int64_t sc, int n_layers, int l0, float (&raw)[4]) {
+    for (int k = 0; k < KS; ++k) my_enc[k] = a.enc_stat[2 * k + half];
+    auto fetch_raw = [&](int64_t sc, int n_layers, int l0, float (&raw)[KS]) {
         const float *dyn = a.dyn + sc * (int64_t)a.L * a.K;
+        const int l = l0 + l31;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int l = l0 + (lane >> 3) + 8 * j;
-            raw[j] = (sc < a.S && l < n_layers && my_k < a.K) ? dyn[(int64_t)l * a.K + my_k] : 1.f;
-        }
+        for (int k = 0; k < KS; ++k)
+            raw[k] = (sc < a.S && l < n_layers && 2 * k + half < a.K) ? dyn[(int64_t)l * a.K + 2 * k + half] : 1.f;
     };
 
     int64_t sc = blockIdx.x;
     int Ls = sc < a.S ? layers(sc) : 0;
     int l0 = wave * 32;
-    float raw[4];
+    float raw[KS];
     fetch_raw(sc, Ls, l0, raw);
     for (; sc < a.S; ) {
       const bool has_block = l0 < Ls;                        // (its last block fetches the next scenario's first)
@@ -985,64 +975,62 @@ __global__ __launch_bounds__(256) void tensor_encoder_kernel(const TensorEncArgs
         int64_t sc_n = sc;
         int Ls_n = Ls, l0_n = l0 + 128;
         if (l0_n >= Ls) { sc_n = sc + gridDim.x; Ls_n = sc_n < a.S ? layers(sc_n) : 0; l0_n = wave * 32; }
-        float raw_n[4];
+        float raw_n[KS], x[KS];
         fetch_raw(sc_n, Ls_n, l0_n, raw_n);
-        // transformed statistics of the block's 32 tensors (zero rows past the end)
+        // transformed statistics (zero past the end)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int l = l0 + (lane >> 3) + 8 * j;
+        for (int k = 0; k < KS; ++k) {
             float lg;
-            if constexpr (sizeof(T) == 2) lg = __builtin_amdgcn_logf(raw[j]) * 0.69314718056f;
-            else lg = logf(raw[j]);
-            const float y = ((my_enc.kind == AB_ENC_LOG ? lg : raw[j]) - my_enc.shift) * my_enc.scale;
-            xw[lane + 64 * j] = (l < Ls && my_k < a.K) ? y : 0.f;
+            if constexpr (sizeof(T) == 2) lg = __builtin_amdgcn_logf(raw[k]) * 0.69314718056f;
+            else lg = logf(raw[k]);
+            const float y = ((my_enc[k].kind == AB_ENC_LOG ? lg : raw[k]) - my_enc[k].shift) * my_enc[k].scale;
+            x[k] = (l0 + l31 < Ls && 2 * k + half < a.K) ? y : 0.f;
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // same wavefront: LDS ops are in order
-        // first layer: this lane owns units 2*lane and 2*lane+1 (weights in registers) for all 32 tensors;
-        // a tensor's statistics are one broadcast LDS read, its two results one packed 4-byte write
-#pragma unroll 8
-        for (int r = 0; r < 32; ++r) {
-            const f32x4 x0 = *(const f32x4 *)(xw + r * AB_MAX_ENCODER_STATS);
-            float h0 = fmaf(wa0[3], x0.w, fmaf(wa0[2], x0.z, fmaf(wa0[1], x0.y, fmaf(wa0[0], x0.x, ba0))));
-            float h1 = fmaf(wa1[3], x0.w, fmaf(wa1[2], x0.z, fmaf(wa1[1], x0.y, fmaf(wa1[0], x0.x, ba1))));
-            if (a.K > 4) {
-                const f32x4 x1 = *(const f32x4 *)(xw + r * AB_MAX_ENCODER_STATS + 4);
-                h0 = fmaf(wa0[7], x1.w, fmaf(wa0[6], x1.z, fmaf(wa0[5], x1.y, fmaf(wa0[4], x1.x, h0))));
-                h1 = fmaf(wa1[7], x1.w, fmaf(wa1[6], x1.z, fmaf(wa1[5], x1.y, fmaf(wa1[4], x1.x, h1))));
-            }
-            const uint32_t pk = pack_bf16x2(relu_keep_nan(h0), relu_keep_nan(h1));
-            *(uint32_t *)(hb + r * 256 + (((lane >> 2) ^ (r & 15)) << 4) + (lane & 3) * 4) = pk;
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         f32x16 acc[4];
 #pragma unroll
         for (int jn = 0; jn < 4; ++jn)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[jn][r] = 0.f;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int chunk = q * 2 + half;
-            const i32x4 fa = *(const i32x4 *)(hb + l31 * 256 + ((chunk ^ (l31 & 15)) << 4));
+        for (int jb = 0; jb < 4; ++jb) {                     // 32 hidden units at a time
+            asm volatile("" ::: "memory");                   // (W_b's fragments are read here and not kept in registers)
+            f32x16 h = ba[jb];
 #pragma unroll
-            for (int jn = 0; jn < 4; ++jn) {
-                const int n = jn * 32 + l31;
-                const i32x4 fb = *(const i32x4 *)(wb_s + n * 256 + ((chunk ^ (n & 15)) << 4));
-                // rows = tensors (first operand), columns = units (second operand)
-                acc[jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa),
-                                                                  __builtin_bit_cast(bf16x8, fb), acc[jn], 0, 0, 0);
+            for (int k = 0; k < KS; ++k) h = __builtin_amdgcn_mfma_f32_32x32x2f32(wa[jb][k], x[k], h, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int chunk = (jb * 2 + s) * 2 + half;
+                i32x4 fa;
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    fa[p] = (int)pack_bf16x2(relu_keep_nan(h[s * 8 + 2 * p]), relu_keep_nan(h[s * 8 + 2 * p + 1]));
+#pragma unroll
+                for (int jn = 0; jn < 4; ++jn) {
+                    const int n = jn * 32 + l31;
+                    const i32x4 fb = *(const i32x4 *)(wb_s + n * 256 + ((chunk ^ (n & 15)) << 4));
+                    // rows = tensors (first operand), columns = units (second operand)
+                    acc[jn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa),
+                                                                      __builtin_bit_cast(bf16x8, fb), acc[jn], 0, 0, 0);
+                }
             }
         }
+        if (l0 + 32 <= Ls) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int l = l0 + (r >> 2) * 8 + half * 4 + (r & 3);
-            if (l < Ls) {
+            for (int r = 0; r < 16; ++r)
 #pragma unroll
                 for (int jn = 0; jn < 4; ++jn) colsum[jn] += relu_keep_nan(acc[jn][r] + bb[jn]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int l = l0 + (r >> 2) * 8 + half * 4 + (r & 3);
+                if (l < Ls) {
+#pragma unroll
+                    for (int jn = 0; jn < 4; ++jn) colsum[jn] += relu_keep_nan(acc[jn][r] + bb[jn]);
+                }
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // fragment reads done before the block buffer is reused
 #pragma unroll
-        for (int j = 0; j < 4; ++j) raw[j] = raw_n[j];
+        for (int k = 0; k < KS; ++k) raw[k] = raw_n[k];
         l0 += 128;
       }
       // the scenario is complete for this wavefront: combine the four wavefronts' column sums
@@ -1618,9 +1606,15 @@ hipError_t launch_tensor_encoder(int dtype, const ab_model_desc *d, const float 
     int cus = 0;
     hipError_t e;
     if ((e = compute_units(&cus)) != hipSuccess) return e;
-    const int64_t grid = S < 2 * (int64_t)cus ? S : 2 * (int64_t)cus;      // two work-groups fit a CU's LDS
-    if (dtype == AB_BF16) tensor_encoder_kernel<bf16_t><<<(unsigned)grid, 256, 0, st>>>(a);
-    else tensor_encoder_kernel<float><<<(unsigned)grid, 256, 0, st>>>(a);
+    const int64_t grid = S < 2 * (int64_t)cus ? S : 2 * (int64_t)cus;      // two work-groups a CU (their registers)
+    const unsigned blocks = (unsigned)grid;
+    if (dtype == AB_BF16) {
+        if (a.K <= 4) tensor_encoder_kernel<bf16_t, 2><<<blocks, 256, 0, st>>>(a);
+        else          tensor_encoder_kernel<bf16_t, 4><<<blocks, 256, 0, st>>>(a);
+    } else {
+        if (a.K <= 4) tensor_encoder_kernel<float, 2><<<blocks, 256, 0, st>>>(a);
+        else          tensor_encoder_kernel<float, 4><<<blocks, 256, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 
