@@ -283,6 +283,7 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
     // 1. scenario rows: transformed statistics (or pooled tensor embedding) + scalars, K-padded
     const double es = (double)elem_size(dt);
     bool prep_done = false;
+    bool grid_done = false;             // a per-scenario grid's rows: in the first launch if all scenarios are one chunk
     if (desc->tensor_encoder == 2) {
         {
             // per scenario and layer: two gate products (256 x 96 and 256 x 128) and the K -> 32 embedding
@@ -305,12 +306,14 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                                    desc->enc_hidden[1], 0, st));
     } else {
         // flat statistics: transform and layer-1 preparation (step 2) share one launch where the layout allows
-        const double prep_bytes = (double)p.H[0] * (p.F * es + p.Kp * es) + (double)C * p.H[0] * 4.0;
+        const double prep_bytes = (double)p.H[0] * (p.F * es + p.Kp * es) + (double)C * p.H[0] * 4.0 +
+                                  (per_scenario && p.chunk_scen >= S ? (double)S * C * 8.0 : 0.0);
         TraceScope ts("encode_and_prep", (double)S * (p.Fs * 4.0 + p.Kp * es) + prep_bytes, 1, st);
         AB_HIP(launch_encode_and_prep(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp, params->W[p.base],
                                       params->b[p.base], p.F, p.Fs, p.H[0], w1s, grid, b_term, cfg_vec,
                                       params->W[p.base + p.D], params->b[p.base + p.D], p.H[p.D - 1], w_out_f,
-                                      &prep_done, st));
+                                      per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, &prep_done, st));
+        grid_done = prep_done && p.chunk_scen >= S;
         if (!prep_done) AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp, 0, 1, st));
     }
     // 2. layer-1 split: packed statistics columns of W1, candidate term B[c], fp32 output weights
@@ -337,7 +340,7 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
         const int64_t rows = ns * C;
         const float *a_chunk = a_term + s0 * p.H[0];
         int nt = 1;
-        if (per_scenario) {
+        if (per_scenario && !grid_done) {
             TraceScope ts("grid_rows", (double)rows * 8.0, 1, st);
             AB_HIP(launch_grid_rows(desc, grid->partition_bytes + s0 * grid->P, grid->credit_mult + s0 * grid->Q,
                                     grid->P, grid->Q, xp_row, xc_row, rows, st));

@@ -213,30 +213,33 @@ __global__ __launch_bounds__(256) void prep_layer1_kernel(const PrepArgs a)
     prep_layer1_block<T>(a, blockIdx.x);
 }
 
-// The two launches that open a scoring pass of the flat model are independent of each other (the transform reads
-// the statistics, the preparation reads the model and the grid), so they share one launch: the first
-// `enc_blocks` work-groups do the feature transform (the long, memory-bound part starts at once), the short
-// work-groups of the layer-1 preparation fill in behind them.
-template <typename T>
-__global__ __launch_bounds__(256) void encode_and_prep_kernel(const EncodeArgs a, const QuadSplit g, const PrepArgs p,
-                                                              unsigned enc_blocks)
-{
-    if (blockIdx.x < enc_blocks) encode_stats_quad_block<T>(a, g, blockIdx.x);
-    else prep_layer1_block<T>(p, blockIdx.x - enc_blocks);
-}
-
 // Per-scenario candidate grids: the transformed pair (phi(S_p), phi(S_c)) of every (scenario, candidate) row
 // of a chunk, row = s * P * Q + p * Q + q, from part[S, P] and cred[S, Q].
 struct GridRowsArgs { const float *part, *cred; int32_t P, Q; ab_enc enc_part, enc_cred; float *xp_row, *xc_row; int64_t rows; };
-__global__ __launch_bounds__(256) void grid_rows_kernel(const GridRowsArgs a)
+__device__ __forceinline__ void grid_rows_block(const GridRowsArgs &a, unsigned block)
 {
-    const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t row = (int64_t)block * 256 + threadIdx.x;
     if (row >= a.rows) return;
     const int Cn = a.P * a.Q;
     const int64_t s = row / Cn;
     const int c = (int)(row - s * Cn);
     a.xp_row[row] = phi(a.part[s * a.P + c / a.Q], a.enc_part);
     a.xc_row[row] = phi(a.cred[s * a.Q + c % a.Q], a.enc_cred);
+}
+__global__ __launch_bounds__(256) void grid_rows_kernel(const GridRowsArgs a) { grid_rows_block(a, blockIdx.x); }
+
+// What opens a scoring pass of the flat model is independent of each other (the transform reads the statistics, the
+// preparation the model and the grid, a per-scenario grid's rows the grid), so it shares one launch: the first
+// `enc_blocks` work-groups do the feature transform (the long, memory-bound part starts at once), the short
+// work-groups of the layer-1 preparation fill in behind them, then those of the grid rows (a launch of their own costs
+// 4.6 us), where all scenarios are one chunk.
+template <typename T>
+__global__ __launch_bounds__(256) void encode_and_prep_kernel(const EncodeArgs a, const QuadSplit g, const PrepArgs p,
+                                                              const GridRowsArgs r, unsigned enc_blocks, unsigned grid_from)
+{
+    if (blockIdx.x < enc_blocks) encode_stats_quad_block<T>(a, g, blockIdx.x);
+    else if (blockIdx.x < grid_from) prep_layer1_block<T>(p, blockIdx.x - enc_blocks);
+    else grid_rows_block(r, blockIdx.x - grid_from);
 }
 
 hipError_t launch_grid_rows(const ab_model_desc *d, const float *part, const float *cred, int P, int Q,
@@ -1127,7 +1130,8 @@ hipError_t launch_prep_layer1(int dtype, const ab_model_desc *d, const void *W1,
 hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, void *xs,
                                   int64_t S, int ld, const void *W1, const float *b1, int F, int Fs, int H1, void *w1s,
                                   const ab_grid *grid, float *b_term, float *cfg_vec, const void *Wout,
-                                  const float *b_out, int H_last, float *w_out_f, bool *done, hipStream_t st)
+                                  const float *b_out, int H_last, float *w_out_f, float *xp_row, float *xc_row,
+                                  bool *done, hipStream_t st)
 {
     *done = false;
     if (S == 0) return hipSuccess;
@@ -1138,12 +1142,15 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
     PrepArgs p;
     const int64_t n = fill_prep_args(p, d, W1, b1, F, Fs, H1, ld, w1s, grid, b_term, cfg_vec, Wout, b_out, H_last, w_out_f);
     const int64_t enc_blocks = (S + g.rpb - 1) / g.rpb, prep_blocks = (n + 255) / 256;
-    if (enc_blocks + prep_blocks > 0x7fffffffLL) return hipSuccess;
+    const GridRowsArgs r{grid->partition_bytes, grid->credit_mult, grid->P, grid->Q, d->enc_partition, d->enc_credit, xp_row, xc_row,
+                         xp_row ? S * grid->P * grid->Q : 0};
+    const int64_t blocks = enc_blocks + prep_blocks + (r.rows + 255) / 256;
+    if (blocks > 0x7fffffffLL) return hipSuccess;
     *done = true;
     if (dtype == AB_BF16)
-        encode_and_prep_kernel<bf16_t><<<(unsigned)(enc_blocks + prep_blocks), 256, 0, st>>>(a, g, p, (unsigned)enc_blocks);
+        encode_and_prep_kernel<bf16_t><<<(unsigned)blocks, 256, 0, st>>>(a, g, p, r, (unsigned)enc_blocks, (unsigned)(enc_blocks + prep_blocks));
     else
-        encode_and_prep_kernel<float><<<(unsigned)(enc_blocks + prep_blocks), 256, 0, st>>>(a, g, p, (unsigned)enc_blocks);
+        encode_and_prep_kernel<float><<<(unsigned)blocks, 256, 0, st>>>(a, g, p, r, (unsigned)enc_blocks, (unsigned)(enc_blocks + prep_blocks));
     return hipGetLastError();
 }
 
