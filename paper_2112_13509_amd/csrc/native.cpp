@@ -98,14 +98,21 @@ void *stream_of(PyObject *o)
         Py_INCREF(o);
         h = o;
     }
-    void *v = PyLong_AsVoidPtr(h);
+    PyObject *i = PyNumber_Long(h);
     Py_DECREF(h);
+    if (!i) throw Failed{};
+    void *v = PyLong_AsVoidPtr(i);
+    Py_DECREF(i);
     if (!v && PyErr_Occurred()) throw Failed{};
     return v;
 }
+// Whatever int() takes: 256.0 and 0-dimensional arrays count as whole numbers.
 int64_t int_of(PyObject *o)
 {
-    const long long v = PyLong_AsLongLong(o);
+    PyObject *i = PyNumber_Long(o);
+    if (!i) throw Failed{};
+    const long long v = PyLong_AsLongLong(i);
+    Py_DECREF(i);
     if (v == -1 && PyErr_Occurred()) throw Failed{};
     return v;
 }

@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 
+import numpy as np
 import pytest
 
 from paper_2112_13509_amd import binding as ab
@@ -210,6 +211,18 @@ def test_binding_refuses_cpu_tensors(lib):
     d = ab.desc_from_workload(w)
     with pytest.raises(TypeError):
         ab.ab_select_best(torch.zeros(2, 4), torch.zeros(2, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("count", [4, 4.0, np.int64(4), np.float32(4)])
+def test_binding_takes_counts_as_int_does(lib, count):
+    """A count may be anything that int() takes (a column count computed in numpy, say); the call then gets as far as
+    the tensors' place, and a text that is no number is refused before that."""
+    import torch
+    sc, idx = torch.zeros(2, 4), torch.zeros(2, dtype=torch.int32)
+    with pytest.raises(TypeError, match="must be a tensor on the GPU"):
+        ab.ab_select_best(sc, idx, C_=count, row_stride=count, stream=0)
+    with pytest.raises(ValueError):
+        ab.ab_select_best(sc, idx, C_="four")
 
 
 def test_static_scratch_form_checks_its_arguments_on_the_host(lib):
