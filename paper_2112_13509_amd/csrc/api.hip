@@ -272,7 +272,11 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
     }
     unsigned char *ws = (unsigned char *)workspace;
     void *xs = ws + p.off_xs, *w1s = ws + p.off_w1s;
-    float *a_term = (float *)(ws + p.off_aterm), *b_term = (float *)(ws + p.off_bterm);
+    float *a_term = (float *)(ws + p.off_aterm);
+    // the candidate term as a table [C, H]: only the generic tiles and the scorer with one hidden layer read it (a
+    // per-scenario grid comes in factored form there too)
+    const bool table = !grid->per_scenario && (p.D == 1 || (!p.big[1] && p.tile[1] != TILE_SLIM));
+    float *b_term = table ? (float *)(ws + p.off_bterm) : nullptr;
     float *w_out_f = (float *)(ws + p.off_wout), *partial = (float *)(ws + p.off_partial);
     float *cfg_vec = (float *)(ws + p.off_cfgv);
     float *xp_row = (float *)(ws + p.off_xrow), *xc_row = xp_row + p.chunk_rows;

@@ -152,7 +152,7 @@ struct PrepArgs {
     const float *b1;
     const float *part; const float *cred; int32_t P, Q;
     ab_enc enc_part, enc_cred;
-    float *b_term;                               // [P*Q, H1]
+    float *b_term;                               // [P*Q, H1], or NULL: not wanted
     float *wp_f, *wc_f, *xp_f, *xc_f;            // [H1], [H1], [P*Q], [P*Q]
     const void *Wout; const float *b_out; int32_t H_last, n_out; float *w_out_f;   // w_out_f[H_last + 1]
 };
@@ -169,7 +169,7 @@ __device__ __forceinline__ void prep_layer1_block(const PrepArgs &a, unsigned bl
 {
     const int64_t gid = (int64_t)block * 256 + threadIdx.x;
     const int64_t n_pack = (int64_t)a.H1 * a.ld;
-    const int64_t n_bt = (int64_t)a.P * a.Q * a.H1;
+    const int64_t n_bt = a.b_term ? (int64_t)a.P * a.Q * a.H1 : 0;
     if (gid < n_pack) {
         const int h = (int)(gid / a.ld), k = (int)(gid - (int64_t)h * a.ld);
         if constexpr (sizeof(T) == 2) {
@@ -1164,7 +1164,7 @@ static int64_t fill_prep_args(PrepArgs &a, const ab_model_desc *d, const void *W
     const int Cn = grid->P * grid->Q;
     a.wp_f = cfg_vec; a.wc_f = cfg_vec + H1; a.xp_f = cfg_vec + 2 * H1; a.xc_f = cfg_vec + 2 * H1 + Cn;
     a.Wout = Wout; a.b_out = b_out; a.H_last = H_last; a.n_out = d->n_outputs > 1 ? d->n_outputs : 1; a.w_out_f = w_out_f;
-    return (int64_t)H1 * ld + (int64_t)Cn * H1 + H_last + H1 + Cn;
+    return (int64_t)H1 * ld + (b_term ? (int64_t)Cn * H1 : 0) + H_last + H1 + Cn;
 }
 
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,
