@@ -9,18 +9,23 @@
 // times the work-groups at twice the bytes, which a product that leaves most CUs idle does not notice.
 //
 // With GEN the first operand is the first hidden layer, relu(a_term[s] + wp xp + wc xc) (gemm_core.hpp, factored form):
-// the rows' a_term chunks, wp and wc come by DMA as well and the fragment is formed when it is read.
+// the a_term chunks, wp and wc come by DMA as well and the fragment is formed when it is read.  With 32 or more rows a
+// scenario a tile touches at most two of them (GEN_PAIR): one request a slab brings both scenarios' terms, wp and wc, and a
+// row picks its scenario's (one job on the 1024-wide network, a call: 27.7 us with every row's terms, 26.0 so).  With fewer
+// rows a scenario (GEN_ROWS) every row's terms come, in bf16 eight requests more a slab.
 #include "stream_util.hpp"
 
 namespace ab {
 
-template <typename T, bool GEN>
+enum { GEN_NONE = 0, GEN_ROWS = 1, GEN_PAIR = 2 };
+
+template <typename T, int GEN>
 struct SlimShape {
     static constexpr int BK = TileTraits<T>::BK;
-    static constexpr int A_BYTES = GEN ? 32 * BK * 4 : 4096, B_BYTES = 4096, W_BYTES = GEN ? 1024 : 0;
+    static constexpr int A_BYTES = GEN == GEN_ROWS ? 32 * BK * 4 : GEN == GEN_PAIR ? 0 : 4096, B_BYTES = 4096, W_BYTES = GEN ? 1024 : 0;
     static constexpr int SLAB = A_BYTES + B_BYTES + W_BYTES;
     static constexpr int REQ = SLAB / 1024;                  // DMA requests of a slab
-    static constexpr int NS = GEN && sizeof(T) == 2 ? 3 : 4; // slabs in flight a wavefront (160 KB of LDS)
+    static constexpr int NS = GEN == GEN_ROWS && sizeof(T) == 2 ? 3 : 4; // slabs in flight a wavefront (160 KB of LDS)
     static constexpr int TABLES = 512;                       // xp, xc of the tile's rows, bias and output weights of its columns
 };
 
@@ -33,7 +38,7 @@ __device__ __forceinline__ void wait_slabs(int left)         // at most `left` s
     else                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <typename T, bool GEN, int EPI>
+template <typename T, int GEN, int EPI>
 __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int stages)
 {
     typedef SlimShape<T, GEN> Z;
@@ -58,10 +63,20 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int st
 
     // DMA sources.  128-byte rows: chunk c of row r sits at c ^ ((r >> 1) & 7); 256-byte rows (a_term of a bf16 slab): c ^ (r & 15)
     constexpr int AROW = Z::A_BYTES / 32, ACH = AROW / 16, A_REQ = Z::A_BYTES / 1024;
-    const unsigned char *pa, *pb = (const unsigned char *)g.B + (int64_t)n0 * g.ldb * ES;
-    int32_t off_a[A_REQ], off_b[4];
+    const unsigned char *pa = nullptr, *pb = (const unsigned char *)g.B + (int64_t)n0 * g.ldb * ES;
+    int32_t off_a[A_REQ ? A_REQ : 1], off_b[4];
+    const float *pv = nullptr;                               // vectors of a generated operand: this lane's piece of a request
+    int second = 0;                                          // GEN_PAIR: this lane's row is of the tile's second scenario
     auto place = [](int row, int c) { return AROW == 256 ? c ^ (row & 15) : c ^ ((row >> 1) & 7); };
-    if constexpr (GEN) {
+    if constexpr (GEN == GEN_PAIR) {
+        // a_term of the two scenarios (the last one twice at the end), wp, wc: BK / 4 lanes each (fp32: the rest repeats them)
+        const int64_t s0 = m0 / g.C, s1 = min(s0 + 1, (g.M - 1) / g.C);
+        const int part = (lane / (BK / 4)) & 3;
+        pv = (part == 0 ? g.a_term + s0 * g.ldt : part == 1 ? g.a_term + s1 * g.ldt : part == 2 ? g.wp : g.wc) + (lane & (BK / 4 - 1)) * 4;
+        second = m0 + l31 >= (s0 + 1) * g.C;
+    } else if constexpr (GEN == GEN_ROWS) {
+        // wp, wc: lanes 0 .. BK/4 - 1, then as many (the rest of the request repeats them)
+        pv = (lane & (BK / 4) ? g.wc : g.wp) + (lane & (BK / 4 - 1)) * 4;
         const int64_t s0 = m0 / g.C;
         pa = (const unsigned char *)(g.a_term + s0 * g.ldt);
 #pragma unroll
@@ -89,11 +104,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int st
         for (int q = 0; q < A_REQ; ++q) dma16<false>(pa + kt * AROW + off_a[q], dst + q * 1024);
 #pragma unroll
         for (int q = 0; q < 4; ++q) dma16<false>(pb + kt * 128 + off_b[q], dst + Z::A_BYTES + q * 1024);
-        if constexpr (GEN) {
-            // the slab's wp, wc: lanes 0 .. BK/4 - 1, then as many (the rest of the request repeats them)
-            const int c = lane & (BK / 4 - 1);
-            dma16<false>((lane & (BK / 4) ? g.wc : g.wp) + kt * BK + c * 4, dst + Z::A_BYTES + Z::B_BYTES);
-        }
+        if constexpr (GEN) dma16<false>(pv + kt * BK, dst + Z::A_BYTES + Z::B_BYTES);
     };
     const int slabs = g.K / BK, n = (slabs - wave + 3) >> 2;
     for (int i = 0; i < stages && i < n; ++i) fetch(i, ring + i * Z::SLAB);
@@ -116,12 +127,13 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int st
             if constexpr (!GEN) {
                 fa[q] = *(const i32x4 *)(slot + l31 * 128 + (place(l31, c) << 4));
             } else {
-                const float *w = (const float *)(slot + Z::A_BYTES + Z::B_BYTES);
+                const float *vec = (const float *)(slot + Z::A_BYTES + Z::B_BYTES), *w = GEN == GEN_PAIR ? vec + 2 * BK : vec;
                 float h[16 / ES];
 #pragma unroll
                 for (int p = 0; p < 4 / ES; ++p) {
                     const int ch = c * (4 / ES) + p;         // chunk of four floats
-                    const f32x4 a = *(const f32x4 *)(slot + l31 * AROW + (place(l31, ch) << 4));
+                    const f32x4 a = GEN == GEN_PAIR ? *(const f32x4 *)(vec + second * BK + ch * 4)
+                                                    : *(const f32x4 *)(slot + l31 * AROW + (place(l31, ch) << 4));
                     const f32x4 wp = *(const f32x4 *)(w + ch * 4), wc = *(const f32x4 *)(w + BK + ch * 4);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) h[4 * p + e] = relu_keep_nan(fmaf(wc[e], xc, fmaf(wp[e], xp, a[e])));
@@ -172,7 +184,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int st
     }
 }
 
-template <typename T, bool GEN, int EPI>
+template <typename T, int GEN, int EPI>
 static hipError_t launch_slim(const GemmArgs &g, hipStream_t st)
 {
     typedef SlimShape<T, GEN> Z;
@@ -185,18 +197,24 @@ static hipError_t launch_slim(const GemmArgs &g, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t launch_slim_as(bool gen, int epi, const GemmArgs &g, hipStream_t st)
+template <typename T, int GEN>
+static hipError_t launch_slim_as(int epi, const GemmArgs &g, hipStream_t st)
 {
-    if (epi == EPI_STORE) return gen ? launch_slim<T, true, EPI_STORE>(g, st) : launch_slim<T, false, EPI_STORE>(g, st);
-    return gen ? launch_slim<T, true, EPI_SCORE>(g, st) : launch_slim<T, false, EPI_SCORE>(g, st);
+    return epi == EPI_STORE ? launch_slim<T, GEN, EPI_STORE>(g, st) : launch_slim<T, GEN, EPI_SCORE>(g, st);
+}
+
+template <typename T>
+static hipError_t launch_slim_of(bool gen, int epi, const GemmArgs &g, hipStream_t st)
+{
+    if (!gen) return launch_slim_as<T, GEN_NONE>(epi, g, st);
+    return g.C >= 32 ? launch_slim_as<T, GEN_PAIR>(epi, g, st) : launch_slim_as<T, GEN_ROWS>(epi, g, st);
 }
 
 hipError_t launch_gemm_slim(int dtype, int amode, int epi, const GemmArgs &g, hipStream_t st)
 {
     if (!g.bias || g.out_t || (epi != EPI_STORE && epi != EPI_SCORE) || g.m_tiles * g.n_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
     const bool gen = amode != AMODE_LOAD;
-    return dtype == AB_BF16 ? launch_slim_as<bf16_t>(gen, epi, g, st) : launch_slim_as<float>(gen, epi, g, st);
+    return dtype == AB_BF16 ? launch_slim_of<bf16_t>(gen, epi, g, st) : launch_slim_of<float>(gen, epi, g, st);
 }
 
 }  // namespace ab

@@ -23,6 +23,8 @@ pytestmark = pytest.mark.gpu
     (3, 100, 6, 11, [1088, 64], False),          # more slabs than the ring holds
     (2, 128, 17, 3, [2112, 256, 128], True),
     (1, 128, 16, 16, [1024, 1024], False),
+    (4, 20, 32, 1, [256, 128], False),           # 32 rows a scenario: a tile each
+    (5, 33, 9, 5, [576, 64], True),              # 45: two scenarios in most tiles, the last tile ends with the last one
     (7, 10, 3, 3, [256], False),                 # scenario term only
 ])
 def test_small_products(dtype, S, L, P, Q, hidden, own_grids):
