@@ -338,6 +338,15 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
         TraceScope ts("gemm_scenario_term", 2.0 * S * p.H[0] * p.Kp, 0, st);
         AB_HIP(launch_gemm(dt, p.tile_a, AMODE_LOAD, EPI_STORE, g, st));
     }
+    // the chosen candidate's pair for step 5: written by the selection where its room holds all scenarios (a launch of its
+    // own; 300 scenarios of 256 candidates with V, a call: 115.8 us with that launch, 114.3 so)
+    float *xp_sel = (float *)(ws + p.off_vx), *xc_sel = xp_sel + p.v_chunk;
+    const bool pairs_done = S <= p.v_chunk;
+    auto chosen_at = [&](int64_t s0, float *xp, float *xc) {
+        const int64_t own = per_scenario ? s0 : 0;
+        return ChosenArgs{grid->partition_bytes + own * grid->P, grid->credit_mult + own * grid->Q, grid->P, grid->Q, per_scenario,
+                          desc->enc_partition, desc->enc_credit, xp, xc};
+    };
     // 4. candidate rows, a chunk of scenarios at a time
     for (int64_t s0 = 0; s0 < S; s0 += p.chunk_scen) {
         const int64_t ns = (S - s0 < p.chunk_scen) ? S - s0 : p.chunk_scen;
@@ -385,26 +394,24 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                     AB_HIP(launch_gemm(dt, p.tile[k], amode == AMODE_GEN && per_scenario ? AMODE_GENV : amode, epi, g, st));
             }
         }
+        const ChosenArgs pair = chosen_at(s0, xp_sel + s0, xc_sel + s0);
         TraceScope ts("finish_select", (double)rows * (nt * 4.0 + (scores ? 4.0 : 0.0)) + ns * 8.0, 1, st);
         AB_HIP(launch_finish_select(partial, nt, C, w_out_f + p.H[p.D - 1],
                                     scores ? scores + s0 * C : nullptr, C,
                                     best_idx ? best_idx + s0 : nullptr,
-                                    best_score ? best_score + s0 : nullptr, ns, C, st));
+                                    best_score ? best_score + s0 : nullptr, ns, C, v_best && pairs_done ? &pair : nullptr, st));
     }
     // 5. the chosen candidate's prediction vector: the hidden chain once more on one row per scenario (the row's
     // candidate values are those of best_idx), then the output layer unit by unit
     if (v_best) {
         const int n_out = desc->n_outputs > 0 ? desc->n_outputs : 1;
-        float *xp_sel = (float *)(ws + p.off_vx), *xc_sel = xp_sel + p.v_chunk;
         float *h_last = (float *)(ws + p.off_vlast);
         void *vact[2] = {ws + p.off_vact0, ws + p.off_vact1};
         for (int64_t s0 = 0; s0 < S; s0 += p.v_chunk) {
             const int64_t ns = (S - s0 < p.v_chunk) ? S - s0 : p.v_chunk;
-            ab_grid gsub = *grid;
-            if (per_scenario) { gsub.partition_bytes += s0 * grid->P; gsub.credit_mult += s0 * grid->Q; }
-            {
+            if (!pairs_done) {
                 TraceScope ts("chosen_pair", (double)ns * 20.0, 1, st);
-                AB_HIP(launch_chosen_pair(desc, &gsub, best_idx + s0, xp_sel, xc_sel, ns, st));
+                AB_HIP(launch_chosen_pair(chosen_at(s0, xp_sel, xc_sel), best_idx + s0, ns, st));
             }
             for (int k = 1; k < p.D; ++k) {
                 GemmArgs g;
@@ -507,7 +514,7 @@ ab_status ab_select_best(const float *scores, int64_t S, int32_t C, int64_t row_
         const int64_t ns = (S - s0 < (1 << 30)) ? S - s0 : (1 << 30);
         TraceScope ts("select_best", (double)ns * (C * 4.0 + 8.0), 1, st);
         AB_HIP(launch_finish_select(scores + s0 * row_stride, 1, row_stride, nullptr, nullptr, 0,
-                                    best_idx + s0, best_score ? best_score + s0 : nullptr, ns, C, st));
+                                    best_idx + s0, best_score ? best_score + s0 : nullptr, ns, C, nullptr, st));
     }
     return AB_OK;
 }

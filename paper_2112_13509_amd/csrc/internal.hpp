@@ -86,9 +86,11 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
                                   const ab_grid *grid, float *b_term, float *cfg_vec, const void *Wout,
                                   const float *b_out, int H_last, float *w_out_f, float *xp_row, float *xc_row,
                                   bool *done, hipStream_t st);     // xp_row: also the rows of a per-scenario grid
+// Where the chosen candidate's transformed pair goes, and the grid that it comes from.
+struct ChosenArgs { const float *part, *cred; int32_t P, Q, per_scenario; ab_enc enc_part, enc_cred; float *xp_sel, *xc_sel; };
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,
                                 float *scores, int64_t score_stride, int32_t *best_idx, float *best_score,
-                                int64_t S, int C, hipStream_t st);
+                                int64_t S, int C, const ChosenArgs *chosen, hipStream_t st);   // chosen: or NULL
 hipError_t launch_trigger(const float *scores, int64_t S, int C, int64_t row_stride, const int32_t *cur_idx,
                           const float *observed, float gain_threshold, float error_threshold, int32_t *best_idx,
                           float *gain, uint8_t *reconf, uint8_t *adapt, hipStream_t st);
@@ -97,8 +99,7 @@ hipError_t launch_score_single_hidden(const float *a_term, const float *b_term, 
                                       const float *xp_row, const float *xc_row, hipStream_t st);
 hipError_t launch_grid_rows(const ab_model_desc *d, const float *part, const float *cred, int P, int Q,
                             float *xp_row, float *xc_row, int64_t rows, hipStream_t st);
-hipError_t launch_chosen_pair(const ab_model_desc *d, const ab_grid *grid, const int32_t *best_idx,
-                              float *xp_sel, float *xc_sel, int64_t S, hipStream_t st);
+hipError_t launch_chosen_pair(const ChosenArgs &a, const int32_t *best_idx, int64_t S, hipStream_t st);
 hipError_t launch_output_v(int dtype, const float *h_last, const float *a_term, const float *wp, const float *wc,
                            const float *xp_sel, const float *xc_sel, const void *W, const float *b, int H, int n_out,
                            const int32_t *best_idx, float *V, int64_t S, hipStream_t st);

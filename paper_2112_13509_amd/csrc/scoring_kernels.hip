@@ -2,6 +2,7 @@
 // candidate term, weight packing, the shared per-tensor encoder, score assembly and argmax.
 #include "internal.hpp"
 #include <type_traits>
+#include <string.h>
 
 namespace ab {
 
@@ -257,13 +258,8 @@ hipError_t launch_grid_rows(const ab_model_desc *d, const float *part, const flo
 // scenario the hidden chain is run once more (one row per scenario) and the output layer applied unit by unit.
 // ------------------------------------------------------------------------------------------------
 // The chosen candidate's transformed pair (phi(S_p), phi(S_c)) per scenario; NaN where nothing was chosen.
-struct ChosenArgs { const float *part, *cred; int32_t P, Q, per_scenario; ab_enc enc_part, enc_cred;
-                    const int32_t *best_idx; float *xp_sel, *xc_sel; int64_t S; };
-__global__ __launch_bounds__(256) void chosen_pair_kernel(const ChosenArgs a)
+__device__ __forceinline__ void chosen_pair(const ChosenArgs &a, int64_t s, int c)
 {
-    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (s >= a.S) return;
-    const int c = a.best_idx[s];
     float xp = __builtin_nanf(""), xc = __builtin_nanf("");
     if (c >= 0 && c < a.P * a.Q) {
         const int p = c / a.Q, q = c - p * a.Q;
@@ -273,14 +269,16 @@ __global__ __launch_bounds__(256) void chosen_pair_kernel(const ChosenArgs a)
     a.xp_sel[s] = xp;
     a.xc_sel[s] = xc;
 }
+__global__ __launch_bounds__(256) void chosen_pair_kernel(const ChosenArgs a, const int32_t *best_idx, int64_t S)
+{
+    const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (s < S) chosen_pair(a, s, best_idx[s]);
+}
 
-hipError_t launch_chosen_pair(const ab_model_desc *d, const ab_grid *grid, const int32_t *best_idx,
-                              float *xp_sel, float *xc_sel, int64_t S, hipStream_t st)
+hipError_t launch_chosen_pair(const ChosenArgs &a, const int32_t *best_idx, int64_t S, hipStream_t st)
 {
     if (S == 0) return hipSuccess;
-    ChosenArgs a{grid->partition_bytes, grid->credit_mult, grid->P, grid->Q, grid->per_scenario,
-                 d->enc_partition, d->enc_credit, best_idx, xp_sel, xc_sel, S};
-    chosen_pair_kernel<<<(unsigned)((S + 255) / 256), 256, 0, st>>>(a);
+    chosen_pair_kernel<<<(unsigned)((S + 255) / 256), 256, 0, st>>>(a, best_idx, S);
     return hipGetLastError();
 }
 
@@ -398,6 +396,7 @@ struct FinishArgs {
     int32_t *best_idx; float *best_score;                    // may be NULL
     int32_t C;
     int32_t vec;                                             // `partial` is 16-byte aligned
+    ChosenArgs chosen;                                       // xp_sel: also the chosen candidate's pair
 };
 
 __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
@@ -459,6 +458,7 @@ __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
         for (int w = 1; w < 4; ++w) amax_take(bv, bi, sv[w], si[w]);
         a.best_idx[s] = (bi == AB_NONE) ? -1 : bi;
         if (a.best_score) a.best_score[s] = (bi == AB_NONE) ? __uint_as_float(0x7fc00000u) : bv;
+        if (a.chosen.xp_sel) chosen_pair(a.chosen, s, (bi == AB_NONE) ? -1 : bi);
     }
 }
 
@@ -506,6 +506,7 @@ __global__ __launch_bounds__(256) void finish_select_wave_kernel(const FinishArg
     if (lane == 0) {
         a.best_idx[s] = (bi == AB_NONE) ? -1 : bi;
         if (a.best_score) a.best_score[s] = (bi == AB_NONE) ? __uint_as_float(0x7fc00000u) : bv;
+        if (a.chosen.xp_sel) chosen_pair(a.chosen, s, (bi == AB_NONE) ? -1 : bi);
     }
 }
 
@@ -1169,15 +1170,17 @@ static int64_t fill_prep_args(PrepArgs &a, const ab_model_desc *d, const void *W
 
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,
                                 float *scores, int64_t score_stride, int32_t *best_idx, float *best_score,
-                                int64_t S, int C, hipStream_t st)
+                                int64_t S, int C, const ChosenArgs *chosen, hipStream_t st)
 {
     if (S == 0) return hipSuccess;
     FinishArgs a;
+    if (chosen) a.chosen = *chosen;
+    else memset(&a.chosen, 0, sizeof(a.chosen));
     a.partial = partial; a.nt = nt; a.row_stride = row_stride; a.b_out = b_out; a.scores = scores;
     a.score_stride = score_stride; a.best_idx = best_idx; a.best_score = best_score; a.C = C;
     a.vec = ((uintptr_t)partial & 15) == 0 && row_stride * nt % 4 == 0;
     const unsigned wave_blocks = (unsigned)((S + 3) / 4);
-    if (C <= 1024 && nt == 1 && !b_out && !scores && best_idx) {
+    if (C <= 1024 && nt == 1 && !b_out && !scores && best_idx && !chosen) {
         launch_decide_rows16(a, partial, row_stride, S, st);
     } else if (C <= 1024 && nt == 1)
         finish_select_wave_kernel<1><<<wave_blocks, 256, 0, st>>>(a, S);

@@ -203,3 +203,19 @@ def test_table1_record_of_a_sixteen_worker_job(dtype, S, L, hidden):
     errv = np.abs(V - refv).max() / np.abs(refv).max()
     print("Table 1 record, 16 workers, %s: score err %.3g, exact-argmax fraction %.2f, V err %.3g" % (dtype, err, frac, errv))
     assert errv <= TOL[dtype]
+
+
+@pytest.mark.parametrize("S,P,Q", [(4096, 3, 3), (4097, 3, 3), (1100, 41, 25)])
+def test_chosen_pair_with_the_selection_and_alone(S, P, Q):
+    """The chosen candidate's pair comes from the selection while all scenarios fit the second pass's room (4096), from a
+    launch of its own beyond; grids per scenario, rows of up to and beyond 1024 candidates, two chunks of scenarios."""
+    w = wl.make_scoring("v-pair", S, 4, [64, 64], P, Q, 16e3, 64e6, 1.0, 16.0, False, "f32", seed=S)
+    w = with_worker_outputs(w, 3, seed=4)
+    rng = np.random.default_rng(S)
+    part = np.exp(rng.uniform(np.log(16e3), np.log(64e6), (S, P))).astype(np.float32)
+    cred = rng.uniform(1.0, 16.0, (S, Q)).astype(np.float32)
+    w.dyn[S - 1, 1, 0] = np.nan
+    _, idx, best, V = Scorer(w).run(want_v=True, part=part, cred=cred)
+    ref = orc.predict_v(oracle_model(w), w.dyn, w.scal, part, cred, idx)
+    assert idx[S - 1] == -1 and np.isnan(V[S - 1]).all() and (idx[:-1] >= 0).all()
+    assert np.abs(V[:-1] - ref[:-1]).max() <= TOL["f32"] * np.abs(ref[:-1]).max()
