@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libautobyte.so")
-SOURCES = ["api.hip", "gemm_launch.hip", "gemm_big.hip", "gemm_span.hip", "gemm_slim.hip", "scoring_kernels.hip", "update.hip", "update_rows.hip"]
+SOURCES = ["api.hip", "gemm_launch.hip", "gemm_big.hip", "gemm_span.hip", "gemm_slim.hip", "gemm_split.hip", "scoring_kernels.hip", "update.hip", "update_rows.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -77,7 +77,7 @@ def build_host_sanitized(verbose: bool = False) -> str:
     error paths; a process that loads it needs clang's ASan runtime preloaded."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    plain = ["gemm_big.hip", "gemm_span.hip", "gemm_slim.hip", "scoring_kernels.hip", "update_rows.hip"]
+    plain = ["gemm_big.hip", "gemm_span.hip", "gemm_slim.hip", "gemm_split.hip", "scoring_kernels.hip", "update_rows.hip"]
     for src in plain:
         if not os.path.exists(os.path.join(objdir, src.replace(".hip", ".o"))):
             _compile(src, objdir)

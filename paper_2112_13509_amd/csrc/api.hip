@@ -28,6 +28,13 @@ static int pick_tile(int64_t M, int N)
 static const int64_t kSlimTiles = 512;
 static bool slim(int64_t M, int N) { return (M + 31) / 32 * (N / 32) <= kSlimTiles; }
 
+// fp32 products of at least so many 128 x 128 (or 128 x 64) tiles go to gemm_split.hip, smaller ones (and all 32 x 32 tiles
+// above) to the fp32 instruction, whose smaller tiles fill the chip.  Whole calls, 32 layers of statistics, fp32 -> split:
+// 256-256 with 9000 rows (142 tiles) 31.2 -> 30.4 us, 16000 (248) 36.7 -> 32.0, 60000 88 -> 56, 4.2 M 4625 -> 2690;
+// 128-128 with 16000 rows (124 tiles) 22.7 -> 23.5, 30000 (234) 27.0 -> 24.1; 64-64 with 16000 (124) 17.8 -> 18.6, 30000
+// (234) 19.3 -> 19.1, 60000 21.8 -> 20.6; 256-128-64 with 16000 34.8 -> 39.4, 30000 47.2 -> 42.7.
+static const int64_t kSplitTiles = 192;
+
 static ab_status check_desc(const ab_model_desc *d)
 {
     if (!d) return AB_ERR_NULL;
@@ -65,6 +72,7 @@ struct ScorePlan {
     int dtype, Fs, F, Kp, D, base;
     int H[AB_MAX_HIDDEN];
     int tile[AB_MAX_HIDDEN];      // tile of hidden GEMM k (k >= 1)
+    int split[AB_MAX_HIDDEN];     // hidden GEMM k runs on gemm_split.hip with so many column groups, or 0
     int big[AB_MAX_HIDDEN];       // hidden GEMM k runs on a 256x256 bf16 kernel: BIG_TILE, BIG_SPAN, or 0
     int tile_a;                   // tile of the scenario-term GEMM
     int nt_last;
@@ -145,6 +153,17 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
         }
         p->tile[k] = TILE_SLIM;
     }
+    // fp32 products of enough work: bf16 matrix cores with split operands (gemm_split.hip).  A work-group takes one column
+    // tile; of the last product all of them where the room for the partial sums does not hold one value a tile.
+    for (int k = 1; k < p->D; ++k) {
+        const int bn = p->H[k] % 128 == 0 ? 128 : 64, n_tiles = p->H[k] / bn;
+        if (p->dtype != AB_F32 || p->tile[k] == TILE_SLIM || (p->chunk_rows + 127) / 128 * n_tiles < kSplitTiles) continue;
+        p->split[k] = n_tiles;
+        if (k == p->D - 1) {
+            if (p->nt_last < n_tiles) p->split[k] = 1;
+            p->nt_last = p->split[k];
+        }
+    }
     return AB_OK;
 }
 
@@ -155,6 +174,13 @@ int scoring_big_kernel(const ab_model_desc *d, int64_t S, int32_t C, int k)
 {
     ScorePlan p;
     return plan_scoring(d, S, C, &p) == AB_OK ? p.big[k] : -1;
+}
+
+// How many column groups hidden product k takes on gemm_split.hip (for tests); 0: not there.
+int scoring_split_groups(const ab_model_desc *d, int64_t S, int32_t C, int k)
+{
+    ScorePlan p;
+    return plan_scoring(d, S, C, &p) == AB_OK ? p.split[k] : -1;
 }
 
 static inline bool misaligned(const void *p, size_t a) { return ((uintptr_t)p % a) != 0; }
@@ -280,7 +306,7 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
     float *a_term = (float *)(ws + p.off_aterm);
     // the candidate term as a table [C, H]: only the generic tiles and the scorer with one hidden layer read it (a
     // per-scenario grid comes in factored form there too)
-    const bool table = !grid->per_scenario && (p.D == 1 || (!p.big[1] && p.tile[1] != TILE_SLIM));
+    const bool table = !grid->per_scenario && (p.D == 1 || (!p.big[1] && !p.split[1] && p.tile[1] != TILE_SLIM));
     float *b_term = table ? (float *)(ws + p.off_bterm) : nullptr;
     float *w_out_f = (float *)(ws + p.off_wout), *partial = (float *)(ws + p.off_partial);
     float *cfg_vec = (float *)(ws + p.off_cfgv);
@@ -389,7 +415,9 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                                      : (last ? "gemm_hidden_last" : "gemm_hidden_mid"),
                               2.0 * rows * p.H[k] * p.H[k - 1], 0, st);
                 const int amode = k == 1 ? AMODE_GEN : AMODE_LOAD, epi = last ? EPI_SCORE : EPI_STORE;
-                if (p.big[k] == BIG_SPAN)
+                if (p.split[k])
+                    AB_HIP(launch_gemm_split(amode, epi, g, p.split[k], st));
+                else if (p.big[k] == BIG_SPAN)
                     AB_HIP(launch_gemm_span(epi, g, st));
                 else if (p.big[k] && gemm_big_supported(dt, amode, epi, g))
                     AB_HIP(launch_gemm_big(amode, epi, g, st));

@@ -68,6 +68,10 @@ hipError_t launch_gemm(int dtype, int tile, int amode, int epi, GemmArgs g, hipS
 // A generated operand is taken in its factored form, whichever amode names it.
 hipError_t launch_gemm_slim(int dtype, int amode, int epi, const GemmArgs &g, hipStream_t st);
 
+// fp32 products on the bf16 matrix cores (gemm_split.hip): EPI_STORE (with ReLU) or EPI_SCORE, with a bias; the column tiles
+// are shared out among `n_groups` work-groups a row panel, which is also the row stride of the partial sums.
+hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, hipStream_t st);
+
 // The 256x256 bf16 kernel (gemm_big.hip): EPI_STORE (bf16 out) or EPI_SCORE, AMODE_LOAD or AMODE_GEN.
 bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g);
 hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st);
