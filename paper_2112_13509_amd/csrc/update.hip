@@ -33,6 +33,7 @@ struct UpdatePlan {
     size_t total;
     bool rows;                          // row-block form
     bool by_batch;                      // the batch and the frozen layers decide the form
+    bool one_step;                      // gradients and Adam in one launch
     int grad_tile, rows_splits, out_splits;      // its gradient launch: tile width, batch splits of the tiles and of the output unit
 };
 
@@ -93,7 +94,22 @@ static bool rows_form(const RowsArgs &shape, int dtype, int64_t B, int first, bo
     return B > 8192 || B >= (f32 ? 7168 : 6144);
 }
 
-static void plan_rows(UpdatePlan *p)
+// Gradients and Adam in one launch (a work-group per tile of 64 x 64, in fp32 32 x 32, with the whole batch), or two launches with
+// the batch split between work-groups: one saves a launch and the partial sums' way through memory, two keep all CUs busy however
+// few tiles there are.  The line lies where the tiles' own time exceeds what is saved.  One / two, us a step, by trainable tiles:
+//   bf16, none (output unit alone): 66-512-512-1, 2000 rows 24.8 / 26.2, 4096 31.2 / 29.8; 44: 390-256-256-1 1000 rows
+//     30.8 / 31.1, 1500 33.4 / 33.0, 3072 40.5 / 35.9; 72: 66-512-512-1 1400 rows 40.3 / 42.5, 2000 44.1 / 43.6, 4096 52.9 / 47.3;
+//     184: 390-512-512-512-1 500 rows 49.6 / 57.1, 4096 65.3 / 66.6, 6000 105 / 104; 368: 390-1024-1024, first layer frozen, 1000 rows
+//     61.5 / 67.9, 2000 68.3 / 70.5, 3072 78.5 / 75.0
+//   fp32, 28: 126-64-64-1 200 rows 25.0 / 29.7, 1000 28.9 / 30.9, 1400 31.7 / 32.3, 2000 35.9 / 34.0; 160: 366-256-256-1 700 rows
+//     42.1 / 46.1, 2000 52.9 / 55.4; 352: 390-512-256-1 1000 rows 69.9 / 71.4, 2000 81.4 / 80.3
+static bool one_step_form(bool f32, int tiles, int64_t B)
+{
+    if (f32) return B <= (tiles >= 128 && tiles <= 256 ? 2048 : 1024);
+    return B <= (tiles == 0 ? 2048 : tiles < 64 ? 1024 : tiles < 128 ? 1536 : tiles <= 192 ? 4096 : 2048);
+}
+
+static void plan_rows(UpdatePlan *p, int first)
 {
     const size_t es = elem_size(p->dtype);
     size_t off = 0;
@@ -116,6 +132,9 @@ static void plan_rows(UpdatePlan *p)
     p->rows_splits = splits(tiles64, 128, 256);
     p->out_splits = p->n_out > 1 ? splits(p->H[p->D - 1] / 64, 256, 256) : splits(p->H[p->D - 1] / 64, 64, 64);
     p->grad_tile = tiles64 * p->rows_splits >= 512 ? 128 : 64;       // 128-wide tiles once they occupy the chip
+    int tiles = 0;
+    for (int k = first; k < p->D; ++k) tiles += (int)(p->H[k] * es / 128) * (int)(p->in_w[k] * es / 128);
+    p->one_step = one_step_form(p->dtype != AB_BF16, tiles, p->B);
     p->off_scal = take(64);
     p->off_x = take((size_t)p->Bp * p->Kp * es);
     p->off_dout = take((size_t)p->Bp * p->n_out * 4);
@@ -184,7 +203,7 @@ static void plan_update(const ab_model_desc *d, int64_t B, int first, UpdatePlan
         shape.l[k].in = p->in_w[k]; shape.l[k].out = p->H[k];
     }
     p->rows = update_rows_supported(shape, p->dtype) && rows_form(shape, p->dtype, B, first, &p->by_batch);
-    if (p->rows) plan_rows(p);
+    if (p->rows) plan_rows(p, first);
     else plan_layers(p);
 }
 
@@ -197,7 +216,7 @@ size_t update_workspace_bytes(const ab_model_desc *d, int64_t B)
     size_t total = p.total;
     if (p.by_batch) {                                   // a shorter batch, or one with frozen layers, may take the other form
         if (p.rows) plan_layers(&p);
-        else plan_rows(&p);
+        else plan_rows(&p, 0);
         if (p.total > total) total = p.total;
     }
     return total;
@@ -210,6 +229,14 @@ int update_gradient_plan(const ab_model_desc *d, int64_t B, int first, int what)
     UpdatePlan p;
     plan_update(d, B, first, &p);
     return !p.rows ? 0 : what == 0 ? p.grad_tile : what == 1 ? p.rows_splits : p.out_splits;
+}
+
+// Whether a step in row-block form takes its gradients and Adam in one launch (for tests).
+bool update_one_step(const ab_model_desc *d, int64_t B, int first)
+{
+    UpdatePlan p;
+    plan_update(d, B, first, &p);
+    return p.rows && p.one_step;
 }
 
 // The form that a step takes (for tests).
@@ -898,6 +925,28 @@ static ab_status run_update(const ab_model_desc *d, ab_params *prm, const Update
         {
             TraceScope ts("upd_gemm_rows", flops, 0, st);
             AB_HIP(launch_update_rows(dt, a, st));
+        }
+        if (p.one_step) {
+            StepArgs sa;
+            memset(&sa, 0, sizeof(sa));
+            double n_param = 0.0;
+            for (int k = k0; k < D; ++k) {
+                StepArgs::L &l = sa.l[sa.n++];
+                l.d = ws + p.off_d[k]; l.h_in = k == 0 ? x : (const void *)(ws + p.off_h[k - 1]);
+                l.W = AdamTensor{prm->W_master[k], prm->adam_mW[k], prm->adam_vW[k], (void *)prm->W[k]};
+                l.b = AdamTensor{prm->b[k], prm->adam_mb[k], prm->adam_vb[k], nullptr};
+                l.H = p.H[k]; l.in_w = p.in_w[k]; l.cols = k == 0 ? p.F : p.in_w[k]; l.start = sa.n_tiles;
+                sa.n_tiles += (p.H[k] * (int)esz / 128) * (p.in_w[k] * (int)esz / 128);
+                n_param += (double)p.H[k] * (l.cols + 1);
+            }
+            sa.B = B; sa.Bp = Bp; sa.h_last = ws + p.off_h[D - 1]; sa.dout = dout; sa.lossrow = a.lossrow;
+            sa.Wo = AdamTensor{prm->W_master[D], prm->adam_mW[D], prm->adam_vW[D], (void *)prm->W[D]};
+            sa.bo = AdamTensor{prm->b[D], prm->adam_mb[D], prm->adam_vb[D], nullptr};
+            sa.loss_out = loss_out; sa.H_last = p.H[D - 1]; sa.n_out = p.n_out; sa.n_out_blocks = (unsigned)(p.H[D - 1] / 16);
+            sa.scal = scal; sa.lr = lr; sa.beta1 = beta1; sa.beta2 = beta2; sa.eps = eps;
+            TraceScope ts("upd_gemm_grads_adam", grad_flops, 0, st);
+            AB_HIP(launch_update_step(dt, sa, st));
+            return AB_OK;
         }
         {
             TraceScope ts("upd_gemm_grads", grad_flops, 0, st);

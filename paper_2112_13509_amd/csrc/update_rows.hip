@@ -802,4 +802,330 @@ hipError_t launch_update_grads(int dtype, int tile, const GradsArgs &a, hipStrea
     return hipGetLastError();
 }
 
+
+// ---------------------------------------------------------------------------------------------
+// Gradients and Adam in one launch: a work-group of eight wavefronts owns a tile of one weight matrix (128 bytes of the
+// compute type wide and as many rows: 64 x 64 in bf16, 32 x 32 in fp32) over the whole batch, and takes the Adam step for it.
+// The wavefronts share the batch, a share each: private rings of two 8 KB slabs (32 batch rows of both operands) by DMA, no
+// barrier before the partial tiles meet in LDS, in share order.  Against the split launch above it saves the partial sums'
+// way through memory (eight copies of every gradient written and read again) and a launch.
+// By kernel time, 390-512-512-512-1 in bf16: 64 rows 9.2 us (the rest of a large batch's time: old values in, partial tiles
+// together, Adam, out), 1000 rows 12.2, 4096 22.2, i.e. 3.2 us a thousand rows: 35 bytes a clock and CU, each of them into
+// LDS and out again (gradients and Adam as two launches: 4096 rows 17.6 + 9.5).  The output unit's work-groups: one output 4.2
+// us for 64 rows, 11.7 for 4096; eight 6.0 and 14.3.
+// ---------------------------------------------------------------------------------------------
+struct AdamRates { float lr, beta1, beta2, eps, c1, c2; };
+template <typename T>
+__device__ __forceinline__ void adam_store(const AdamTensor &t, const AdamRates &r, int64_t e, float g, float m, float v, float w)
+{
+    m = r.beta1 * m + (1.f - r.beta1) * g;
+    v = r.beta2 * v + (1.f - r.beta2) * g * g;
+    w = w - r.lr * (m / r.c1) / (sqrtf(v / r.c2) + r.eps);
+    t.m[e] = m;
+    t.v[e] = v;
+    t.w[e] = w;
+    if (t.wc) {
+        if constexpr (sizeof(T) == 2) ((uint16_t *)t.wc)[e] = (uint16_t)(pack_bf16x2(w, 0.f) & 0xffffu);
+        else ((float *)t.wc)[e] = w;
+    }
+}
+
+// The output unit's weights: sixteen columns of all its rows, on the vector ALUs (its deltas are fp32).  A wavefront takes an
+// eighth of the batch, a lane every RG-th row of it and 16 bytes of columns; the deltas come by DMA (as per-lane loads they kept
+// the address units busy: 4096 rows, eight outputs 28 us), the next piece of both under the sums.  OW: outputs at a time.
+template <typename T, int OW>
+__device__ __forceinline__ void output_step(const StepArgs &a, const AdamRates &rt, unsigned id, unsigned char *smem)
+{
+    constexpr int ES = sizeof(T), E = 16 / ES, CH = 16 / E, RG = 64 / CH, U = OW == 1 ? 8 : 4, ROWS = RG * U;
+    constexpr int STAGE = OW == 1 ? 1024 : ROWS * AB_MAX_OUTPUTS * 4;     // staged deltas, whole requests of 1 KB
+    static_assert(STAGE >= ROWS * OW * 4 && STAGE % 1024 == 0, "a piece's deltas fit");
+    const int t = threadIdx.x, lane = t & 63, ch = lane % CH, rg = lane / CH, c0 = (int)id * 16;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), n_out = OW == 1 ? 1 : a.n_out;
+    unsigned char *stage = smem + wave * (2 * STAGE);
+    float *red = (float *)(smem + 8 * (2 * STAGE));          // [512]
+    const int64_t r0 = a.Bp / 8 * wave, r1 = r0 + a.Bp / 8;              // (rows of the padding are zeros on both sides)
+    const unsigned char *src = (const unsigned char *)a.h_last + (c0 + ch * E) * ES;
+    const int64_t pitch = (int64_t)a.H_last * ES, last = a.Bp * n_out * 4 - 16;
+    for (int w0 = 0; w0 < n_out; w0 += OW) {
+        // the old values of what this thread will step (outputs w0 + t / 16, column t & 15), under the sums
+        const int mw = w0 + (t >> 4);
+        const bool mine = t < OW * 16 && mw < n_out;
+        const int64_t e = mine ? (int64_t)mw * a.H_last + c0 + (t & 15) : 0;
+        const float m0 = a.Wo.m[e], v0 = a.Wo.v[e], x0 = a.Wo.w[e];
+        float acc[OW][E];
+#pragma unroll
+        for (int w = 0; w < OW; ++w)
+#pragma unroll
+            for (int q = 0; q < E; ++q) acc[w][q] = 0.f;
+        i32x4 h[U];
+        auto load = [&](int set, int64_t b) {                // (past the batch: its last row, whose sums are not taken)
+            unsigned char *to = stage + set * STAGE;
+            for (int o = 0; o < ROWS * n_out * 4; o += 1024)
+                dma16<false>((const unsigned char *)a.dout + min(b * n_out * 4 + o + lane * 16, last), to + o);
+#pragma unroll
+            for (int i = 0; i < U; ++i) h[i] = *(const i32x4 *)(src + min(b + rg + RG * i, a.Bp - 1) * pitch);
+        };
+        load(0, r0);
+        int set = 0;
+        for (int64_t b = r0; b < r1; b += ROWS, set ^= 1) {
+            i32x4 g[U];
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < U; ++i) g[i] = h[i];
+            if (b + ROWS < r1) load(set ^ 1, b + ROWS);
+            const float *dl = (const float *)(stage + set * STAGE);
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                float hv[E];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if constexpr (ES == 2) {
+                        hv[2 * q] = __uint_as_float((uint32_t)g[i][q] << 16);
+                        hv[2 * q + 1] = __uint_as_float((uint32_t)g[i][q] & 0xffff0000u);
+                    } else hv[q] = __uint_as_float((uint32_t)g[i][q]);
+                }
+                const bool in = b + rg + RG * i < r1;
+#pragma unroll
+                for (int w = 0; w < OW; ++w) {
+                    const float d = dl[(rg + RG * i) * n_out + min(w0 + w, n_out - 1)], dv = in ? d : 0.f;
+#pragma unroll
+                    for (int q = 0; q < E; ++q) acc[w][q] = fmaf(dv, hv[q], acc[w][q]);
+                }
+            }
+        }
+        // the lanes' sums meet in LDS (each wavefront's where its deltas were: rows of OW x 16, 16-byte chunk c of row r at
+        // c ^ r), are added in PARTS runs of rows, then over the runs
+        constexpr int NC = OW * 4, PARTS = 512 / (OW * 16);
+        auto at = [](int r, int c) { return r * (NC * 16) + ((c ^ (r & (NC - 1))) << 4); };
+        static_assert(RG * NC * 16 <= 2 * STAGE, "a wavefront's sums fit its deltas' room");
+#pragma unroll
+        for (int w = 0; w < OW; ++w)
+#pragma unroll
+            for (int q = 0; q < E / 4; ++q)
+                *(f32x4 *)(stage + at(rg, w * 4 + ch * (E / 4) + q)) = f32x4{acc[w][4 * q], acc[w][4 * q + 1], acc[w][4 * q + 2], acc[w][4 * q + 3]};
+        __syncthreads();
+        {
+            const int v = t % (OW * 16), p = t / (OW * 16);
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8 * RG / PARTS; ++i) {
+                const int r = p * (8 * RG / PARTS) + i;
+                s += *(const float *)(smem + (r / RG) * (2 * STAGE) + at(r % RG, v >> 2) + (v & 3) * 4);
+            }
+            red[t] = s;
+        }
+        __syncthreads();
+        if (mine) {
+            float g = 0.f;
+#pragma unroll
+            for (int q = 0; q < PARTS; ++q) g += red[q * OW * 16 + t];
+            adam_store<T>(a.Wo, rt, e, g, m0, v0, x0);
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(512) void update_step_kernel(const StepArgs a)
+{
+    constexpr int ES = sizeof(T), W = 128 / ES, MB = W / 32, BK = 32, SLAB = 8192, RING = 2 * SLAB;
+    constexpr int EPT = W * W / 512;                        // elements of the tile a thread steps
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int t = threadIdx.x, lane = t & 63, l31 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // the arguments' cache lines, all requested at once (each would be a miss of its own at its first use)
+    {
+        typedef __attribute__((address_space(4))) const uint32_t karg;
+        karg *ka = (karg *)__builtin_amdgcn_kernarg_segment_ptr();
+        uint32_t sink = 0;
+#pragma unroll
+        for (int i = 0; i < (int)sizeof(StepArgs); i += 64) sink ^= ka[i / 4];
+        asm volatile("" ::"s"(sink));
+    }
+    const AdamRates rt{a.lr, a.beta1, a.beta2, a.eps, a.scal[0], a.scal[1]};
+    unsigned id = blockIdx.x;
+    if (id < a.n_out_blocks) {
+        if (a.n_out == 1) output_step<T, 1>(a, rt, id, smem);
+        else              output_step<T, 8>(a, rt, id, smem);
+        return;
+    }
+    id -= a.n_out_blocks;
+    if (id < (unsigned)a.n_out + 1) {                        // the output unit's biases and the loss
+        const int w = (int)id;
+        float v = 0.f;
+        if (w < a.n_out) {
+#pragma unroll 8
+            for (int64_t b = t; b < a.B; b += 512) v += a.dout[b * a.n_out + w];
+        } else {
+#pragma unroll 8
+            for (int64_t b = t; b < a.B; b += 512) v += a.lossrow[b];
+        }
+        v = wave_sum(v);
+        float *red = (float *)smem;
+        if (lane == 0) red[wave] = v;
+        __syncthreads();
+        if (t == 0) {
+            const float s = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+            if (w < a.n_out) adam_store<T>(a.bo, rt, w, s, a.bo.m[w], a.bo.v[w], a.bo.w[w]);
+            else if (a.loss_out) a.loss_out[0] = s / (float)a.B;
+        }
+        return;
+    }
+    id -= (unsigned)a.n_out + 1;
+
+    // ---- tiles: each XCD takes a run of neighbours (they share panels of deltas and inputs in its L2)
+    const int per = (a.n_tiles + 7) / 8, local = (int)(id >> 3);
+    int tile = (int)(id & 7) * per + local, k = 0;
+    if (tile >= a.n_tiles) return;
+    while (k + 1 < a.n && tile >= a.l[k + 1].start) ++k;
+    tile -= a.l[k].start;
+    const int H = a.l[k].H, in_w = a.l[k].in_w, cols = a.l[k].cols, tiles_n = in_w / W, tm = tile / tiles_n, tn = tile - tm * tiles_n;
+    const int slabs = (int)(a.Bp / BK), s0 = slabs * wave / 8, s1 = slabs * (wave + 1) / 8;
+
+    // the old values of this thread's elements (rows i * 512 / W + t / W, column t % W), under the products
+    const AdamTensor tw = a.l[k].W;
+    const int col = tn * W + t % W, e0 = (tm * W + t / W) * cols + col;
+    float om[EPT], ov[EPT], ow[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        const int e = col < cols ? e0 + i * (512 / W) * cols : 0;
+        om[i] = tw.m[e]; ov[i] = tw.v[e]; ow[i] = tw.w[e];
+    }
+
+    // DMA: four requests of eight rows an operand; bf16: chunk c of row r sits at c ^ 2 (r & 3) (the transposing reads take four
+    // rows x 32 bytes at a time), fp32: rows as they are
+    auto chunk = [](int row, int c) { return ES == 2 ? c ^ ((row & 3) << 1) : c; };
+    unsigned char *ring = smem + wave * RING;
+    const unsigned char *pa = (const unsigned char *)a.l[k].d + tm * 128, *pb = (const unsigned char *)a.l[k].h_in + tn * 128;
+    const uint32_t lda = H * ES, ldb = in_w * ES, c16 = chunk(lane >> 3, lane & 7) * 16;      // (8 i rows on: the same chunk)
+    const uint32_t off_a = (lane >> 3) * lda + c16, off_b = (lane >> 3) * ldb + c16;
+    auto fetch = [&](int slab, int slot) {
+        if (slab > s1 - 1) slab = s1 - 1;                    // (past the end: the last one again, nobody reads it)
+        const unsigned char *qa = pa + (int64_t)slab * BK * lda, *qb = pb + (int64_t)slab * BK * ldb;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            dma16<false>(qa + off_a + i * 8 * lda, ring + slot * SLAB + i * 1024);
+            dma16<false>(qb + off_b + i * 8 * ldb, ring + slot * SLAB + 4096 + i * 1024);
+        }
+    };
+    f32x16 acc[MB][MB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+    f32x16 bacc[MB];                                         // bias sums of layer's first column tiles: every column the same
+    float bsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) bacc[i][q] = 0.f;
+    int o_f[MB];                                             // this lane's place in an operand's slab, per block of 32 columns
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        if (ES == 2) {
+            const int q = lane & 15, sub = (lane >> 4) & 1, row = 8 * half + (q >> 2), in = sub * 2 + ((q & 3) >> 1);
+            o_f[i] = row * 128 + (chunk(row, i * 4 + in) << 4) + (q & 1) * 8;
+        } else o_f[i] = half * 128 + l31 * 4;
+    }
+    if (s0 < s1) {
+        fetch(s0, 0);
+        fetch(s0 + 1, 1);
+        for (int s = s0, slot = 0; s < s1; ++s, slot ^= 1) {
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            const unsigned char *sa = ring + slot * SLAB, *sb = sa + 4096;
+            if constexpr (ES == 2) {
+                uint2 f[4][4];
+                const unsigned char *p[4] = {sa + o_f[0], sa + o_f[MB - 1], sb + o_f[0], sb + o_f[MB - 1]};
+                lds_read_tr_4x4<128>(f, p);
+                fetch(s + 2, slot);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                    for (int i = 0; i < MB; ++i)
+#pragma unroll
+                        for (int j = 0; j < MB; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, join(f[i][2 * ks], f[i][2 * ks + 1])),
+                                                                                __builtin_bit_cast(bf16x8, join(f[2 + j][2 * ks], f[2 + j][2 * ks + 1])),
+                                                                                acc[i][j], 0, 0, 0);
+                if (tn == 0) {                               // bias sums: the same product with ones
+                    const bf16x8 ones = __builtin_bit_cast(bf16x8, i32x4{0x3f803f80, 0x3f803f80, 0x3f803f80, 0x3f803f80});
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int i = 0; i < MB; ++i)
+                            bacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, join(f[i][2 * ks], f[i][2 * ks + 1])), ones, bacc[i], 0, 0, 0);
+                }
+            } else {
+                float fa[BK / 2], fb[BK / 2];
+#pragma unroll
+                for (int ks = 0; ks < BK / 2; ++ks) {
+                    fa[ks] = *(const float *)(sa + o_f[0] + ks * 256);
+                    fb[ks] = *(const float *)(sb + o_f[0] + ks * 256);
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                fetch(s + 2, slot);
+#pragma unroll
+                for (int ks = 0; ks < BK / 2; ++ks) {
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[ks], fb[ks], acc[0][0], 0, 0, 0);
+                    if (tn == 0) bsum += fa[ks];             // (this lane's column, the rows of its half)
+                }
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // nothing is on its way into the ring
+    // partial tiles, a wavefront's in its own ring: column c of row r at c, in bf16 tiles c ^ 32 in rows with bit 2 set (the two
+    // halves of a wavefront write rows four apart)
+    auto at = [&](int q, int r, int c) { return (float *)(smem + q * RING) + r * W + (W == 64 ? c ^ ((r & 4) << 3) : c); };
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) *at(wave, i * 32 + 8 * (q >> 2) + 4 * half + (q & 3), j * 32 + l31) = acc[i][j][q];
+    float *bred = (float *)(smem + 8 * RING);                // [wavefront][half (fp32)][W]
+    if (tn == 0) {
+        if constexpr (ES == 2) {
+            if (l31 == 0) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) bred[wave * W + i * 32 + 8 * (q >> 2) + 4 * half + (q & 3)] = bacc[i][q];
+            }
+        } else bred[(wave * 2 + half) * W + l31] = bsum;
+    }
+    __syncthreads();
+    if (col < cols) {
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            float g = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) g += *at(q, i * (512 / W) + t / W, t % W);
+            adam_store<T>(tw, rt, e0 + i * (512 / W) * cols, g, om[i], ov[i], ow[i]);
+        }
+    }
+    if (tn == 0 && t < W) {
+        const AdamTensor &tb = a.l[k].b;
+        const int e = tm * W + t;
+        float g = 0.f;
+#pragma unroll
+        for (int q = 0; q < (ES == 2 ? 8 : 16); ++q) g += bred[q * W + t];
+        adam_store<T>(tb, rt, e, g, tb.m[e], tb.v[e], tb.w[e]);
+    }
+}
+
+hipError_t launch_update_step(int dtype, const StepArgs &a, hipStream_t st)
+{
+    constexpr int smem = 8 * 16384 + 4096;                   // rings, bias sums (or the output unit's)
+    auto kb = update_step_kernel<bf16_t>;
+    auto kf = update_step_kernel<float>;
+    static DeviceOnce once_b, once_f;
+    const hipError_t e = dtype == AB_BF16 ? ensure_dynamic_lds((const void *)kb, smem, once_b) : ensure_dynamic_lds((const void *)kf, smem, once_f);
+    if (e != hipSuccess) return e;
+    const unsigned blocks = a.n_out_blocks + (unsigned)a.n_out + 1 + (unsigned)(a.n_tiles + 7) / 8 * 8;
+    if (dtype == AB_BF16) kb<<<blocks, 512, smem, st>>>(a);
+    else                  kf<<<blocks, 512, smem, st>>>(a);
+    return hipGetLastError();
+}
+
 }  // namespace ab

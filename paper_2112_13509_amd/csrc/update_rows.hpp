@@ -43,6 +43,26 @@ struct GradsArgs {
     unsigned n_out_blocks, n_tile_blocks;    // work-groups of the output unit's gradient, of the tiles (n_out + 1 between them)
 };
 
+// The gradients launch that takes the Adam step as well: each work-group has the whole batch of its part.
+struct AdamTensor { float *w, *m, *v; void *wc; };                  // master, moments, compute-type copy (NULL for biases)
+struct StepArgs {
+    struct L {
+        const void *d, *h_in;                // deltas [Bp, H], the layer's inputs [Bp, in_w]
+        AdamTensor W, b;
+        int32_t H, in_w, cols, start;        // cols: of W itself (layer 0's inputs are padded); start: first tile of the layer
+    } l[AB_MAX_HIDDEN];
+    int32_t n, n_tiles;
+    int64_t B, Bp;
+    const void *h_last; const float *dout, *lossrow;
+    AdamTensor Wo, bo;
+    float *loss_out;                         // may be NULL
+    int32_t H_last, n_out;
+    unsigned n_out_blocks;
+    const float *scal;                       // {1 - beta1^t, 1 - beta2^t}
+    float lr, beta1, beta2, eps;
+};
+hipError_t launch_update_step(int dtype, const StepArgs &a, hipStream_t st);
+
 bool update_rows_supported(const RowsArgs &shape, int dtype);      // looks at D, n_out and the widths only
 hipError_t launch_update_rows(int dtype, RowsArgs a, hipStream_t st);
 hipError_t launch_update_grads(int dtype, int tile, const GradsArgs &a, hipStream_t st);     // tile: 64 or 128

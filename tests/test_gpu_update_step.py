@@ -1,0 +1,32 @@
+"""Gradients and Adam in one launch (csrc/update_rows.hip, update_step_kernel) and the two-launch form beside it: batches whose
+last shares are empty, one row, both sides of each line of the choice, inputs that are no multiple of a tile, every kind of output
+count (one; a piece of deltas that is no whole request; sixteen), frozen layers down to the output unit alone.  One step from a
+fresh state against the fp64 oracle, as in test_gpu_update_rows."""
+import pytest
+
+import test_gpu_update_rows as rows
+from paper_2112_13509_amd import workloads as wl
+from test_kernel_choice import one_step
+from paper_2112_13509_amd import binding as ab
+
+pytestmark = pytest.mark.gpu
+
+ONE = [
+    # dtype, layers, hidden, rows, workers, first trainable layer
+    ("bf16", 3, (64,), 2, 3, 0), ("f32", 3, (64,), 33, 3, 0), ("bf16", 9, (192, 64), 100, 5, 0), ("f32", 9, (192, 64), 100, 11, 0),
+    ("bf16", 19, (64, 64), 1024, 16, 0), ("f32", 19, (64, 64), 1024, 16, 0), ("bf16", 20, (512, 512), 1536, 0, 0),
+    ("bf16", 50, (512, 512, 512), 4096, 2, 0), ("bf16", 20, (512, 512), 2048, 16, 2), ("f32", 20, (128, 128), 1000, 1, 2),
+    ("bf16", 127, (1024, 512, 256), 700, 0, 0), ("f32", 128, (320, 256), 2048, 7, 0),
+]
+TWO = [
+    ("bf16", 19, (64, 64), 1025, 0, 0), ("f32", 19, (64, 64), 1025, 2, 0), ("bf16", 20, (512, 512), 1537, 3, 0), ("bf16", 20, (512, 512), 2049, 1, 2),
+    ("bf16", 100, (576, 448, 512), 4160, 0, 0), ("bf16", 100, (512, 512, 512), 4097, 4, 1), ("f32", 128, (320, 256), 2049, 0, 0),
+]
+
+
+@pytest.mark.parametrize("dtype,L,hidden,B,n,first", ONE + TWO)
+def test_step(dtype, L, hidden, B, n, first, monkeypatch):
+    d = ab.desc_from_workload(wl.make_update(N=64, batch=64, L=L, hidden=hidden, dtype=dtype, n_workers=n))
+    assert one_step(d, B, first) == ((dtype, L, hidden, B, n, first) in ONE)
+    monkeypatch.setattr(rows, "CASES", [])                    # (the allowance for ReLU flips by fp32 rounding: for these too)
+    rows.test_step(dtype, L, hidden, B, n, first)
