@@ -906,20 +906,20 @@ __device__ __forceinline__ void output_step(const StepArgs &a, const AdamRates &
         __syncthreads();
         {
             const int v = t % (OW * 16), p = t / (OW * 16);
-            float s = 0.f;
+            float s[4] = {0.f, 0.f, 0.f, 0.f};               // (four chains: less rounding than one)
 #pragma unroll
             for (int i = 0; i < 8 * RG / PARTS; ++i) {
                 const int r = p * (8 * RG / PARTS) + i;
-                s += *(const float *)(smem + (r / RG) * (2 * STAGE) + at(r % RG, v >> 2) + (v & 3) * 4);
+                s[i & 3] += *(const float *)(smem + (r / RG) * (2 * STAGE) + at(r % RG, v >> 2) + (v & 3) * 4);
             }
-            red[t] = s;
+            red[t] = (s[0] + s[1]) + (s[2] + s[3]);
         }
         __syncthreads();
         if (mine) {
-            float g = 0.f;
+            float g[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int q = 0; q < PARTS; ++q) g += red[q * OW * 16 + t];
-            adam_store<T>(a.Wo, rt, e, g, m0, v0, x0);
+            for (int q = 0; q < PARTS; ++q) g[q & 3] += red[q * OW * 16 + t];
+            adam_store<T>(a.Wo, rt, e, (g[0] + g[1]) + (g[2] + g[3]), m0, v0, x0);
         }
     }
 }
