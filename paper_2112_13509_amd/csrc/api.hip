@@ -169,6 +169,22 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
 
 #define AB_HIP(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return AB_ERR_DEVICE; } while (0)
 
+// Flat statistics of few scenarios: transform and the scenario term's product in the first launch (scenario_term_kernel), every
+// column tile transforming its scenarios' statistics anew; with more of them that costs more than the launch that goes away.
+// Joined / apart, us a call: bf16, 512 units, 16 scenarios (32 tiles of 16 x 16) 13.1 / 17.3 with 304 columns, 27.9 / 30.4 with 2086;
+// 100 scenarios (224 tiles) 21.8 / 26.5 and 38.2 / 40.8; 160 (320) 25.4 / 27.8 and 45.7 / 41.8; 300 (608) 28.1 / 27.7 and 53 / 43;
+// 1024 units, 388 columns, 64 scenarios (256) 31.6 / 34.7, 160 (640) 37.3 / 35.2; 64 units, 6004 columns, one scenario 21.1 / 20.1.
+// fp32, 64 units, 52 columns, one scenario 11.0 / 17.0, 8000 (500 tiles of 32 x 32) 54.2 / 61.3 with 388; 256 units, 388 columns, 2000
+// scenarios (504) 101.6 / 106.3; 2104 columns, one 18.8 / 25.3, 17 32.1 / 28.8
+bool term_in_first_launch(const ab_model_desc *d, int64_t S)
+{
+    if (d->tensor_encoder || d->n_hidden < 1) return false;
+    const int H = d->hidden[0], Fs = d->n_layers * d->n_stats + d->n_scalars;
+    const int64_t tiles16 = (S + 15) / 16 * (H / 16), tiles32 = (S + 31) / 32 * (H / 32);
+    if (d->compute_dtype == AB_BF16 || S <= 16) return Fs <= 4096 && (tiles16 <= 256 || (tiles16 <= 448 && Fs <= 400));
+    return Fs <= 1024 && tiles32 <= 512;
+}
+
 // Which kernel hidden product k (k >= 1) of a pass takes (for tests): BIG_TILE, BIG_SPAN, or 0 for the smaller tiles.
 int scoring_big_kernel(const ab_model_desc *d, int64_t S, int32_t C, int k)
 {
@@ -317,7 +333,7 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
 
     // 1. scenario rows: transformed statistics (or pooled tensor embedding) + scalars, K-padded
     const double es = (double)elem_size(dt);
-    bool prep_done = false;
+    bool prep_done = false, term_done = false;
     bool grid_done = false;             // a per-scenario grid's rows: in the first launch if all scenarios are one chunk
     if (desc->tensor_encoder == 2) {
         {
@@ -339,6 +355,15 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
         TraceScope ts("encode_stats", (double)S * (desc->n_scalars * 4.0 + (p.Kp - desc->enc_hidden[1]) * es), 1, st);
         AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp,
                                    desc->enc_hidden[1], 0, st));
+    } else if (term_in_first_launch(desc, S)) {
+        // few scenarios: transform, preparation (step 2) and scenario term (step 3) in one launch
+        const double bytes = (double)S * (p.Fs * 4.0 + p.H[0] * 4.0) + (double)p.H[0] * p.F * es + (table ? (double)C * p.H[0] * 4.0 : 0.0);
+        TraceScope ts("encode_and_prep", bytes, 1, st);
+        AB_HIP(launch_scenario_term(dt, desc, stats->dyn, stats->scalars, S, params->W[p.base], params->b[p.base], p.F, p.Fs, p.H[0], p.Kp,
+                                    a_term, grid, b_term, cfg_vec, params->W[p.base + p.D], params->b[p.base + p.D], p.H[p.D - 1],
+                                    w_out_f, per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, st));
+        prep_done = term_done = true;
+        grid_done = p.chunk_scen >= S;
     } else {
         // flat statistics: transform and layer-1 preparation (step 2) share one launch where the layout allows
         const double prep_bytes = (double)p.H[0] * (p.F * es + p.Kp * es) + (table ? (double)C * p.H[0] * 4.0 : 0.0) +
@@ -359,7 +384,9 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                                   p.H[p.D - 1], w_out_f, st));
     }
     // 3. scenario term A[s] = x_s W1_s^T + b1 (fp32 out)
-    {
+    if (term_done) {
+        TraceScope ts("gemm_scenario_term", 0.0, 0, st);     // (in the first launch: every pass reports the same stages)
+    } else {
         GemmArgs g;
         memset(&g, 0, sizeof(g));
         g.A = xs; g.lda = p.Kp; g.B = w1s; g.ldb = p.Kp;

@@ -90,6 +90,11 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
                                   const ab_grid *grid, float *b_term, float *cfg_vec, const void *Wout,
                                   const float *b_out, int H_last, float *w_out_f, float *xp_row, float *xc_row,
                                   bool *done, hipStream_t st);     // xp_row: also the rows of a per-scenario grid
+// Transform, layer-1 preparation and the scenario term's product in one launch, for few scenarios.
+hipError_t launch_scenario_term(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, int64_t S, const void *W1,
+                                const float *b1, int F, int Fs, int H1, int Kp, float *a_term, const ab_grid *grid, float *b_term,
+                                float *cfg_vec, const void *Wout, const float *b_out, int H_last, float *w_out_f, float *xp_row,
+                                float *xc_row, hipStream_t st);
 // Where the chosen candidate's transformed pair goes, and the grid that it comes from.
 struct ChosenArgs { const float *part, *cred; int32_t P, Q, per_scenario; ab_enc enc_part, enc_cred; float *xp_sel, *xc_sel; };
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,

@@ -166,10 +166,9 @@ __device__ __forceinline__ float load_as_f32(const void *p, int64_t i)
 }
 
 template <typename T>
-__device__ __forceinline__ void prep_layer1_block(const PrepArgs &a, unsigned block)
+__device__ __forceinline__ void prep_layer1_item(const PrepArgs &a, int64_t gid)
 {
-    const int64_t gid = (int64_t)block * 256 + threadIdx.x;
-    const int64_t n_pack = (int64_t)a.H1 * a.ld;
+    const int64_t n_pack = a.w1s ? (int64_t)a.H1 * a.ld : 0;
     const int64_t n_bt = a.b_term ? (int64_t)a.P * a.Q * a.H1 : 0;
     if (gid < n_pack) {
         const int h = (int)(gid / a.ld), k = (int)(gid - (int64_t)h * a.ld);
@@ -211,15 +210,14 @@ __device__ __forceinline__ void prep_layer1_block(const PrepArgs &a, unsigned bl
 template <typename T>
 __global__ __launch_bounds__(256) void prep_layer1_kernel(const PrepArgs a)
 {
-    prep_layer1_block<T>(a, blockIdx.x);
+    prep_layer1_item<T>(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 // Per-scenario candidate grids: the transformed pair (phi(S_p), phi(S_c)) of every (scenario, candidate) row
 // of a chunk, row = s * P * Q + p * Q + q, from part[S, P] and cred[S, Q].
 struct GridRowsArgs { const float *part, *cred; int32_t P, Q; ab_enc enc_part, enc_cred; float *xp_row, *xc_row; int64_t rows; };
-__device__ __forceinline__ void grid_rows_block(const GridRowsArgs &a, unsigned block)
+__device__ __forceinline__ void grid_rows_item(const GridRowsArgs &a, int64_t row)
 {
-    const int64_t row = (int64_t)block * 256 + threadIdx.x;
     if (row >= a.rows) return;
     const int Cn = a.P * a.Q;
     const int64_t s = row / Cn;
@@ -227,7 +225,7 @@ __device__ __forceinline__ void grid_rows_block(const GridRowsArgs &a, unsigned 
     a.xp_row[row] = phi(a.part[s * a.P + c / a.Q], a.enc_part);
     a.xc_row[row] = phi(a.cred[s * a.Q + c % a.Q], a.enc_cred);
 }
-__global__ __launch_bounds__(256) void grid_rows_kernel(const GridRowsArgs a) { grid_rows_block(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void grid_rows_kernel(const GridRowsArgs a) { grid_rows_item(a, (int64_t)blockIdx.x * 256 + threadIdx.x); }
 
 // What opens a scoring pass of the flat model is independent of each other (the transform reads the statistics, the
 // preparation the model and the grid, a per-scenario grid's rows the grid), so it shares one launch: the first
@@ -239,8 +237,191 @@ __global__ __launch_bounds__(256) void encode_and_prep_kernel(const EncodeArgs a
                                                               const GridRowsArgs r, unsigned enc_blocks, unsigned grid_from)
 {
     if (blockIdx.x < enc_blocks) encode_stats_quad_block<T>(a, g, blockIdx.x);
-    else if (blockIdx.x < grid_from) prep_layer1_block<T>(p, blockIdx.x - enc_blocks);
-    else grid_rows_block(r, blockIdx.x - grid_from);
+    else if (blockIdx.x < grid_from) prep_layer1_item<T>(p, (int64_t)(blockIdx.x - enc_blocks) * 256 + threadIdx.x);
+    else grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 256 + threadIdx.x);
+}
+
+// The same opening for few scenarios, with the scenario term's product in it: A[s] = W1_s phi(x_s) + b1 straight from the raw
+// statistics and W1 as it lies, so neither the transformed rows nor a packed copy of W1 is written and read again, and a
+// launch goes away.  A work-group makes 16 R scenarios x 16 R units on 16 x 16 instructions; its eight wavefronts share the
+// summed index in steps of 64 bytes of a row of W1, each transforms just the values that its steps need (every column tile anew:
+// cheap while there are few scenarios), the loads of two steps together and the next two under them.  Bound by latency: the
+// arguments, one round trip for statistics and weights, the logarithms, the partial tiles.
+// One scenario of 388 columns, 1024 units, bf16: 5.1 us where the two launches take 3.3 + 3.0 - 4.2 (the call 25.4 -> 23.1 us); on
+// 32 x 32 tiles of 32 x 32 instructions 6.4, with half the work-groups and 32-byte pieces of W1's rows.
+struct TermArgs { const float *b1; float *a_term; uint32_t magic_k; int32_t n_tiles, hw_log; };
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+typedef i32x4 __attribute__((aligned(4))) i32x4_any;
+
+template <typename T, int R>
+__global__ __launch_bounds__(512) void scenario_term_kernel(const EncodeArgs a, const TermArgs q, const PrepArgs p, const GridRowsArgs r,
+                                                            unsigned term_blocks, unsigned grid_from)
+{
+    constexpr int ES = sizeof(T), E = 16 / ES, KS = 4 * E, U = 2, EDGE = 16 * R;
+    __shared__ __attribute__((aligned(16))) float part[8][R * R * 256];
+    __shared__ f32x4 tab[AB_MAX_STATS + AB_MAX_SCALARS];     // statistics first, then the scalars
+    if (blockIdx.x >= grid_from) { grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 512 + threadIdx.x); return; }
+    if (blockIdx.x >= term_blocks) { prep_layer1_item<T>(p, (int64_t)(blockIdx.x - term_blocks) * 512 + threadIdx.x); return; }
+    const int t = threadIdx.x, lane = t & 63, l15 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int tn = (int)(blockIdx.x % (unsigned)q.n_tiles);
+    const int64_t m0 = (int64_t)(blockIdx.x / (unsigned)q.n_tiles) * EDGE;
+    const int n0 = tn * EDGE, Fs = a.n_stat + a.n_scal;
+    const float *dyn[R], *scal[R];
+    const T *w_row[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int64_t row = min(m0 + 16 * i + l15, a.S - 1);
+        dyn[i] = a.dyn + row * a.n_stat;
+        scal[i] = a.scal + row * a.n_scal;
+        w_row[i] = (const T *)p.W1 + (int64_t)(n0 + 16 * i + l15) * p.F;
+    }
+
+    // A step: columns step * KS + g * E .. + E - 1 of this lane's scenarios and units.  The first `full` steps hold statistics only;
+    // the few behind them (the last statistics, the scalars) go to one wavefront each and are taken value by value.
+    auto pack = [](const float (&v)[E]) {
+        if constexpr (ES == 2) return i32x4{(int)pack_bf16x2(v[0], v[1]), (int)pack_bf16x2(v[2], v[3]), (int)pack_bf16x2(v[4], v[5]), (int)pack_bf16x2(v[6], v[7])};
+        else return __builtin_bit_cast(i32x4, f32x4{v[0], v[1], v[2], v[3]});
+    };
+    const int full = a.n_stat / KS, tail = full + 7 - wave, jt = tail * KS + g * E;
+    const bool has_tail = tail * KS < Fs;
+    // Rows of an odd number of bf16 columns: every other one begins in the middle of a word; the words around are taken and shifted.
+    const bool odd = ES == 2 && (p.F & 1);
+    float x[2][U][R][E];
+    i32x4 w[2][U][R];
+    int w5[2][U][R];
+    auto request = [&](int set, int s0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(s0 + 8 * u, full - 1) * KS + g * E;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const unsigned char *word = (const unsigned char *)((uintptr_t)(w_row[i] + j) & ~(uintptr_t)3);
+                w[set][u][i] = *(const i32x4_any *)word;
+                if (odd) w5[set][u][i] = *(const int *)(word + 16);
+#pragma unroll
+                for (int h = 0; h < E / 4; ++h) {
+                    const f32x4 v = *(const f32x4_any *)(dyn[i] + j + 4 * h);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[set][u][i][4 * h + e] = v[e];
+                }
+            }
+        }
+    };
+    if (wave < full) request(0, wave);
+    float xt[R][E], wt[R][E];
+    if (has_tail) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int c = min(jt + e, Fs - 1);
+                xt[i][e] = *(c < a.n_stat ? dyn[i] + c : scal[i] + (c - a.n_stat));
+                wt[i][e] = load_as_f32<T>(w_row[i], c);
+            }
+    }
+    if (t < AB_MAX_STATS + AB_MAX_SCALARS) {
+        const ab_enc *e = t < AB_MAX_STATS ? &a.enc_stat[t] : &a.enc_scal[t - AB_MAX_STATS];
+        tab[t] = f32x4{e->kind == AB_ENC_LOG ? 1.f : 0.f, e->shift, e->scale, 0.f};
+    }
+    __syncthreads();
+    f32x4 acc[R][R];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const i32x4 (&fx)[R], const i32x4 (&fw)[R]) {                 // scenarios first: they end up in the registers
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if constexpr (ES == 2) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fx[i]), __builtin_bit_cast(bf16x8, fw[j]), acc[i][j], 0, 0, 0);
+                } else {
+                    const f32x4 u = __builtin_bit_cast(f32x4, fx[i]), v = __builtin_bit_cast(f32x4, fw[j]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[e], v[e], acc[i][j], 0, 0, 0);
+                }
+            }
+    };
+    auto run = [&](auto log_tag) {
+        auto phi_of = [&](float v, const f32x4 &c) {
+            float lg;
+            if constexpr (decltype(log_tag)::value) lg = __builtin_amdgcn_logf(v) * 0.69314718056f;
+            else lg = logf(v);
+            return ((c.x != 0.f ? lg : v) - c.y) * c.z;
+        };
+        auto take = [&](int set, int s0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (s0 + 8 * u >= full) break;
+                const int j = (s0 + 8 * u) * KS + g * E;
+                int k = q.magic_k ? j - (int)__umulhi((uint32_t)j, q.magic_k) * a.n_stats_per_layer : 0;     // j mod the statistics of a layer
+                float v[R][E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const f32x4 c = tab[k];
+#pragma unroll
+                    for (int i = 0; i < R; ++i) v[i][e] = phi_of(x[set][u][i][e], c);
+                    k = k + 1 == a.n_stats_per_layer ? 0 : k + 1;
+                }
+                i32x4 fx[R], fw[R];
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    fx[i] = pack(v[i]);
+                    fw[i] = w[set][u][i];
+                    if (odd && ((uintptr_t)w_row[i] & 2)) {
+                        const uint32_t word[5] = {(uint32_t)fw[i].x, (uint32_t)fw[i].y, (uint32_t)fw[i].z, (uint32_t)fw[i].w, (uint32_t)w5[set][u][i]};
+#pragma unroll
+                        for (int h = 0; h < 4; ++h) fw[i][h] = (int)(word[h] >> 16 | word[h + 1] << 16);
+                    }
+                }
+                mma(fx, fw);
+            }
+        };
+        for (int s0 = wave; s0 < full; s0 += 16 * U) {
+            if (s0 + 8 * U < full) request(1, s0 + 8 * U);
+            take(0, s0);
+            if (s0 + 16 * U < full) request(0, s0 + 16 * U);
+            take(1, s0 + 8 * U);
+        }
+        if (has_tail) {
+            i32x4 fx[R], fw[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                float v[E], wv[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const int c = min(jt + e, Fs - 1);
+                    const int k = c < a.n_stat ? (q.magic_k ? c - (int)__umulhi((uint32_t)c, q.magic_k) * a.n_stats_per_layer : 0)
+                                               : AB_MAX_STATS + c - a.n_stat;
+                    v[e] = jt + e < Fs ? phi_of(xt[i][e], tab[k]) : 0.f;
+                    wv[e] = jt + e < Fs ? wt[i][e] : 0.f;
+                }
+                fx[i] = pack(v);
+                fw[i] = pack(wv);
+            }
+            mma(fx, fw);
+        }
+    };
+    if (ES == 2 && q.hw_log) run(std::true_type{});
+    else                     run(std::false_type{});
+    // the eight partial tiles
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[wave][(16 * i + 4 * g + e) * EDGE + 16 * j + l15] = acc[i][j][e];
+    __syncthreads();
+    for (int e = t; e < EDGE * EDGE; e += 512) {
+        const int64_t row = m0 + e / EDGE;
+        const int col = n0 + e % EDGE;
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v += part[k][e];
+        if (row < a.S) q.a_term[row * p.H1 + col] = v + q.b1[col];
+    }
 }
 
 hipError_t launch_grid_rows(const ab_model_desc *d, const float *part, const float *cred, int P, int Q,
@@ -1168,6 +1349,31 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
     return hipGetLastError();
 }
 
+hipError_t launch_scenario_term(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, int64_t S, const void *W1,
+                                const float *b1, int F, int Fs, int H1, int Kp, float *a_term, const ab_grid *grid, float *b_term,
+                                float *cfg_vec, const void *Wout, const float *b_out, int H_last, float *w_out_f, float *xp_row,
+                                float *xc_row, hipStream_t st)
+{
+    if (S == 0) return hipSuccess;
+    EncodeArgs a;
+    fill_encode_args(a, d, dyn, scal, nullptr, S, Kp, 0, 1);
+    QuadSplit g;
+    PrepArgs p;
+    const int64_t n = fill_prep_args(p, d, W1, b1, F, Fs, H1, Kp, nullptr, grid, b_term, cfg_vec, Wout, b_out, H_last, w_out_f);
+    const int edge = S <= 16 || dtype == AB_BF16 ? 16 : 32;
+    const TermArgs q{b1, a_term, d->n_stats >= 2 ? (uint32_t)(0x100000000ull / (uint32_t)d->n_stats) + 1u : 0u, H1 / edge,
+                     quad_split(dtype, d, a, g)};            // (the transform's two forms take the logarithm differently in bf16)
+    const GridRowsArgs r{grid->partition_bytes, grid->credit_mult, grid->P, grid->Q, d->enc_partition, d->enc_credit, xp_row, xc_row,
+                         xp_row ? S * grid->P * grid->Q : 0};
+    const int64_t term_blocks = (S + edge - 1) / edge * q.n_tiles, grid_from = term_blocks + (n + 511) / 512, blocks = grid_from + (r.rows + 511) / 512;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    auto launch = [&](auto kern) { kern<<<(unsigned)blocks, 512, 0, st>>>(a, q, p, r, (unsigned)term_blocks, (unsigned)grid_from); };
+    if (dtype == AB_BF16) launch(scenario_term_kernel<bf16_t, 1>);
+    else if (edge == 16)  launch(scenario_term_kernel<float, 1>);
+    else                  launch(scenario_term_kernel<float, 2>);
+    return hipGetLastError();
+}
+
 static int64_t fill_prep_args(PrepArgs &a, const ab_model_desc *d, const void *W1, const float *b1, int F, int Fs,
                               int H1, int ld, void *w1s, const ab_grid *grid, float *b_term, float *cfg_vec,
                               const void *Wout, const float *b_out, int H_last, float *w_out_f)
@@ -1178,7 +1384,7 @@ static int64_t fill_prep_args(PrepArgs &a, const ab_model_desc *d, const void *W
     const int Cn = grid->P * grid->Q;
     a.wp_f = cfg_vec; a.wc_f = cfg_vec + H1; a.xp_f = cfg_vec + 2 * H1; a.xc_f = cfg_vec + 2 * H1 + Cn;
     a.Wout = Wout; a.b_out = b_out; a.H_last = H_last; a.n_out = d->n_outputs > 1 ? d->n_outputs : 1; a.w_out_f = w_out_f;
-    return (int64_t)H1 * ld + (b_term ? (int64_t)Cn * H1 : 0) + H_last + H1 + Cn;
+    return (w1s ? (int64_t)H1 * ld : 0) + (b_term ? (int64_t)Cn * H1 : 0) + H_last + H1 + Cn;
 }
 
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,

@@ -1,0 +1,45 @@
+"""Transform and scenario term in one launch (csrc/scoring_kernels.hip, scenario_term_kernel): scenarios around a tile of 16 or 32,
+statistics shorter than one step of the summed index, ending with one and inside one, more steps than a wavefront holds at once,
+rows of W1 that begin in the middle of a word (odd column counts in bf16), one and sixteen statistics a layer, grids per
+scenario (their rows come from the same launch); each against the fp64 oracle.  The last sizes are beyond its line."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2112_13509_amd import binding as ab
+from paper_2112_13509_amd import workloads as wl
+from gpu_helpers import Scorer
+from helpers import oracle_model, tensor_scaled_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("S,L,workers,hidden,own_grids,joined", [
+    (1, 2, 0, [192, 64], False, True),                # 6 statistics, 4 scalars: one step, none of it whole
+    (16, 8, 0, [64, 128], False, True), (17, 32, 0, [320, 64], True, True), (3, 101, 0, [256, 192], True, True),
+    (33, 64, 0, [128], False, True), (2, 339, 0, [64, 64], False, True), (40, 41, 3, [256, 128], False, True),
+    (5, 60, 16, [192, 320], True, True), (31, 1, 5, [64, 64, 64], False, True), (16, 256, 0, [1024, 64], False, True),
+    (100, 8, 0, [512, 64], False, True), (1100, 20, 0, [1024, 64], False, False), (2, 2000, 0, [64, 64], False, False),
+])
+def test_scenario_term(dtype, S, L, workers, hidden, own_grids, joined):
+    if workers:
+        w = wl.make_per_worker("term", S, L, workers, hidden, 3, 11, dtype, 13000 + S)
+    else:
+        w = wl.make_scoring("term", S, L, hidden, 3, 11, 16 * wl.KIB, 64 * wl.MIB, 1.0, 64.0, False, dtype, 13000 + S)
+    f = ab.load()._ZN2ab20term_in_first_launchEPK13ab_model_descl
+    f.restype, f.argtypes = C.c_bool, (C.c_void_p, C.c_int64)
+    assert f(C.byref(ab.desc_from_workload(w)), S) == joined
+    part = cred = None
+    if own_grids:
+        rng = np.random.default_rng(S)
+        part = (w.part[None] * np.exp2(rng.uniform(-1, 1, (S, 1)))).astype(np.float32)
+        cred = (w.cred[None] * rng.uniform(1, 1.25, (S, 1))).astype(np.float32)
+    scores, idx, best = Scorer(w).run(part=part, cred=cred)
+    m = oracle_model(w)
+    m.round_stored_bf16 = dtype == "bf16"                    # (as in test_gpu_slim_shapes)
+    ref = orc.score(m, w.dyn, w.scal, w.part if part is None else part, w.cred if cred is None else cred)
+    assert tensor_scaled_error(scores, ref) <= (1e-4 if dtype == "f32" else 2e-3 if len(hidden) <= 2 else 1e-2)
+    assert np.array_equal(idx, np.argmax(scores, axis=1)) and np.array_equal(best, scores[np.arange(S), idx])
