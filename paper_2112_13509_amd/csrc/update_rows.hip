@@ -467,9 +467,12 @@ static bool rows_layout(RowsArgs &a, int es, int r16, int *bytes)
         RowsJob &j = a.job[a.n_jobs++];
         fill(j, k, false);
         masks += j.passes * 2048;
-        if (j.ks_shift && j.n_slices * ((1 << j.ks_shift) - 1) > part) part = j.n_slices * ((1 << j.ks_shift) - 1);
     }
-    for (int k = a.D - 1; k > a.k0; --k) fill(a.job[a.n_jobs++], k, true);     // (widths of forward layers: no more scratch)
+    for (int k = a.D - 1; k > a.k0; --k) fill(a.job[a.n_jobs++], k, true);
+    for (int i = 0; i < a.n_jobs; ++i) {                    // sums that meet in LDS: a product's wavefronts beyond the first of a slice
+        const int n = a.job[i].n_slices * ((1 << a.job[i].ks_shift) - 1);
+        if (n > part) part = n;
+    }
     int o = 8 * NU * UNIT;
     auto take = [&](int n) { const int at = o; o += (n + 255) / 256 * 256; return at; };      // (tables arrive in pieces of 256 bytes)
     a.o_even = take(16 * r16 * even);
