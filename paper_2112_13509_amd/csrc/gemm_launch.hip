@@ -6,6 +6,10 @@ namespace ab {
 template <typename T, int WB, int AMODE, int EPI>
 static hipError_t launch_one(const GemmArgs &g, hipStream_t st)
 {
+    // (fp32 hidden products that are large enough for these tiles go to gemm_split.hip; what is left for them: the scenario term of
+    // many scenarios and, on 128 x 128 tiles, the second pass of wide networks)
+    if constexpr (sizeof(T) == 4 && WB > 1 && (EPI == EPI_SCORE || AMODE == AMODE_GEN || (AMODE == AMODE_GENV && WB > 2))) return hipErrorInvalidValue;
+    else {
     constexpr int BM = 64 * WB, BN = 64 * WB;
     constexpr int smem = 2 * (BM + BN) * 128;
     auto kern = gemm_tn_kernel<T, WB, WB, AMODE, EPI>;
@@ -21,6 +25,7 @@ static hipError_t launch_one(const GemmArgs &g, hipStream_t st)
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     kern<<<(unsigned)blocks, 256, smem, st>>>(g);
     return hipGetLastError();
+    }
 }
 
 template <typename T, int WB>
