@@ -1,6 +1,6 @@
 // The online update in row-block form: forward pass, output unit, loss terms and the delta chain of a block of 16 or 32
-// batch rows in one work-group, then all weight gradients in one launch (update.hip decides when, and ends the step with
-// the Adam launch).
+// batch rows in one work-group, then all weight gradients in one launch, with the Adam step in it (update_step_kernel) or in a
+// launch of update.hip behind it (update.hip decides when).
 //
 // Why this form: a chain of GEMM launches pays about 5 us a launch before its first product (dispatch, arguments, first
 // misses: what a launch reads was written by other XCDs and comes from the Infinity Cache) and the chain has one launch
