@@ -1580,19 +1580,21 @@ hipError_t launch_score_single_hidden(const float *a_term, const float *b_term, 
 // (K -> 32), two stacked LSTM layers of 64 units over t = 0..L-1 with zero initial state, gate blocks in
 // the order input, forget, candidate, output; the second layer's last hidden state becomes the first 64
 // columns of the scenario row.
-// One work-group of eight wavefronts per 32 scenarios, the whole sequence in one launch; four wavefronts run
-// the first layer, four the second one step behind (two wavefronts per SIMD hide each other's latencies):
-//   - a wavefront owns 16 units of its layer and keeps their rows of [W_ih | W_hh] (bf16) in registers
-//     as matrix-instruction operands, permuted so that the four gates of a unit land in one lane:
-//     column 8g + 4h + j of output block b is gate g of unit 16w + 8b + 4h + j;  the bias is the
-//     addend of the first matrix instruction;
-//   - the recurrent operands live in LDS as rows [e | h1 | h2] (bf16), double-buffered by iteration parity:
-//     in iteration t layer 1 makes h1_t from (e_t, h1_{t-1}) and layer 2 makes h2_{t-1} from (h1_{t-1},
-//     h2_{t-2}), all read from buffer t&1 and written to the other one: one barrier per iteration;
+// One work-group of eight wavefronts per 2 G scenarios, the whole sequence in one launch; four wavefronts run
+// the first layer, four the second one step behind:
+//   - a wavefront owns 16 units of its layer and keeps their rows of [W_ih | W_hh] (bf16) in registers as first operands of
+//     16 x 16 blocks, permuted so that the four gates of a unit land in one lane: row 4 u + g of block b is gate g of
+//     unit 16 w + 4 u + b;  the bias is the addend of the first matrix instruction;
+//   - the scenarios are two groups, half a step apart: while the gates of one group's step go through the vector ALUs,
+//     the products of the other group's are on the matrix cores, then they change places (a step in one piece has all
+//     wavefronts at the matrix cores first and at the vector ALUs afterwards);
+//   - the recurrent operands live in LDS as rows [e | h1 | h2] (bf16), read in one half step and written in the next, a barrier
+//     between: in iteration t layer 1 makes h1_t from (e_t, h1_{t-1}) and layer 2 makes h2_{t-1} from (h1_{t-1}, h2_{t-2});
 //   - cell states stay in fp32 registers; sigmoid and tanh through exp2 and reciprocal;
-//   - the statistics come in chunks of 16 steps (transformed once, one chunk ahead in registers).
-// The step is bound by the transcendental rate of the vector ALUs (10 per unit and step), not by the
-// matrix cores.
+//   - the statistics come in chunks of 16 steps, one chunk ahead; their loads are in flight over fourteen steps (a barrier
+//     waits for LDS traffic only) and are transformed then.
+// Columns of a block are scenarios; with G < 16 they repeat the group, and column c takes its cells from blocks
+// (c / G) G / 4 ... alone: G / 4 cells a lane and group.
 // ------------------------------------------------------------------------------------------------
 struct LstmEncArgs {
     const float *dyn; int32_t L, K; int64_t S;
@@ -1613,196 +1615,260 @@ __device__ __forceinline__ float fast_tanh(float x)
     return 1.f - 2.f * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(2.88539008177793f * x));
 }
 
-__global__ __launch_bounds__(512) void lstm_encoder_kernel(const LstmEncArgs a)
+template <int G, int NG, int KQ>                           // NG groups of G scenarios, K <= 4 KQ
+struct LstmLds {
+    static constexpr int STRIDE = 336, TC = 16;    // bytes per row: (32 + 64 + 64) bf16 + 16 (bank spread); steps of a chunk
+    alignas(16) unsigned char act[2 * G * STRIDE];   // rows of the two groups (of one group: by the step's parity)
+    alignas(16) float stat[2][NG * G][TC][4 * KQ];   // (zero beyond K)
+};
+template <int G, int NG, int KQ, int ROLE>                 // ROLE 0: the first LSTM layer's wavefronts, 1: the second's
+__device__ __forceinline__ void lstm_layer(const LstmEncArgs &a, LstmLds<G, NG, KQ> &lds)
 {
-    constexpr int E = 32, H = 64, R = 32, TC = 16;
-    constexpr int STRIDE = 336;                    // bytes per row: (32 + 64 + 64) bf16 + 16 (bank spread)
-    constexpr int COL_H1 = E, COL_H2 = E + H;
-    __shared__ __attribute__((aligned(16))) unsigned char act[2][R * STRIDE];
-    __shared__ __attribute__((aligned(16))) float stat[2][R][TC][AB_MAX_ENCODER_STATS];
+    constexpr int E = 32, H = 64, TC = 16, R = NG * G, NC = G / 4, KM = 4 * KQ;
+    constexpr int STRIDE = LstmLds<G, NG, KQ>::STRIDE, COL_H1 = E, COL_H2 = E + H;
+    auto &act = lds.act;
+    auto &stat = lds.stat;
 
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int role = wave >> 2, wu = wave & 3;     // role 0: first LSTM layer, 1: second; wu: which 16 units
-    // Of the two wavefronts of a SIMD the one of the second layer has more to do per step (eight k steps against six,
-    // and the next step's embedding) and, being the younger one, would be served last: it gets the higher priority.
-    if (role) __builtin_amdgcn_s_setprio(2);
-    const int l31 = lane & 31, hf = lane >> 5;
+    const int wu = wave & 3;                       // which 16 units
+    const int col = lane & 15, u = lane >> 4, scen = col % G, b0 = col / G * NC;
     const int64_t s0 = (int64_t)blockIdx.x * R;
     const int L = a.L, K = a.K;
 
-    // ---- this wavefront's weights as first operands: lane -> row (l31 = output column) and 8 k values (hf);
-    // layer 1 has 6 k steps (32 + 64 inputs), layer 2 has 8 (64 + 64)
-    i32x4 wf[2][8];
-    f32x16 bias[2];
-    {
-        const int g = l31 >> 3, hp = (l31 >> 2) & 1, j = l31 & 3;
-        const uint16_t *W = (const uint16_t *)(role ? a.W2 : a.W1);
-        const float *bsrc = role ? a.b2 : a.b1;
-        const int kin = role ? 2 * H : E + H;
+    // ---- statistics chunks: R rows x TC steps x K values; TPS threads to a row's step, KP values each
+    constexpr int TPS = 32 / R, KP = KM > TPS ? KM / TPS : 1;
+    const int prow = t / (TPS * TC), pstep = t / TPS % TC, k0 = t % TPS * KP;
+    float pre[KP];
+    ab_enc enc[KP];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int wrow = g * H + 16 * wu + 8 * b + 4 * hp + j;
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) {
-                wf[b][ks] = i32x4{0, 0, 0, 0};
-                if (ks * 16 < kin) wf[b][ks] = *(const i32x4 *)(W + (size_t)wrow * kin + ks * 16 + 8 * hf);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r)          // register r of the result: gate r / 4, unit offset r & 3 (+ 4 hf)
-                bias[b][r] = bsrc[(r >> 2) * H + 16 * wu + 8 * b + 4 * hf + (r & 3)];
-        }
-    }
-    // ---- embedding (the second layer's wavefronts do it): thread -> row te >> 3, outputs 4 (te & 7) .. + 3
-    // (W_e and b_e sit in LDS: 33 values per output would crowd the registers that hold the gate weights)
-    __shared__ __attribute__((aligned(16))) float we_s[E][AB_MAX_ENCODER_STATS];
-    __shared__ float be_s[E];
-    const int te = t & 255, erow = te >> 3, ej = (te & 7) * 4;
-    if (t < E * AB_MAX_ENCODER_STATS) {
-        const int o = t / AB_MAX_ENCODER_STATS, k = t % AB_MAX_ENCODER_STATS;
-        we_s[o][k] = k < K ? bf16_bits_to_f32(((const uint16_t *)a.We)[o * K + k]) : 0.f;
-    }
-    if (t < E) be_s[t] = a.be[t];
-    // ---- statistics chunks: 32 rows x TC steps x K values, element idx = t + 512 i
-    constexpr int PRE = R * TC * AB_MAX_ENCODER_STATS / 512;     // 8 registers at K = 8
-    float pre[PRE];
-    const int per_row = TC * K;
+    for (int i = 0; i < KP; ++i) enc[i] = a.enc_stat[k0 + i];
+    const float *src = a.dyn + min(s0 + prow, a.S - 1) * (int64_t)L * K;
+    float *mine = &stat[0][prow][pstep][k0];
     auto fetch_chunk = [&](int n) {
+        const float *q = src + (int64_t)min(n * TC + pstep, L - 1) * K;
 #pragma unroll
-        for (int i = 0; i < PRE; ++i) {
-            const int idx = t + 512 * i;
-            pre[i] = 0.f;
-            if (idx < R * per_row) {
-                const int row = idx / per_row, o = idx - row * per_row;
-                int step = n * TC + o / K;
-                if (step > L - 1) step = L - 1;
-                int64_t sc = s0 + row;
-                if (sc > a.S - 1) sc = a.S - 1;
-                const int k = o % K;
-                pre[i] = phi(a.dyn[(sc * L + step) * K + k], a.enc_stat[k]);
-            }
-        }
+        for (int i = 0; i < KP; ++i) pre[i] = q[min(k0 + i, K - 1)];
+        asm volatile("");                                // (keeps the compiler from merging this with put_chunk's stores: pre stays in registers)
     };
     auto put_chunk = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < PRE; ++i) {
-            const int idx = t + 512 * i;
-            if (idx < R * per_row) {
-                const int row = idx / per_row, o = idx - row * per_row;
-                stat[buf][row][o / K][o % K] = pre[i];
+        for (int i = 0; i < KP; ++i)
+            if (k0 < KM) {
+                const float l = logf(pre[i]), v = ((enc[i].kind == AB_ENC_LOG ? l : pre[i]) - enc[i].shift) * enc[i].scale;      // phi, branch-free
+                mine[buf * (R * TC * KM) + i] = k0 + i < K ? v : 0.f;
             }
-        }
     };
-    auto embed_step = [&](int step, int buf) {           // e_step -> act[buf], columns [0, 32)
-        const float *sp = &stat[(step / TC) & 1][erow][step % TC][0];
-        float e[4] = {be_s[ej], be_s[ej + 1], be_s[ej + 2], be_s[ej + 3]};
+    // ---- embedding of a group's rows by the second layer's wavefronts: thread -> row, EO outputs (with G = 4 twice over)
+    constexpr int EO = G == 16 ? 2 : 1;
+    const int te = t & 255, erow = te / (E / EO) % G, ej = te % (E / EO) * EO;
+    f32x4 we[EO][KQ];
+    float be[EO];
 #pragma unroll
-        for (int k = 0; k < AB_MAX_ENCODER_STATS; ++k)
-            if (k < K) {
-                const float x = sp[k];
+    for (int i = 0; i < EO; ++i) {
+        be[i] = a.be[ej + i];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) e[i] = fmaf(we_s[ej + i][k], x, e[i]);
-            }
-        uint2 pk = {pack_bf16x2(e[0], e[1]), pack_bf16x2(e[2], e[3])};
-        *(uint2 *)(&act[buf][erow * STRIDE + ej * 2]) = pk;
+        for (int k = 0; k < KM; ++k) we[i][k / 4][k % 4] = k < K ? bf16_bits_to_f32(((const uint16_t *)a.We)[(ej + i) * K + k]) : 0.f;
+    }
+    auto embed_step = [&](int step, int grp, int rows) { // e_step of a group -> columns [0, 32) of rows `rows` G ..
+        const float *sp = &stat[(step / TC) & 1][grp * G + erow][step % TC][0];
+        float e[EO];
+#pragma unroll
+        for (int i = 0; i < EO; ++i) e[i] = be[i];
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+            const f32x4 x = *(const f32x4 *)(sp + 4 * q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < EO; ++i) e[i] = fmaf(we[i][q][k], x[k], e[i]);
+        }
+        const uint32_t pk = pack_bf16x2(e[0], e[EO - 1]);
+        unsigned char *dst = act + (rows * G + erow) * STRIDE + ej * 2;
+        if constexpr (EO == 2) *(uint32_t *)dst = pk;
+        else                   *(uint16_t *)dst = (uint16_t)(pk & 0xffffu);
+    };
+    auto meet = [&]() {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     };
 
     // ---- start: zero state, first chunk, e_0
-    for (int i = t; i < 2 * R * STRIDE / 4; i += 512) ((uint32_t *)&act[0][0])[i] = 0u;
+    for (int i = t; i < 2 * G * STRIDE / 4; i += 512) ((uint32_t *)act)[i] = 0u;
     fetch_chunk(0);
     put_chunk(0);
     __syncthreads();
-    if (role == 1) embed_step(0, 0);
-
-    float c[2][4], hv[2][4], hlast[2][4];
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c[b][j] = hv[b][j] = hlast[b][j] = 0.f;
-    // this lane's scenario (row l31) may have fewer layers than the block runs for: its result is the second
-    // layer's hidden state after its own last layer; what the recurrence does to that row afterwards is unused
-    int my_len = L;
-    if (a.layers_of) {
-        int64_t sc = s0 + l31;
-        if (sc > a.S - 1) sc = a.S - 1;
-        my_len = a.layers_of[sc];
-        my_len = my_len < 1 ? 1 : (my_len > L ? L : my_len);
+    if (ROLE) {
+        embed_step(0, 0, 0);
+        if constexpr (NG == 2) embed_step(0, 1, 1);
     }
+    meet();
 
-    const int frag_rd = l31 * STRIDE + 16 * hf;          // + column * 2
-    const int h_wr = l31 * STRIDE + (16 * wu + 4 * hf) * 2;     // + (field column + 8 b) * 2
-    auto cell = [&](const f32x16 &z, float (&cs)[4], float (&h)[4]) {
+    constexpr int NK = ROLE ? 4 : 3;
+    constexpr int COL = ROLE ? COL_H1 : 0, OUT = ROLE ? COL_H2 : COL_H1, KIN = ROLE ? 2 * H : E + H;
+    // this wavefront's weights: lane -> row (col) of a block and eight k values (u)
+    bf16x8 wf[4][NK];
+    f32x4 bias[4];
+    const uint16_t *W = (const uint16_t *)(ROLE ? a.W2 : a.W1);
+    const float *bsrc = ROLE ? a.b2 : a.b1;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float ig = fast_sigmoid(z[j]), fg = fast_sigmoid(z[4 + j]);
-            const float gg = fast_tanh(z[8 + j]), og = fast_sigmoid(z[12 + j]);
-            cs[j] = fmaf(fg, cs[j], ig * gg);
-            h[j] = og * fast_tanh(cs[j]);
+    for (int b = 0; b < 4; ++b) {
+        const int wrow = (col & 3) * H + 16 * wu + 4 * (col >> 2) + b;
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) wf[b][ks] = __builtin_bit_cast(bf16x8, *(const i32x4 *)(W + (size_t)wrow * KIN + ks * 32 + 8 * u));
+#pragma unroll
+        for (int g = 0; g < 4; ++g) bias[b][g] = bsrc[g * H + 16 * wu + 4 * u + b];
+    }
+    // the scenario of a lane may have fewer layers than the block runs for: its result is the second layer's hidden state
+    // after its own last layer; what the recurrence does to that row afterwards is unused
+    int my_len[NG];
+#pragma unroll
+    for (int x = 0; x < NG; ++x) my_len[x] = L;
+    if (ROLE && a.layers_of) {
+#pragma unroll
+        for (int x = 0; x < NG; ++x) {
+            const int n = a.layers_of[min(s0 + x * G + scen, a.S - 1)];
+            my_len[x] = n < 1 ? 1 : (n > L ? L : n);
+        }
+    }
+    float c[NG][NC], hv[NC], hlast[NG][NC];
+#pragma unroll
+    for (int x = 0; x < NG; ++x)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) c[x][i] = hlast[x][i] = 0.f;
+    f32x4 z[NG][4];
+    const unsigned char *frag = act + scen * STRIDE + 16 * u + COL * 2;
+    unsigned char *h_wr = act + scen * STRIDE + (16 * wu + 4 * u + b0 + OUT) * 2;
+
+    auto products = [&](int x, int rows) {
+        bf16x8 xf[NK];
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) xf[ks] = __builtin_bit_cast(bf16x8, *(const i32x4 *)(frag + rows * G * STRIDE + ks * 64));
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                z[x][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[b][ks], xf[ks], ks == 0 ? bias[b] : z[x][b], 0, 0, 0);
+    };
+    auto cells = [&](int x) {
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            f32x4 y = z[x][i];
+            if constexpr (G == 8) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) y[g] = b0 ? z[x][2 + i][g] : z[x][i][g];
+            }
+            if constexpr (G == 4) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float lo = b0 & 1 ? z[x][1][g] : z[x][0][g], hi = b0 & 1 ? z[x][3][g] : z[x][2][g];
+                    y[g] = b0 & 2 ? hi : lo;
+                }
+            }
+            const float ig = fast_sigmoid(y[0]), fg = fast_sigmoid(y[1]), gg = fast_tanh(y[2]), og = fast_sigmoid(y[3]);
+            c[x][i] = fmaf(fg, c[x][i], ig * gg);
+            hv[i] = og * fast_tanh(c[x][i]);
         }
     };
-
-    // Iteration tau: the first layer makes h1_tau from (e_tau, h1_{tau-1}) while the second layer makes
-    // h2_{tau-1} from (h1_{tau-1}, h2_{tau-2}); all of these sit in buffer tau & 1 and every result (with
-    // e_{tau+1}) goes to the other buffer, so one barrier per iteration orders everything.
-    for (int tau = 0; tau <= L; ++tau) {
-        const int p = tau & 1;
-        __syncthreads();
+    auto put = [&](int rows) {
+        unsigned char *dst = h_wr + rows * G * STRIDE;
+        if constexpr (NC == 4)      *(uint2 *)dst = uint2{pack_bf16x2(hv[0], hv[1]), pack_bf16x2(hv[2], hv[3])};
+        else if constexpr (NC == 2) *(uint32_t *)dst = pack_bf16x2(hv[0], hv[1]);
+        else                        *(uint16_t *)dst = (uint16_t)(pack_bf16x2(hv[0], 0.f) & 0xffffu);
+    };
+    // Half a step: the gates of group X's step tau, the products of the other group's next ones.  (One group: all of a step.)
+    // Past its last step a layer makes rows that nobody reads.
+    auto half_step = [&](auto x_tag, int tau) {
+        constexpr int X = decltype(x_tag)::value;
+        const int from = NG == 2 ? X ^ 1 : tau & 1, to = NG == 2 ? X : from ^ 1;
+        if constexpr (ROLE) embed_step(min(tau + 1, L - 1), X, to);
+        products(NG == 2 ? X ^ 1 : 0, from);
+        cells(X);
+        put(to);
+        if constexpr (ROLE) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) hlast[X][i] = tau == my_len[X] ? hv[i] : hlast[X][i];
+        }
+        if constexpr (NG == 2) {                     // one matrix instruction, then some of the gates' work
+            __builtin_amdgcn_sched_group_barrier(0x100, NK + (ROLE ? KQ : 0), 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, G, 0);
+#pragma unroll
+            for (int i = 0; i < 4 * NK; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
+            }
+        }
+        meet();
+    };
+    auto chunks = [&](int tau) {
         const int tc = tau % TC, n = tau / TC;
         if (tc == 0 && (n + 1) * TC < L) fetch_chunk(n + 1);
         if (tc == TC - 2 && (n + 1) * TC < L) put_chunk((n + 1) & 1);
-        f32x16 z[2];
-        if (role == 0) {
-            if (tau < L) {
+    };
+    int tau = 0;
+    if constexpr (NG == 2) {
+        products(0, 0);
+        meet();
+    }
+    if constexpr (ROLE) {                            // (the second layer has no step yet)
+        chunks(0);
+        embed_step(min(1, L - 1), 0, NG == 2 ? 0 : 1);
+        if constexpr (NG == 2) {
+            products(1, 1);
+            meet();
+            embed_step(min(1, L - 1), 1, 1);
+            products(0, 0);
+        }
+        meet();
+        tau = 1;
+    }
+    for (; tau <= L; ++tau) {
+        chunks(tau);
+        half_step(std::integral_constant<int, 0>{}, tau);
+        if constexpr (NG == 2) half_step(std::integral_constant<int, 1>{}, tau);
+    }
+    // ---- second layer's hidden state after the scenario's last layer
+    if constexpr (ROLE) {
 #pragma unroll
-                for (int ks = 0; ks < 6; ++ks) {
-                    const i32x4 xf = *(const i32x4 *)(&act[p][frag_rd + ks * 32]);
-#pragma unroll
-                    for (int b = 0; b < 2; ++b)
-                        z[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[b][ks]),
-                                                                       __builtin_bit_cast(bf16x8, xf),
-                                                                       ks == 0 ? bias[b] : z[b], 0, 0, 0);
-                }
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    cell(z[b], c[b], hv[b]);
-                    uint2 pk = {pack_bf16x2(hv[b][0], hv[b][1]), pack_bf16x2(hv[b][2], hv[b][3])};
-                    *(uint2 *)(&act[p ^ 1][h_wr + (COL_H1 + 8 * b) * 2]) = pk;
-                }
-            }
-        } else {
-            if (tau + 1 < L) embed_step(tau + 1, p ^ 1);
-            if (tau >= 1) {
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) {
-                    const i32x4 xf = *(const i32x4 *)(&act[p][frag_rd + (COL_H1 + ks * 16) * 2]);
-#pragma unroll
-                    for (int b = 0; b < 2; ++b)
-                        z[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[b][ks]),
-                                                                       __builtin_bit_cast(bf16x8, xf),
-                                                                       ks == 0 ? bias[b] : z[b], 0, 0, 0);
-                }
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    cell(z[b], c[b], hv[b]);
-                    uint2 pk = {pack_bf16x2(hv[b][0], hv[b][1]), pack_bf16x2(hv[b][2], hv[b][3])};
-                    *(uint2 *)(&act[p ^ 1][h_wr + (COL_H2 + 8 * b) * 2]) = pk;
-                    if (tau == my_len) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) hlast[b][j] = hv[b][j];
-                    }
-                }
-            }
+        for (int x = 0; x < NG; ++x) {
+            if (s0 + x * G + scen >= a.S) continue;
+            uint16_t *dst = (uint16_t *)a.xs + (s0 + x * G + scen) * (int64_t)a.ld + 16 * wu + 4 * u + b0;
+            if constexpr (NC == 4)      *(uint2 *)dst = uint2{pack_bf16x2(hlast[x][0], hlast[x][1]), pack_bf16x2(hlast[x][2], hlast[x][3])};
+            else if constexpr (NC == 2) *(uint32_t *)dst = pack_bf16x2(hlast[x][0], hlast[x][1]);
+            else                        *dst = (uint16_t)(pack_bf16x2(hlast[x][0], 0.f) & 0xffffu);
         }
     }
-    // ---- second layer's hidden state after the scenario's last layer -> columns 16 wu + 8 b + 4 hf .. + 3
-    if (role == 1 && s0 + l31 < a.S) {
-        uint16_t *row = (uint16_t *)a.xs + (s0 + l31) * (int64_t)a.ld + 16 * wu + 4 * hf;
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            uint2 pk = {pack_bf16x2(hlast[b][0], hlast[b][1]), pack_bf16x2(hlast[b][2], hlast[b][3])};
-            *(uint2 *)(row + 8 * b) = pk;
-        }
-    }
+}
+
+template <int G, int NG, int KQ>
+__global__ __launch_bounds__(512) void lstm_encoder_kernel(const LstmEncArgs a)
+{
+    __shared__ LstmLds<G, NG, KQ> lds;
+    // Of the two wavefronts of a SIMD the one of the second layer has more to do per step (four k steps against three,
+    // and the next step's embedding) and, being the younger one, would be served last: it gets the higher priority.
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8)) {
+        __builtin_amdgcn_s_setprio(2);
+        lstm_layer<G, NG, KQ, 1>(a, lds);
+    } else lstm_layer<G, NG, KQ, 0>(a, lds);
+}
+
+// As few scenarios a work-group as fill the CUs once: a call runs its steps one after another, and a step takes 0.50, 0.58, 0.81
+// and 1.49 us with 4, 8, 16 and 32 of them.  A call of 200 steps, us, with 4 / 8 / 16 / 32 a work-group: 16 scenarios 125 / 140 / 186 /
+// 325, 1024 153 / 167 / 213 / 353, 2048 287 / 196 / 242 / 380, 4096 557 / 374 / 298 / 436.  Beyond 16 a CU: 32.
+template <int KQ>
+static hipError_t launch_lstm(const LstmEncArgs &a, hipStream_t st)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    auto blocks = [&](int r) { return (unsigned)((a.S + r - 1) / r); };
+    if (a.S <= 4 * (int64_t)cus)       lstm_encoder_kernel<4, 1, KQ><<<blocks(4), 512, 0, st>>>(a);
+    else if (a.S <= 8 * (int64_t)cus)  lstm_encoder_kernel<8, 1, KQ><<<blocks(8), 512, 0, st>>>(a);
+    else if (a.S <= 16 * (int64_t)cus) lstm_encoder_kernel<16, 1, KQ><<<blocks(16), 512, 0, st>>>(a);
+    else if ((a.S + 31) / 32 > 0x7fffffffLL) return hipErrorInvalidValue;
+    else                               lstm_encoder_kernel<16, 2, KQ><<<blocks(32), 512, 0, st>>>(a);
+    return hipGetLastError();
 }
 
 hipError_t launch_lstm_encoder(const ab_model_desc *d, const float *dyn, const void *We, const float *be,
@@ -1815,10 +1881,7 @@ hipError_t launch_lstm_encoder(const ab_model_desc *d, const float *dyn, const v
     a.dyn = dyn; a.L = d->n_layers; a.K = d->n_stats; a.S = S;
     a.We = We; a.be = be; a.W1 = W1; a.b1 = b1; a.W2 = W2; a.b2 = b2; a.xs = xs; a.ld = ld;
     for (int i = 0; i < AB_MAX_ENCODER_STATS; ++i) a.enc_stat[i] = d->enc_stat[i];
-    const int64_t blocks = (S + 31) / 32;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    lstm_encoder_kernel<<<(unsigned)blocks, 512, 0, st>>>(a);
-    return hipGetLastError();
+    return a.K <= 4 ? launch_lstm<1>(a, st) : launch_lstm<2>(a, st);
 }
 
 hipError_t launch_tensor_encoder(const ab_model_desc *d, const float *dyn, const void *Wa, const float *ba,

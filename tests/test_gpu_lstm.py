@@ -131,3 +131,25 @@ def test_integer_tensor_encoder_with_own_layer_counts_is_reproduced_exactly():
     assert np.isfinite(ref).all() and len(np.unique(ref)) > 8
     assert (scores == ref.astype(np.float32)).all()
     assert (idx == ridx).all() and (best == rbest.astype(np.float32)).all()
+
+
+@pytest.mark.parametrize("S,K,L", [(3, 1, 1), (1024, 8, 3), (1027, 5, 17), (2048, 4, 2), (2051, 3, 33), (4096, 8, 18), (4133, 4, 16),
+                                   (4109, 7, 31)])
+def test_lstm_encoder_at_every_number_of_scenarios_a_work_group(S, K, L):
+    """Work-groups of 4, 8, 16 and 32 scenarios (up to 4, 8, 16 a CU of 256, and beyond), with remainders; one to eight
+    statistics a layer; chunks of sixteen steps and their borders; own layer counts with NaN in the padding."""
+    from gpu_helpers import Scorer
+    w = wl.make_lstm_encoder("lstm-groups", S, [64], 2, 2, "bf16", 100 + K, n_blocks=1, per_block=L, extra=0)
+    assert w.L == L
+    cols = np.arange(K) % 4
+    w.K, w.stat_enc = K, [w.stat_enc[c] for c in cols]
+    w.te_W[0], w.dyn = w.te_W[0][:, cols].copy(), w.dyn[:, :, cols].copy()
+    lens = np.random.default_rng(S).integers(1, L + 1, S).astype(np.int32)
+    for s in range(S):
+        w.dyn[s, lens[s]:] = np.nan
+    scores, idx, best = Scorer(w).run(layers_of=lens)
+    ref = orc.score(oracle_model(w), w.dyn, w.scal, w.part, w.cred, layers_of=lens)
+    err, strict = tensor_scaled_error(scores, ref), scaled_error(scores, ref)
+    print("S=%d K=%d L=%d: rel err %.3g strict %.3g" % (S, K, L, err, strict))
+    assert np.isfinite(scores).all() and err <= TOL and strict <= 5e-2
+    check_selection(idx, ref, TOL)
