@@ -35,6 +35,21 @@ static bool slim(int64_t M, int N) { return (M + 31) / 32 * (N / 32) <= kSlimTil
 // (234) 19.3 -> 19.1, 60000 21.8 -> 20.6; 256-128-64 with 16000 34.8 -> 39.4, 30000 47.2 -> 42.7.
 static const int64_t kSplitTiles = 192;
 
+// bf16 products of at least so many 256 x 256 tiles go to gemm_big.hip and gemm_span.hip, smaller ones to the generic tiles, which fill
+// more CUs but have one slab requested ahead.  Up to 1024 columns a product of less than a round goes in parts of its tiles, so
+// the line lies low; where a pass has this product alone, lowest.  Whole calls, 50 layers of statistics, generic / 256 x 256, us, by tiles:
+//   one product: 1024-1024 16 tiles 28.6 / 22.1, 56 32.9 / 23.1; 768-768 12 24.7 / 19.1 (with 255 candidates 24.5 / 20.7); 1024-256 12 28.2 / 21.9
+//     (28.0 / 23.7); 256-256 24 15.4 / 14.6 (15.5 / 15.4), 48 16.5 / 14.7 (16.6 / 15.6); 128-1024 32 13.5 / 13.2 (13.6 / 14.0), 56 14.8 / 13.7
+//   several: 512-512-512 32 26.0 / 26.2 (26.1 / 27.4), 40 29.7 / 26.4; 768-768-768 30 32.4 / 31.4 (32.3 / 33.2), 36 37.3 / 31.5; 1024 four
+//     times 32 49.7 / 58.0, 40 57.5 / 58.0 (57.5 / 59.5), 48 60.4 / 58.1; 256-256-256 32 21.0 / 22.4, 48 23.2 / 22.8 (23.3 / 23.4)
+static const int64_t kBigTiles = 64;
+static int64_t big_tiles_least(int K, int N, bool alone)
+{
+    if (N > 1024) return kBigTiles;
+    if (alone) return K >= 512 ? 12 : 40;
+    return K < 512 ? kBigTiles : K < 1024 ? 36 : 44;
+}
+
 static ab_status check_desc(const ab_model_desc *d)
 {
     if (!d) return AB_ERR_NULL;
@@ -107,18 +122,19 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
     p->chunk_scen = cs;
     p->chunk_rows = cs * C;
     p->tile_a = slim(S, p->H[0]) ? TILE_SLIM : pick_tile(S, p->H[0]);
+    auto big_tiles = [&](int k) { return (p->chunk_rows + 255) / 256 * (p->H[k] / 256); };
     for (int k = 1; k < p->D; ++k) {
         p->tile[k] = pick_tile(p->chunk_rows, p->H[k]);
-        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 ||
-            ((p->chunk_rows + 255) / 256) * (p->H[k] / 256) < 64)            // (measured crossover against the generic tiles)
-            continue;
+        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 || big_tiles(k) < big_tiles_least(p->H[k - 1], p->H[k], p->D == 2)) continue;
         if (k > 1 || C % 256 == 0) p->big[k] = BIG_TILE;       // (its generating kernel has one scenario per row tile)
         else if (gemm_span_shape(C, p->H[0], p->H[k])) p->big[k] = BIG_SPAN;
     }
     p->nt_last = 1;
+    int nt_room = 1;              // (the generic tiles' below kBigTiles, so that a workspace serves fewer scenarios as well)
     if (p->D >= 2) {
-        const int kl = p->D - 1;
-        p->nt_last = p->big[kl] ? p->H[kl] / 256 : p->H[kl] / tile_edge(p->tile[kl]);
+        const int kl = p->D - 1, generic = p->H[kl] / tile_edge(p->tile[kl]);
+        p->nt_last = p->big[kl] ? p->H[kl] / 256 : generic;
+        nt_room = p->big[kl] && big_tiles(kl) >= kBigTiles ? p->nt_last : generic;
     }
     const size_t es = elem_size(p->dtype);
     size_t off = 0;
@@ -130,7 +146,7 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
     p->off_cfgv = take(((size_t)2 * p->H[0] + 2 * (size_t)C) * 4);
     p->off_wout = take((size_t)(p->H[p->D - 1] + 1) * 4);     // folded output weights, then the folded bias
     p->off_xrow = take((size_t)p->chunk_rows * 2 * 4);          // per-scenario grids: (phi(S_p), phi(S_c)) of a chunk's rows
-    p->off_partial = take((size_t)p->chunk_rows * p->nt_last * 4);
+    p->off_partial = take((size_t)p->chunk_rows * nt_room * 4);
     p->off_act0 = p->off_act1 = 0;
     if (p->D >= 3) p->off_act0 = take((size_t)p->chunk_rows * hmax * es);
     if (p->D >= 4) p->off_act1 = take((size_t)p->chunk_rows * hmax * es);

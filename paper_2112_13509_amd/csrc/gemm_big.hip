@@ -316,8 +316,14 @@ __global__ __launch_bounds__(512) void gemm_big_kernel(const GemmArgs g)
 //   - bias (and output weights) are read through the scalar cache in the epilogue, so no ordinary
 //     vector load has to be waited for while slab fetches are in flight.
 //
-template <int EPI, bool COL_REGS>
-__global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
+// Where the tiles are no whole number of rounds and the last round's are at most a half (a quarter) of the work-groups, each of
+// them is shared out among PARTS = 2 (4) of those by rows: a part is multiplied with 2 (1) instead of 4 row blocks a wavefront.  A
+// product of less than a round is all parts.  Whole calls, whole tiles / parts, us: 1024 four times x 256 candidates, 16 scenarios (64
+// tiles) 76 / 59, 32 77 / 64, 65 (260) 142 / 127, 96 154 / 144, 144 229 / 216, 330 447 / 434; 512-512, 144 scenarios (288) 34.4 / 30.3,
+// 300 (600) 47.7 / 45.1.  (A tile of a nearly empty round is faster than one of a full round: the clock is higher.)  W of a part
+// requested two slabs ahead, in a third stage behind the rows that a part leaves free, gave another 0 to 3 % and is not kept.
+template <int EPI, bool COL_REGS, int PARTS>
+__device__ __forceinline__ void stream_tiles(const GemmArgs &g)
 {
     // (the storing epilogue's staging areas fill the idle stage; with it the scalar loads hide under the draining stores anyway)
     static_assert(!(COL_REGS && EPI == EPI_STORE), "COL_REGS goes with the fused output unit only");
@@ -340,8 +346,9 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     const unsigned n_tiles = (unsigned)g.n_tiles;
     const unsigned panels = (unsigned)g.m_tiles > xcd ? ((unsigned)g.m_tiles - xcd + 7) / 8 : 0;
     const unsigned n_local = panels * n_tiles;
-    if (l0 >= n_local) return;
-    const unsigned n_my = (n_local - l0 + G8 - 1) / G8;
+    const LastRound last = last_round<PARTS>(n_local, G8, l0);
+    const unsigned n_my = last.n_my;
+    if (n_my == 0) return;
 
     // ---- DMA sources: a wave-uniform byte pointer per operand (advanced per slab on the scalar unit) plus
     // four 32-bit per-lane byte offsets (row dma_r0 + 64 i, chunk dma_cc)
@@ -349,7 +356,7 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     const unsigned char *a_base, *w_base;
     uint32_t a_off[4], w_off[4];
     auto set_w = [&](unsigned q) {
-        const unsigned local = l0 + q * G8;
+        const unsigned local = last.tile(q, l0, G8);
         w_base = (const unsigned char *)g.B + (int64_t)(local % n_tiles) * 256 * g.ldb * 2;
         const int ln = opaque_lane();
         const int dma_cc = (ln & 7) ^ ((wave & 1) * 4 + (ln >> 4)), dma_r0 = wave * 8 + (ln >> 3);
@@ -357,8 +364,9 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
         for (int i = 0; i < 4; ++i) w_off[i] = (uint32_t)(dma_r0 + 64 * i) * (uint32_t)g.ldb * 2u + dma_cc * 16;
     };
     auto set_a = [&](unsigned q) {
-        const unsigned local = l0 + q * G8;
-        const int64_t m0 = ((int64_t)(local / n_tiles) * 8 + xcd) * BM;
+        const unsigned local = last.tile(q, l0, G8);
+        int64_t m0 = ((int64_t)(local / n_tiles) * 8 + xcd) * BM;
+        if constexpr (PARTS > 1) m0 = min(m0 + last.row(q), g.M - 1);        // (a part may lie past the end as a whole)
         a_base = (const unsigned char *)g.A + m0 * g.lda * 2;
         const int64_t rows_left = g.M - m0;                 // >= 1; rows past the end re-read the last row
         const int ln = opaque_lane();
@@ -379,10 +387,10 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
         dma16<false>(w_base + w_off[i0], sb + (wave + 8 * i0) * 1024);
         dma16<false>(w_base + w_off[i0 + 1], sb + (wave + 8 * (i0 + 1)) * 1024);
     };
-    auto dma_a_rows = [&](int slot, int i0) {
+    auto dma_a_rows = [&](int slot, int i0, bool one = false) {
         unsigned char *sb = smem + slot * SLAB;
         dma16<true>(a_base + a_off[i0], sb + (wave + 8 * i0) * 1024);
-        dma16<true>(a_base + a_off[i0 + 1], sb + (wave + 8 * (i0 + 1)) * 1024);
+        if (!one) dma16<true>(a_base + a_off[i0 + 1], sb + (wave + 8 * (i0 + 1)) * 1024);
     };
     auto advance_w = [&]() {
         w_base += BK * 2;
@@ -398,34 +406,35 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     int rd[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) rd[q] = l31 * 128 + ((((q << 1) | half) ^ sw) << 4);
-    const int a_rd = wave_m * 128 * 128;
     const int w_rd = W_BASE + wave_n * 64 * 128;
 
     f32x16 acc[2][4];
     f32x16 cinit[2];                                       // the tile's bias in accumulator layout (same for all four row blocks)
     i32x4 fa[2][4], fw[2][2];
-    auto load_frags = [&](int a_slot, int w_slot, int q, int set) {
-        const unsigned char *sa = smem + a_slot * SLAB + a_rd;
+    // (the tags name the row blocks of 32 a wavefront takes: 4, or fewer of a part)
+    auto load_frags = [&](auto im_tag, int a_slot, int w_slot, int q, int set) {
+        constexpr int IM = decltype(im_tag)::value;
+        const unsigned char *sa = smem + a_slot * SLAB + wave_m * (IM * 4096);
         const unsigned char *sw_ = smem + w_slot * SLAB + w_rd;
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) fw[set][jn] = *(const i32x4 *)(sw_ + jn * 4096 + rd[q]);
 #pragma unroll
-        for (int im = 0; im < 4; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
+        for (int im = 0; im < IM; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
     };
-    auto mma = [&](int set) {
+    auto mma = [&](auto im_tag, int set) {
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 0; im < 4; ++im)
+            for (int im = 0; im < decltype(im_tag)::value; ++im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     acc[jn][im], 0, 0, 0);
     };
-    auto mma_first = [&](int set) {                        // a tile's first quarter: the accumulators start at the bias
+    auto mma_first = [&](auto im_tag, int set) {           // a tile's first quarter: the accumulators start at the bias
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 0; im < 4; ++im)
+            for (int im = 0; im < decltype(im_tag)::value; ++im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     cinit[jn], 0, 0, 0);
@@ -459,10 +468,11 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     // accumulators' starting value, in their layout: register rg*4+e of column block jn is column
     // jn*32 + rg*8 + (lane>>5)*4 + e.
     auto begin_tile = [&](unsigned q, int idle_stage) {
-        const unsigned local = l0 + q * G8;
+        const unsigned local = last.tile(q, l0, G8);
         tn = local % n_tiles;
         n0 = (int)tn * 256;
         m0 = ((int64_t)(local / n_tiles) * 8 + xcd) * BM;
+        if constexpr (PARTS > 1) m0 += last.row(q);
         const int ln = opaque_lane();
         const int hf = ln >> 5;
         const unsigned char *scr = smem + idle_stage * SLAB + 4096 + wave * 256;     // behind the row sums' exchange area
@@ -498,7 +508,6 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     // A stricter wait than needed is always safe.
     constexpr int EPI_OPS_LOW = EPI == EPI_STORE ? 16 : 1;              // wavefronts 0..3
     constexpr int EPI_OPS_HIGH = EPI == EPI_STORE ? 16 : 0;             // wavefronts 4..7 (no partial store)
-    static_assert(EPI_OPS_LOW + 4 == (EPI == EPI_STORE ? 20 : 5) && EPI_OPS_HIGH + 4 == (EPI == EPI_STORE ? 20 : 4), "");
 
     // ---- prologue: slabs 0 and 1 whole
     set_w(0); set_a(0);
@@ -511,7 +520,6 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     AB_FENCE();
-    load_frags(0, 0, 0, 0);
 
     int a_slot = 0, w_slot = 0;
     unsigned q = 0;
@@ -523,37 +531,36 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
     // runs alone, and each would expose its own fragment-read latencies.  With the priority falling from quarter
     // to quarter the wavefront that is behind wins, the two stay within one quarter of each other (the wait falls
     // to about 400 cycles) and fill each other's gaps.
-    auto slab = [&](auto first_tag) {
+    auto slab = [&](auto im_tag, auto first_tag) {
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int IM = decltype(im_tag)::value;         // also the requests of an A slab
         const int pa = a_slot == 0 ? 2 : a_slot - 1;       // the A stage retired one slab ago
         AB_FENCE();
         __builtin_amdgcn_s_setprio(2);
-        load_frags(a_slot, w_slot, 1, 1);
-        dma_a_rows(pa, 0);
-        dma_a_rows(pa, 2);
-        if constexpr (FIRST) mma_first(0); else mma(0);
-        AB_INTERLEAVE_6_V4();
+        load_frags(im_tag, a_slot, w_slot, 1, 1);
+        dma_a_rows(pa, 0, IM == 1);
+        if constexpr (IM == 4) dma_a_rows(pa, 2);
+        if constexpr (FIRST) mma_first(im_tag, 0); else mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6_V4(); else AB_INTERLEAVE_PART(IM, IM);
         AB_FENCE();
         advance_a();
         AB_FENCE();
         __builtin_amdgcn_s_setprio(1);
-        load_frags(a_slot, w_slot, 2, 0);
-        mma(1);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 2, 0);
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         __builtin_amdgcn_s_setprio(0);
-        load_frags(a_slot, w_slot, 3, 1);
-        mma(0);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 3, 1);
+        mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         if (!FIRST || q == 0) {
-            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"i"(IM) : "memory");
         } else if (wave < 4) {
-            if constexpr (EPI == EPI_STORE) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
-            else                            asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"i"(EPI_OPS_LOW + IM) : "memory");
         } else {
-            if constexpr (EPI == EPI_STORE) asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
-            else                            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"i"(EPI_OPS_HIGH + IM) : "memory");
         }
         // own fragment reads of this slab returned; then meet: slab j+1 is complete and visible to
         // everybody and slab j's stages may be refilled
@@ -562,33 +569,34 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
         AB_FENCE();
         __builtin_amdgcn_s_setprio(3);
         const int na = a_slot == 2 ? 0 : a_slot + 1, nw = w_slot ^ 1;
-        load_frags(na, nw, 0, 0);
+        load_frags(im_tag, na, nw, 0, 0);
         dma_w_rows(w_slot, 0);
         dma_w_rows(w_slot, 2);
-        mma(1);
-        AB_INTERLEAVE_6_V4();
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6_V4(); else AB_INTERLEAVE_PART(IM, 4);
         AB_FENCE();
         advance_w();
         a_slot = na;
         w_slot = nw;
     };
-    while (true) {
-        slab(std::true_type{});
-        for (int kt = 1; kt < KT; ++kt) slab(std::false_type{});
+    auto tile = [&](auto im_tag) {
+        constexpr int IM = decltype(im_tag)::value;
+        slab(im_tag, std::true_type{});
+        for (int kt = 1; kt < KT; ++kt) slab(im_tag, std::false_type{});
         {
             // ------------------------------------------------------------ epilogue of tile q
             // staging room: the A stage retired by the last barrier; A(j+3) goes there later
             unsigned char *stage = smem + (a_slot == 0 ? 2 : a_slot - 1) * SLAB;
-            const bool ragged = m0 + BM > g.M;
+            const bool ragged = m0 + IM * 64 > g.M;
             const int ln = opaque_lane();
             const int half = ln >> 5, l31 = ln & 31, sw = (l31 >> 1) & 7;
             if constexpr (EPI == EPI_STORE) {
                 unsigned char *mine = stage + wave * 4096;
                 const int rrow = ln >> 3, rch = ln & 7;
-                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * 128 + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
+                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * (IM * 32) + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
                 auto store_tile = [&](auto relu_tag) {
 #pragma unroll
-                    for (int im = 0; im < 4; ++im) {
+                    for (int im = 0; im < IM; ++im) {
 #pragma unroll
                         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
@@ -616,7 +624,7 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
                         } else {
 #pragma unroll
                             for (int it = 0; it < 4; ++it)
-                                if (m0 + wave_m * 128 + im * 32 + rrow + 8 * it < g.M)
+                                if (m0 + wave_m * (IM * 32) + im * 32 + rrow + 8 * it < g.M)
                                     __builtin_nontemporal_store(o[it], (i32x4 *)(d + (int64_t)(8 * it) * g.ldo));
                         }
                     }
@@ -624,7 +632,9 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
                 if (g.relu) store_tile(std::true_type{});
                 else        store_tile(std::false_type{});
             } else {   // EPI_SCORE
-                float ps[4] = {0.f, 0.f, 0.f, 0.f};
+                float ps[IM];
+#pragma unroll
+                for (int im = 0; im < IM; ++im) ps[im] = 0.f;
                 const unsigned char *scr = stage + 4096 + wave * 256;      // behind the row sums' exchange area
                 if constexpr (COL_REGS) {
                     const float wsel = tn == 0 ? wout_v[0] : tn == 1 ? wout_v[1] : tn == 2 ? wout_v[2] : wout_v[3];
@@ -644,19 +654,19 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
                             if constexpr (COL_REGS) wv = w4[e];
                             else wv = half ? w8[4 + e] : w8[e];
 #pragma unroll
-                            for (int im = 0; im < 4; ++im)
+                            for (int im = 0; im < IM; ++im)
                                 ps[im] += relu_keep_nan(acc[jn][im][rg * 4 + e]) * wv;
                         }
                     }
                 float *red = (float *)stage;               // [4 column-waves][256 rows]
 #pragma unroll
-                for (int im = 0; im < 4; ++im) {
+                for (int im = 0; im < IM; ++im) {
                     const float v = ps[im] + __shfl_xor(ps[im], 32, 64);
-                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * 128 + l31 + im * 32, v);
+                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * (IM * 32) + l31 + im * 32, v);
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
-                if (wave < 4) {
+                if (wave < IM) {
                     const int tt = wave * 64 + ln;
                     const float v = (red[tt] + red[BM + tt]) + (red[2 * BM + tt] + red[3 * BM + tt]);
                     if (!ragged) g.partial[(m0 + tt) * g.n_tiles + tn] = v;
@@ -665,8 +675,23 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
             }
             // a ragged tile may have issued fewer stores than the counts assume: drain instead
             if (ragged) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (q + 1 == n_my) break;
-            ++q;
+        }
+    };
+    typedef std::integral_constant<int, 4> full_tag;
+    typedef std::integral_constant<int, 4 / PARTS> part_tag;
+    load_frags(full_tag{}, 0, 0, 0, 0);
+    while (true) {
+        if constexpr (PARTS > 1) {
+            if (q == last.q_part) {
+                load_frags(part_tag{}, a_slot, w_slot, 0, 0);      // (the last tile's wavefronts had other rows)
+                tile(part_tag{});
+                break;
+            }
+        }
+        tile(full_tag{});
+        if (q + 1 == n_my) break;
+        ++q;
+        {
             // the next tile's coordinates and bias: through the staging room, which this wavefront is done with,
             // or by scalar loads, which are better left to return under the draining stores behind the barrier
             if constexpr (COL_REGS) begin_tile(q, a_slot == 0 ? 2 : a_slot - 1);
@@ -696,8 +721,8 @@ __global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g)
 //     is therefore for everything, at a tile's first slab 19 operations may stay in flight, unless the tile has two
 //     slabs only: then the next slab already reads what the vector fetch brings.
 // Needs K <= 1024 (vector area) and at least two slabs.
-template <int EPI, bool COL_REGS, bool SHARE>
-__global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
+template <int EPI, bool COL_REGS, bool SHARE, int PARTS>
+__device__ __forceinline__ void stream_gen_tiles(const GemmArgs &g)
 {
     constexpr int BM = 256, BK = 64;
     constexpr int SLAB = BM * 128;
@@ -717,14 +742,15 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     const unsigned n_tiles = (unsigned)g.n_tiles;
     const unsigned panels = (unsigned)g.m_tiles > xcd ? ((unsigned)g.m_tiles - xcd + 7) / 8 : 0;
     const unsigned n_local = panels * n_tiles;
-    if (l0 >= n_local) return;
-    const unsigned n_my = (n_local - l0 + G8 - 1) / G8;
+    const LastRound last = last_round<PARTS>(n_local, G8, l0);
+    const unsigned n_my = last.n_my;
+    if (n_my == 0) return;
 
     // ---- W slabs by DMA
     const unsigned char *w_base;
     uint32_t w_off[4];
     auto set_w = [&](unsigned q) {
-        const unsigned local = l0 + q * G8;
+        const unsigned local = last.tile(q, l0, G8);
         w_base = (const unsigned char *)g.B + (int64_t)(local % n_tiles) * 256 * g.ldb * 2;
         const int ln = opaque_lane();
         const int dma_cc = (ln & 7) ^ ((wave & 1) * 4 + (ln >> 4)), dma_r0 = wave * 8 + (ln >> 3);
@@ -747,17 +773,20 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     auto fetch_vec = [&](unsigned qq) {
         const int b = (int)(qq & 1);
         if (qq > n_my - 1) qq = n_my - 1;
-        const unsigned local = l0 + qq * G8;
-        const unsigned m0u = ((local / n_tiles) * 8 + xcd) * BM;
-        const unsigned s = m0u / (unsigned)g.C, c0 = m0u - s * (unsigned)g.C;
+        const unsigned local = last.tile(qq, l0, G8);
+        unsigned m0u = ((local / n_tiles) * 8 + xcd) * BM;
+        const unsigned s = m0u / (unsigned)g.C;
         const int ln = opaque_lane();
+        int xi = (wave & 3) * 64 + ln;                      // (of a part: its rows first, the last one's again behind the tile's end)
+        if constexpr (PARTS > 1) xi = min(xi + (int)last.row(qq), 255);
+        const unsigned c0 = m0u - s * (unsigned)g.C;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             int i = wave + 8 * h;
             if (i > KT - 1) i = KT - 1;
             dma4(g.a_term + (int64_t)s * g.ldt + i * 64 + ln, smem + V_AT + b * 4096 + i * 256);
         }
-        dma4((wave < 4 ? g.xp : g.xc) + (g.x_per_row ? m0u : c0) + (wave & 3) * 64 + ln,
+        dma4((wave < 4 ? g.xp : g.xc) + (g.x_per_row ? m0u : c0) + xi,
              smem + V_XP + b * 2048 + (wave >> 2) * 1024 + (wave & 3) * 256);
     };
     auto fetch_wp_wc = [&]() {                              // 4 requests per wavefront, once
@@ -774,14 +803,28 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     // ---- generation: thread -> k chunk t & 7 of the four adjacent rows 4 (t >> 3) + i.  With SHARE (the rows of
     // such a group take the same xp, GemmArgs::xp_runs4) the inner term wp * xp + a_term is formed once for the
     // four rows: 5 instead of 8 fused multiply-adds per row chunk, the same values bit for bit.
-    const int gcc = t & 7, grow4 = (t >> 3) * 4;
+    // Of a part a thread owns IM = 2 or 1 adjacent rows.
+    const int gcc = t & 7;
     int gen_st[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) gen_st[i] = (grow4 + i) * 128 + ((gcc ^ (((grow4 + i) >> 1) & 7)) << 4);
     f32x4 gxp, gxc;
-    auto load_xpc = [&](int b) {
-        gxp = *(const f32x4 *)(smem + V_XP + b * 2048 + grow4 * 4);
-        gxc = *(const f32x4 *)(smem + V_XP + b * 2048 + 1024 + grow4 * 4);
+    auto load_xpc = [&](auto im_tag, int b) {
+        constexpr int IM = decltype(im_tag)::value;
+        const float *px = (const float *)(smem + V_XP + b * 2048) + (t >> 3) * IM, *pc = px + 256;
+        if constexpr (IM == 4) {
+            gxp = *(const f32x4 *)px;
+            gxc = *(const f32x4 *)pc;
+        } else {
+#pragma unroll
+            for (int i = 0; i < IM; ++i) { gxp[i] = px[i]; gxc[i] = pc[i]; }
+        }
+    };
+    auto own_rows = [&](auto im_tag) {
+        constexpr int IM = decltype(im_tag)::value;
+#pragma unroll
+        for (int i = 0; i < IM; ++i) {
+            const int row = (t >> 3) * IM + i;
+            gen_st[i] = row * 128 + ((gcc ^ ((row >> 1) & 7)) << 4);
+        }
     };
     f32x4 va[2], vp[2], vc[2];
     auto load_slices = [&](int b, int gk) {
@@ -814,35 +857,35 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     int rd[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) rd[q] = l31 * 128 + ((((q << 1) | half) ^ sw) << 4);
-    const int a_rd = wave_m * 128 * 128;
     const int w_rd = W_BASE + wave_n * 64 * 128;
 
     f32x16 acc[2][4];
     f32x16 cinit[2];                                       // the tile's bias in accumulator layout
     i32x4 fa[2][4], fw[2][2];
-    auto load_frags = [&](int a_slot, int w_slot, int q, int set) {
-        const unsigned char *sa = smem + a_slot * SLAB + a_rd;
+    auto load_frags = [&](auto im_tag, int a_slot, int w_slot, int q, int set) {
+        constexpr int IM = decltype(im_tag)::value;
+        const unsigned char *sa = smem + a_slot * SLAB + wave_m * (IM * 4096);
         const unsigned char *sw_ = smem + w_slot * SLAB + w_rd;
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) fw[set][jn] = *(const i32x4 *)(sw_ + jn * 4096 + rd[q]);
 #pragma unroll
-        for (int im = 0; im < 4; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
+        for (int im = 0; im < IM; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
     };
-    auto mma = [&](int set) {
+    auto mma = [&](auto im_tag, int set) {
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 0; im < 4; ++im)
+            for (int im = 0; im < decltype(im_tag)::value; ++im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     acc[jn][im], 0, 0, 0);
     };
 
-    auto mma_first = [&](int set) {                        // a tile's first quarter: the accumulators start at the bias
+    auto mma_first = [&](auto im_tag, int set) {           // a tile's first quarter: the accumulators start at the bias
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 0; im < 4; ++im)
+            for (int im = 0; im < decltype(im_tag)::value; ++im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     cinit[jn], 0, 0, 0);
@@ -887,10 +930,11 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
             }
     };
     auto begin_tile = [&](unsigned q) {
-        const unsigned local = l0 + q * G8;
+        const unsigned local = last.tile(q, l0, G8);
         tn = local % n_tiles;
         n0 = (int)tn * 256;
         m0 = ((int64_t)(local / n_tiles) * 8 + xcd) * BM;
+        if constexpr (PARTS > 1) m0 += last.row(q);
     };
 
     // ---- prologue
@@ -906,13 +950,16 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     __builtin_amdgcn_s_barrier();                          // vectors, column tables and W(0) are in LDS for everybody
     AB_FENCE();
     load_cinit();
-    load_xpc(0);
+    typedef std::integral_constant<int, 4> full_tag;
+    typedef std::integral_constant<int, 4 / PARTS> part_tag;
+    own_rows(full_tag{});
+    load_xpc(full_tag{}, 0);
     load_slices(0, 0);
     gen_chunk(0, 0); gen_chunk(0, 1); gen_chunk(0, 2); gen_chunk(0, 3);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();                          // A(0) is complete
     AB_FENCE();
-    load_frags(0, 0, 0, 0);
+    load_frags(full_tag{}, 0, 0, 0, 0);
 
     int a_slot = 0, w_slot = 0, gpar = 0;
     unsigned q = 0;
@@ -922,31 +969,32 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
     // work fills them), so taking turns by progress as in the stored-operand kernel changes nothing; what the clock
     // stamps show is the younger wavefront held up in the first quarter, the one with two row chunks to generate
     // (990 cycles against 510).  It goes first there (3 against 0), after that the priority falls with progress.
-    auto slab = [&](auto first_tag, int kt) {
+    auto slab = [&](auto im_tag, auto first_tag, int kt) {
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int IM = decltype(im_tag)::value;
         const int nxt = a_slot ^ 1;                        // retired one slab ago: slab j+1 is generated there
         int gk = kt + 1;                                   // its place in its tile
-        if (gk == KT) { gk = 0; gpar ^= 1; load_xpc(gpar); }
+        if (gk == KT) { gk = 0; gpar ^= 1; load_xpc(im_tag, gpar); }
         load_slices(gpar, gk);
         AB_FENCE();
         if (wave_m) __builtin_amdgcn_s_setprio(3); else __builtin_amdgcn_s_setprio(0);
-        load_frags(a_slot, w_slot, 1, 1);
+        load_frags(im_tag, a_slot, w_slot, 1, 1);
         gen_chunk(nxt, 0);
-        gen_chunk(nxt, 1);
-        if constexpr (FIRST) mma_first(0); else mma(0);
-        AB_INTERLEAVE_6();
+        if constexpr (IM > 1) gen_chunk(nxt, 1);
+        if constexpr (FIRST) mma_first(im_tag, 0); else mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         __builtin_amdgcn_s_setprio(1);
-        load_frags(a_slot, w_slot, 2, 0);
-        gen_chunk(nxt, 2);
-        mma(1);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 2, 0);
+        if constexpr (IM == 4) gen_chunk(nxt, 2);
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         __builtin_amdgcn_s_setprio(0);
-        load_frags(a_slot, w_slot, 3, 1);
-        gen_chunk(nxt, 3);
-        mma(0);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 3, 1);
+        if constexpr (IM == 4) gen_chunk(nxt, 3);
+        mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         if (!FIRST || q == 0 || KT == 2) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -963,19 +1011,20 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
         AB_FENCE();
         __builtin_amdgcn_s_setprio(2);
         const int nw = w_slot ^ 1;
-        load_frags(nxt, nw, 0, 0);
+        load_frags(im_tag, nxt, nw, 0, 0);
         dma_w_rows(w_slot, 0);
         dma_w_rows(w_slot, 2);
-        mma(1);
-        AB_INTERLEAVE_6_V4();
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6_V4(); else AB_INTERLEAVE_PART(IM, 4);
         AB_FENCE();
         advance_w();
         a_slot = nxt;
         w_slot = nw;
     };
-    while (true) {
-        slab(std::true_type{}, 0);
-        for (int kt = 1; kt < KT; ++kt) slab(std::false_type{}, kt);
+    auto tile = [&](auto im_tag) {
+        constexpr int IM = decltype(im_tag)::value;
+        slab(im_tag, std::true_type{}, 0);
+        for (int kt = 1; kt < KT; ++kt) slab(im_tag, std::false_type{}, kt);
         {
             // ------------------------------------------------------------ epilogue of tile q (never ragged)
             unsigned char *stage = smem + (a_slot ^ 1) * SLAB;            // the A stage retired by the last barrier
@@ -984,10 +1033,10 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
             if constexpr (EPI == EPI_STORE) {
                 unsigned char *mine = stage + wave * 4096;
                 const int rrow = ln >> 3, rch = ln & 7;
-                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * 128 + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
+                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * (IM * 32) + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
                 auto store_tile = [&](auto relu_tag) {
 #pragma unroll
-                    for (int im = 0; im < 4; ++im) {
+                    for (int im = 0; im < IM; ++im) {
 #pragma unroll
                         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
@@ -1016,7 +1065,9 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
                 if (g.relu) store_tile(std::true_type{});
                 else        store_tile(std::false_type{});
             } else {   // EPI_SCORE: the output unit as a per-lane dot product, reduced over the four column wavefronts
-                float ps[4] = {0.f, 0.f, 0.f, 0.f};
+                float ps[IM];
+#pragma unroll
+                for (int im = 0; im < IM; ++im) ps[im] = 0.f;
 #pragma unroll
                 for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
@@ -1031,26 +1082,40 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
                             if constexpr (COL_REGS) wv = w4[e];
                             else wv = half ? w8[4 + e] : w8[e];
 #pragma unroll
-                            for (int im = 0; im < 4; ++im)
+                            for (int im = 0; im < IM; ++im)
                                 ps[im] += relu_keep_nan(acc[jn][im][rg * 4 + e]) * wv;
                         }
                     }
                 float *red = (float *)stage;               // [4 column-waves][256 rows]
 #pragma unroll
-                for (int im = 0; im < 4; ++im) {
+                for (int im = 0; im < IM; ++im) {
                     const float v = ps[im] + __shfl_xor(ps[im], 32, 64);
-                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * 128 + l31 + im * 32, v);
+                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * (IM * 32) + l31 + im * 32, v);
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
-                if (wave < 4) {
+                if (wave < IM) {
                     const int tt = wave * 64 + ln;
                     const float v = (red[tt] + red[BM + tt]) + (red[2 * BM + tt] + red[3 * BM + tt]);
                     g.partial[(m0 + tt) * g.n_tiles + tn] = v;
                 }
             }
-            if (q + 1 == n_my) break;
-            ++q;
+        }
+    };
+    while (true) {
+        if constexpr (PARTS > 1) {
+            if (q == last.q_part) {                        // (its first slab was generated as a whole tile's)
+                own_rows(part_tag{});
+                load_xpc(part_tag{}, gpar);
+                load_frags(part_tag{}, a_slot, w_slot, 0, 0);
+                tile(part_tag{});
+                break;
+            }
+        }
+        tile(full_tag{});
+        if (q + 1 == n_my) break;
+        ++q;
+        {
             begin_tile(q);
             if constexpr (COL_REGS) load_cinit();          // (a fixed table: its reads may return under the wait below)
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1064,38 +1129,39 @@ __global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g)
 }
 
 template <int EPI, bool COL_REGS, bool SHARE>
-static hipError_t launch_stream_gen_impl(const GemmArgs &g, hipStream_t st);
-template <int EPI>
+__global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g) { stream_gen_tiles<EPI, COL_REGS, SHARE, 1>(g); }
+template <int EPI, bool COL_REGS>
+__global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g) { stream_tiles<EPI, COL_REGS, 1>(g); }
+// those whose last round's tiles go in parts
+template <int EPI, bool SHARE, int PARTS>
+__global__ __launch_bounds__(512) void gemm_parts_gen_kernel(const GemmArgs g) { stream_gen_tiles<EPI, true, SHARE, PARTS>(g); }
+template <int EPI, int PARTS>
+__global__ __launch_bounds__(512) void gemm_parts_kernel(const GemmArgs g) { stream_tiles<EPI, EPI == EPI_SCORE, PARTS>(g); }
+
+static hipError_t launch_stream_as(void (*kern)(GemmArgs), int smem, DeviceOnce &once, const GemmArgs &g, unsigned blocks, hipStream_t st)
+{
+    const hipError_t e = ensure_dynamic_lds((const void *)kern, smem, once);
+    if (e != hipSuccess) return e;
+    kern<<<blocks, 512, smem, st>>>(g);
+    return hipGetLastError();
+}
+
+template <int EPI, bool SHARE>
 static hipError_t launch_stream_gen(const GemmArgs &g, hipStream_t st)
 {
     // at most four column tiles: bias and output weights sit in LDS tables (8 KB behind the vector area); otherwise
     // they come by scalar loads
-    if (g.xp_runs4)
-        return g.n_tiles <= 4 ? launch_stream_gen_impl<EPI, true, true>(g, st) : launch_stream_gen_impl<EPI, false, true>(g, st);
-    return g.n_tiles <= 4 ? launch_stream_gen_impl<EPI, true, false>(g, st) : launch_stream_gen_impl<EPI, false, false>(g, st);
-}
-template <int EPI, bool COL_REGS, bool SHARE>
-static hipError_t launch_stream_gen_impl(const GemmArgs &g, hipStream_t st)
-{
-    constexpr int smem = 4 * 256 * 128 + 20480 + (COL_REGS ? 8192 : 0);
-    auto kern = gemm_stream_gen_kernel<EPI, COL_REGS, SHARE>;
-    static DeviceOnce once;
-    hipError_t e = ensure_dynamic_lds((const void *)kern, smem, once);
-    if (e != hipSuccess) return e;
-    int cus = 0;
-    if ((e = compute_units(&cus)) != hipSuccess) return e;
-    const int64_t ids = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
-    if (ids <= 0) return hipSuccess;
-    if (ids > 0x7fffffffLL) return hipErrorInvalidValue;
-    int64_t grid = ids < cus ? ids : cus;
-    grid = grid / 8 * 8;
-    if (grid < 8) grid = 8;
-    kern<<<(unsigned)grid, 512, smem, st>>>(g);
-    return hipGetLastError();
+    constexpr int smem = 4 * 256 * 128 + 20480, tables = 8192;
+    static DeviceOnce once[4];
+    StreamGrid gr;
+    const hipError_t e = stream_grid(g, &gr);
+    if (e != hipSuccess || gr.blocks == 0) return e;
+    if (g.n_tiles > 4)  return launch_stream_as(gemm_stream_gen_kernel<EPI, false, SHARE>, smem, once[0], g, gr.blocks, st);
+    if (gr.parts == 1)  return launch_stream_as(gemm_stream_gen_kernel<EPI, true, SHARE>, smem + tables, once[1], g, gr.blocks, st);
+    if (gr.parts == 2)  return launch_stream_as(gemm_parts_gen_kernel<EPI, SHARE, 2>, smem + tables, once[2], g, gr.blocks, st);
+    return launch_stream_as(gemm_parts_gen_kernel<EPI, SHARE, 4>, smem + tables, once[3], g, gr.blocks, st);
 }
 
-template <int EPI, bool COL_REGS>
-static hipError_t launch_stream_one_impl(const GemmArgs &g, hipStream_t st);
 template <int EPI>
 static hipError_t launch_stream_one(const GemmArgs &g, hipStream_t st)
 {
@@ -1104,29 +1170,17 @@ static hipError_t launch_stream_one(const GemmArgs &g, hipStream_t st)
     // fused output unit 1.58 -> 1.50 ms per launch (1.54 with lane reads in place of the exchange); with the
     // stored output nothing is gained (there the scalar loads already hide under the draining stores), so the
     // storing kernel keeps the scalar loads.
-    if constexpr (EPI == EPI_SCORE) {
-        if (g.n_tiles <= 4) return launch_stream_one_impl<EPI, true>(g, st);
-    }
-    return launch_stream_one_impl<EPI, false>(g, st);
-}
-template <int EPI, bool COL_REGS>
-static hipError_t launch_stream_one_impl(const GemmArgs &g, hipStream_t st)
-{
     constexpr int smem = 5 * 256 * 128;
-    auto kern = gemm_stream_kernel<EPI, COL_REGS>;
-    static DeviceOnce once;
-    hipError_t e = ensure_dynamic_lds((const void *)kern, smem, once);
-    if (e != hipSuccess) return e;
-    int cus = 0;
-    if ((e = compute_units(&cus)) != hipSuccess) return e;
-    const int64_t ids = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
-    if (ids <= 0) return hipSuccess;
-    if (ids > 0x7fffffffLL) return hipErrorInvalidValue;
-    int64_t grid = ids < cus ? ids : cus;
-    grid = grid / 8 * 8;
-    if (grid < 8) grid = 8;
-    kern<<<(unsigned)grid, 512, smem, st>>>(g);
-    return hipGetLastError();
+    static DeviceOnce once[4];
+    StreamGrid gr;
+    const hipError_t e = stream_grid(g, &gr);
+    if (e != hipSuccess || gr.blocks == 0) return e;
+    if (gr.parts == 2) return launch_stream_as(gemm_parts_kernel<EPI, 2>, smem, once[0], g, gr.blocks, st);
+    if (gr.parts == 4) return launch_stream_as(gemm_parts_kernel<EPI, 4>, smem, once[1], g, gr.blocks, st);
+    if constexpr (EPI == EPI_SCORE) {
+        if (g.n_tiles <= 4) return launch_stream_as(gemm_stream_kernel<EPI, true>, smem, once[2], g, gr.blocks, st);
+    }
+    return launch_stream_as(gemm_stream_kernel<EPI, false>, smem, once[3], g, gr.blocks, st);
 }
 
 template <int AMODE, int EPI>
@@ -1170,7 +1224,8 @@ hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st)
     // generated operand: the streaming kernel needs the bias, the vector area bounds K, two slabs at least,
     // 32-bit row arithmetic and 4-byte DMA sources
     if (g.bias && g.K <= 1024 && g.K >= 128 && g.M < (1LL << 31))
-        return epi == EPI_STORE ? launch_stream_gen<EPI_STORE>(g, st) : launch_stream_gen<EPI_SCORE>(g, st);
+        return epi == EPI_STORE ? (g.xp_runs4 ? launch_stream_gen<EPI_STORE, true>(g, st) : launch_stream_gen<EPI_STORE, false>(g, st))
+                                : (g.xp_runs4 ? launch_stream_gen<EPI_SCORE, true>(g, st) : launch_stream_gen<EPI_SCORE, false>(g, st));
     return epi == EPI_STORE ? launch_big_one<AMODE_GEN, EPI_STORE>(g, st)
                             : launch_big_one<AMODE_GEN, EPI_SCORE>(g, st);
 }

@@ -31,8 +31,8 @@ static constexpr int SEGS = 8;
 // n / C for n < 2^31 on the scalar unit: (n * mul) >> shift with mul = ceil(2^shift / C), shift = 31 + ceil(log2 C)
 struct DivC { uint32_t mul, shift; };
 
-template <int EPI, int ROWS4>
-__global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g, const DivC dc)
+template <int EPI, int ROWS4, int PARTS>                  // PARTS: of the last round's tiles, as in gemm_big.hip
+__device__ __forceinline__ void stream_span_tiles(const GemmArgs &g, const DivC &dc)
 {
     constexpr int BM = 256, BK = 64;
     constexpr int SLAB = BM * 128;
@@ -52,17 +52,22 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
     const unsigned n_tiles = (unsigned)g.n_tiles;
     const unsigned panels = (unsigned)g.m_tiles > xcd ? ((unsigned)g.m_tiles - xcd + 7) / 8 : 0;
     const unsigned n_local = panels * n_tiles;
-    if (l0 >= n_local) return;
-    const unsigned n_my = (n_local - l0 + G8 - 1) / G8;
+    const LastRound last = last_round<PARTS>(n_local, G8, l0);
+    const unsigned n_my = last.n_my;
+    if (n_my == 0) return;
     const unsigned C = (unsigned)g.C, M = (unsigned)g.M;
     auto div_c = [&](unsigned n) { return (unsigned)(((uint64_t)n * dc.mul) >> dc.shift); };
-    auto tile_row0 = [&](unsigned qq) { return (((l0 + qq * G8) / n_tiles) * 8 + xcd) * (unsigned)BM; };
+    // first row of a tile or part, for what is read (a part may lie past the end as a whole)
+    auto tile_row0 = [&](unsigned qq) {
+        const unsigned r = ((last.tile(qq, l0, G8) / n_tiles) * 8 + xcd) * (unsigned)BM;
+        return PARTS > 1 ? min(r + last.row(qq), M - 1) : r;
+    };
 
     // ---- W slabs by DMA
     const unsigned char *w_base;
     uint32_t w_off[4];
     auto set_w = [&](unsigned q) {
-        const unsigned local = l0 + q * G8;
+        const unsigned local = last.tile(q, l0, G8);
         w_base = (const unsigned char *)g.B + (int64_t)(local % n_tiles) * 256 * g.ldb * 2;
         const int ln = opaque_lane();
         const int dma_cc = (ln & 7) ^ ((wave & 1) * 4 + (ln >> 4)), dma_r0 = wave * 8 + (ln >> 3);
@@ -124,20 +129,35 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
         }
     };
 
-    // ---- generation: thread -> k chunk t & 7 of the four adjacent rows 4 (t >> 3) + i
-    const int gcc = t & 7, grow4 = (t >> 3) * 4;
+    // ---- generation: thread -> k chunk t & 7 of the four (of a part: IM = 2 or 1) adjacent rows 4 (t >> 3) + i
+    typedef std::integral_constant<int, 4> full_tag;
+    typedef std::integral_constant<int, 4 / PARTS> part_tag;
+    const int gcc = t & 7;
     int gen_st[4];
+    auto own_rows = [&](auto im_tag) {
+        constexpr int IM = decltype(im_tag)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gen_st[i] = (grow4 + i) * 128 + ((gcc ^ (((grow4 + i) >> 1) & 7)) << 4);
+        for (int i = 0; i < IM; ++i) {
+            const int row = (t >> 3) * IM + i;
+            gen_st[i] = row * 128 + ((gcc ^ ((row >> 1) & 7)) << 4);
+        }
+    };
+    own_rows(full_tag{});
     f32x4 gxp, gxc;
     int seg0 = 0, seg3 = 0, border = 4;                    // byte offsets of the group's scenario terms; rows from `border` on take seg3's
-    auto load_group = [&](unsigned q) {                    // what belongs to the group's rows in tile q
-        const int b = (int)(q & 1);
-        gxp = *(const f32x4 *)(smem + V_XP + b * 2048 + grow4 * 4);
-        gxc = *(const f32x4 *)(smem + V_XP + b * 2048 + 1024 + grow4 * 4);
+    auto load_group = [&](auto im_tag, unsigned q) {       // what belongs to the group's rows in tile q
+        constexpr int IM = decltype(im_tag)::value;
+        const float *px = (const float *)(smem + V_XP + (q & 1) * 2048) + (t >> 3) * IM, *pc = px + 256;
+        if constexpr (IM == 4) {
+            gxp = *(const f32x4 *)px;
+            gxc = *(const f32x4 *)pc;
+        } else {
+#pragma unroll
+            for (int i = 0; i < IM; ++i) { gxp[i] = px[i]; gxc[i] = pc[i]; }
+        }
         if (q > n_my - 1) q = n_my - 1;
         const unsigned m0 = tile_row0(q), c0 = m0 - div_c(m0) * C, left = M - 1 - m0;
-        const unsigned r0 = (unsigned)(opaque_lane() >> 3) * 4 + wave * 32, r3 = r0 + 3;
+        const unsigned r0 = ((unsigned)(opaque_lane() >> 3) + wave * 8) * IM, r3 = r0 + IM - 1;
         const unsigned s0 = seg_of(c0 + (r0 < left ? r0 : left));
         seg0 = (int)s0 * 256;
         if constexpr (ROWS4 == 0) {
@@ -183,35 +203,35 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
     int rd[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) rd[q] = l31 * 128 + ((((q << 1) | half) ^ sw) << 4);
-    const int a_rd = wave_m * 128 * 128;
     const int w_rd = W_BASE + wave_n * 64 * 128;
 
     f32x16 acc[2][4];
     i32x4 fa[2][4], fw[2][2];
-    auto load_frags = [&](int a_slot, int w_slot, int q, int set) {
-        const unsigned char *sa = smem + a_slot * SLAB + a_rd;
+    auto load_frags = [&](auto im_tag, int a_slot, int w_slot, int q, int set) {
+        constexpr int IM = decltype(im_tag)::value;
+        const unsigned char *sa = smem + a_slot * SLAB + wave_m * (IM * 4096);
         const unsigned char *sw_ = smem + w_slot * SLAB + w_rd;
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn) fw[set][jn] = *(const i32x4 *)(sw_ + jn * 4096 + rd[q]);
 #pragma unroll
-        for (int im = 0; im < 4; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
+        for (int im = 0; im < IM; ++im) fa[set][im] = *(const i32x4 *)(sa + im * 4096 + rd[q]);
     };
-    auto mma = [&](int set) {
+    auto mma = [&](auto im_tag, int set) {
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 0; im < 4; ++im)
+            for (int im = 0; im < decltype(im_tag)::value; ++im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     acc[jn][im], 0, 0, 0);
     };
     // A tile's first quarter: the accumulators start at the bias, which waits in those of row block 0 (in their layout,
     // the same for all four row blocks), so block 0 goes last.
-    auto mma_first = [&](int set) {
+    auto mma_first = [&](auto im_tag, int set) {
 #pragma unroll
         for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
-            for (int im = 3; im >= 0; --im)
+            for (int im = decltype(im_tag)::value - 1; im >= 0; --im)
                 acc[jn][im] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                     __builtin_bit_cast(bf16x8, fw[set][jn]), __builtin_bit_cast(bf16x8, fa[set][im]),
                     acc[jn][0], 0, 0, 0);
@@ -247,9 +267,11 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
             }
     };
     auto begin_tile = [&](unsigned q) {
-        tn = (l0 + q * G8) % n_tiles;
+        const unsigned local = last.tile(q, l0, G8);
+        tn = local % n_tiles;
         n0 = (int)tn * 256;
-        m0 = (int64_t)tile_row0(q);
+        m0 = (int64_t)((local / n_tiles) * 8 + xcd) * BM;
+        if constexpr (PARTS > 1) m0 += last.row(q);
     };
 
     // ---- prologue
@@ -268,44 +290,45 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
     __builtin_amdgcn_s_barrier();                          // vectors, scenario terms, column tables and W(0) are there for everybody
     AB_FENCE();
     load_bias();
-    load_group(0);
+    load_group(full_tag{}, 0);
     load_slices(0, 0);
     gen_chunk(0, 0); gen_chunk(0, 1); gen_chunk(0, 2); gen_chunk(0, 3);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();                          // A(0) is complete, slot 0 of the scenario terms is free
     AB_FENCE();
     dma_at(); advance_at();                                // slab 2's
-    load_frags(0, 0, 0, 0);
+    load_frags(full_tag{}, 0, 0, 0, 0);
 
     int a_slot = 0, w_slot = 0;
     unsigned gq = 0;                                       // tile that is being generated
     unsigned q = 0;
     // One slab (kt = its place in the tile); wave priorities as in gemm_stream_gen_kernel.
-    auto slab = [&](auto first_tag, int kt) {
+    auto slab = [&](auto im_tag, auto first_tag, int kt) {
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int IM = decltype(im_tag)::value;
         const int nxt = a_slot ^ 1;                        // retired one slab ago: slab j+1 is generated there
         int gk = kt + 1;                                   // its place in its tile
-        if (gk == KT) { gk = 0; ++gq; load_group(gq); }
+        if (gk == KT) { gk = 0; ++gq; load_group(im_tag, gq); }
         load_slices(nxt, gk);                              // (the rings of A and of the scenario terms run in step)
         AB_FENCE();
         if (wave_m) __builtin_amdgcn_s_setprio(3); else __builtin_amdgcn_s_setprio(0);
-        load_frags(a_slot, w_slot, 1, 1);
+        load_frags(im_tag, a_slot, w_slot, 1, 1);
         gen_chunk(nxt, 0);
-        gen_chunk(nxt, 1);
-        if constexpr (FIRST) mma_first(0); else mma(0);
-        AB_INTERLEAVE_6();
+        if constexpr (IM > 1) gen_chunk(nxt, 1);
+        if constexpr (FIRST) mma_first(im_tag, 0); else mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         __builtin_amdgcn_s_setprio(1);
-        load_frags(a_slot, w_slot, 2, 0);
-        gen_chunk(nxt, 2);
-        mma(1);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 2, 0);
+        if constexpr (IM == 4) gen_chunk(nxt, 2);
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         __builtin_amdgcn_s_setprio(0);
-        load_frags(a_slot, w_slot, 3, 1);
-        gen_chunk(nxt, 3);
-        mma(0);
-        AB_INTERLEAVE_6();
+        load_frags(im_tag, a_slot, w_slot, 3, 1);
+        if constexpr (IM == 4) gen_chunk(nxt, 3);
+        mma(im_tag, 0);
+        if constexpr (IM == 4) AB_INTERLEAVE_6(); else AB_INTERLEAVE_PART(IM, 0);
         AB_FENCE();
         if (!FIRST || q == 0 || KT == 2) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -322,11 +345,11 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
         AB_FENCE();
         __builtin_amdgcn_s_setprio(2);
         const int nw = w_slot ^ 1;
-        load_frags(nxt, nw, 0, 0);
+        load_frags(im_tag, nxt, nw, 0, 0);
         dma_w_rows(w_slot, 0);
         dma_w_rows(w_slot, 2);
-        mma(1);
-        AB_INTERLEAVE_6_V4();
+        mma(im_tag, 1);
+        if constexpr (IM == 4) AB_INTERLEAVE_6_V4(); else AB_INTERLEAVE_PART(IM, 4);
         AB_FENCE();
         dma_at();
         AB_FENCE();
@@ -335,21 +358,22 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
         a_slot = nxt;
         w_slot = nw;
     };
-    while (true) {
-        slab(std::true_type{}, 0);
-        for (int kt = 1; kt < KT; ++kt) slab(std::false_type{}, kt);
+    auto tile = [&](auto im_tag) {
+        constexpr int IM = decltype(im_tag)::value;
+        slab(im_tag, std::true_type{}, 0);
+        for (int kt = 1; kt < KT; ++kt) slab(im_tag, std::false_type{}, kt);
         {
             // ------------------------------------------------------------ epilogue of tile q
             unsigned char *stage = smem + (a_slot ^ 1) * SLAB;            // the A stage retired by the last barrier
-            const bool ragged = m0 + BM > g.M;
+            const bool ragged = m0 + IM * 64 > g.M;
             const int ln = opaque_lane();
             const int half = ln >> 5, l31 = ln & 31, sw = (l31 >> 1) & 7;
             if constexpr (EPI == EPI_STORE) {
                 unsigned char *mine = stage + wave * 4096;
                 const int rrow = ln >> 3, rch = ln & 7;
-                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * 128 + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
+                uint16_t *dst = (uint16_t *)g.out + (m0 + wave_m * (IM * 32) + rrow) * g.ldo + n0 + wave_n * 64 + rch * 8;
 #pragma unroll
-                for (int im = 0; im < 4; ++im) {
+                for (int im = 0; im < IM; ++im) {
 #pragma unroll
                     for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
@@ -374,12 +398,14 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
                     } else {
 #pragma unroll
                         for (int it = 0; it < 4; ++it)
-                            if (m0 + wave_m * 128 + im * 32 + rrow + 8 * it < g.M)
+                            if (m0 + wave_m * (IM * 32) + im * 32 + rrow + 8 * it < g.M)
                                 __builtin_nontemporal_store(o[it], (i32x4 *)(d + (int64_t)(8 * it) * g.ldo));
                     }
                 }
             } else {   // EPI_SCORE: the output unit as a per-lane dot product, reduced over the four column wavefronts
-                float ps[4] = {0.f, 0.f, 0.f, 0.f};
+                float ps[IM];
+#pragma unroll
+                for (int im = 0; im < IM; ++im) ps[im] = 0.f;
 #pragma unroll
                 for (int jn = 0; jn < 2; ++jn)
 #pragma unroll
@@ -388,18 +414,18 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
 #pragma unroll
-                            for (int im = 0; im < 4; ++im)
+                            for (int im = 0; im < IM; ++im)
                                 ps[im] += relu_keep_nan(acc[jn][im][rg * 4 + e]) * w4[e];
                     }
                 float *red = (float *)stage;               // [4 column-waves][256 rows]
 #pragma unroll
-                for (int im = 0; im < 4; ++im) {
+                for (int im = 0; im < IM; ++im) {
                     const float v = ps[im] + __shfl_xor(ps[im], 32, 64);
-                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * 128 + l31 + im * 32, v);
+                    if (half == 0) lds_write4(red + wave_n * BM + wave_m * (IM * 32) + l31 + im * 32, v);
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
-                if (wave < 4) {
+                if (wave < IM) {
                     const int tt = wave * 64 + ln;
                     const float v = (red[tt] + red[BM + tt]) + (red[2 * BM + tt] + red[3 * BM + tt]);
                     if (!ragged) g.partial[(m0 + tt) * g.n_tiles + tn] = v;
@@ -408,8 +434,22 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
             }
             // a ragged tile may have issued fewer stores than the counts assume: drain instead
             if (ragged) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (q + 1 == n_my) break;
-            ++q;
+        }
+    };
+    while (true) {
+        if constexpr (PARTS > 1) {
+            if (q == last.q_part) {                        // (its first slab was generated as a whole tile's)
+                own_rows(part_tag{});
+                load_group(part_tag{}, q);
+                load_frags(part_tag{}, a_slot, w_slot, 0, 0);
+                tile(part_tag{});
+                break;
+            }
+        }
+        tile(full_tag{});
+        if (q + 1 == n_my) break;
+        ++q;
+        {
             begin_tile(q);
             load_bias();                                   // (a fixed table: its reads may return under the wait below)
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -422,25 +462,25 @@ __global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g,
 }
 
 template <int EPI, int ROWS4>
+__global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g, const DivC dc) { stream_span_tiles<EPI, ROWS4, 1>(g, dc); }
+template <int EPI, int ROWS4, int PARTS>
+__global__ __launch_bounds__(512) void gemm_parts_span_kernel(const GemmArgs g, const DivC dc) { stream_span_tiles<EPI, ROWS4, PARTS>(g, dc); }
+
+template <int EPI, int ROWS4>
 static hipError_t launch_span_one(const GemmArgs &g, hipStream_t st)
 {
     constexpr int smem = 4 * 256 * 128 + 2 * 4096 + 2 * SEGS * 256 + 4096 + 8192;
-    auto kern = gemm_stream_span_kernel<EPI, ROWS4>;
-    static DeviceOnce once;
-    hipError_t e = ensure_dynamic_lds((const void *)kern, smem, once);
+    StreamGrid gr;
+    hipError_t e = stream_grid(g, &gr);
+    if (e != hipSuccess || gr.blocks == 0) return e;
+    static DeviceOnce once[3];
+    auto kern = gr.parts == 1 ? gemm_stream_span_kernel<EPI, ROWS4> : gr.parts == 2 ? gemm_parts_span_kernel<EPI, ROWS4, 2> : gemm_parts_span_kernel<EPI, ROWS4, 4>;
+    e = ensure_dynamic_lds((const void *)kern, smem, once[gr.parts >> 1]);
     if (e != hipSuccess) return e;
-    int cus = 0;
-    if ((e = compute_units(&cus)) != hipSuccess) return e;
-    const int64_t ids = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
-    if (ids <= 0) return hipSuccess;
-    if (ids > 0x7fffffffLL) return hipErrorInvalidValue;
-    int64_t grid = ids < cus ? ids : cus;
-    grid = grid / 8 * 8;
-    if (grid < 8) grid = 8;
     DivC dc{0, 31};
     while ((1LL << (dc.shift - 31)) < g.C) ++dc.shift;
     dc.mul = (uint32_t)(((1ull << dc.shift) + (uint32_t)g.C - 1) / (uint32_t)g.C);
-    kern<<<(unsigned)grid, 512, smem, st>>>(g, dc);
+    kern<<<gr.blocks, 512, smem, st>>>(g, dc);
     return hipGetLastError();
 }
 

@@ -66,5 +66,52 @@ __device__ __forceinline__ void lds_write16(void *p, i32x4 v)
 #define AB_INTERLEAVE_6_V4() do { __builtin_amdgcn_sched_group_barrier(0x100, 2, 0); \
                                   AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); \
                                   AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); AB_MFMA_VMEM_PAIR(); AB_MFMA_DS_PAIR(); } while (0)
+// The same for a part of a tile: IM row blocks a wavefront, 2 IM matrix instructions and 2 + IM fragment reads a quarter, REQS DMA
+// requests (4 or IM).
+#define AB_INTERLEAVE_PART(IM, REQS) do { \
+        if constexpr ((REQS) > 0) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0); \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); \
+        if constexpr ((REQS) > 0) __builtin_amdgcn_sched_group_barrier(0x010, ((REQS) + 1) / 2, 0); \
+        __builtin_amdgcn_sched_group_barrier(0x100, (REQS) > 0 ? (IM) : 2, 0); \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); \
+        if constexpr ((REQS) > 1) __builtin_amdgcn_sched_group_barrier(0x010, (REQS) / 2, 0); \
+        if constexpr ((REQS) == 0) __builtin_amdgcn_sched_group_barrier(0x100, (IM), 0); \
+        if constexpr ((IM) > 1) __builtin_amdgcn_sched_group_barrier(0x008, 2 * (IM) - 2, 0); } while (0)
+
+// The last round of a streaming kernel's tiles, per XCD: work-group l0 of G8 takes tiles l0 + q G8, q < n_my.  With PARTS > 1 and
+// a last round of at most G8 / PARTS tiles, those are shared out among PARTS work-groups each (item q_part, rows from row(q) on).
+struct LastRound {
+    unsigned n_my, q_part, part_tile, part_row;
+    __device__ __forceinline__ unsigned tile(unsigned q, unsigned l0, unsigned G8) const { return q == q_part ? part_tile : l0 + q * G8; }
+    __device__ __forceinline__ unsigned row(unsigned q) const { return q == q_part ? part_row : 0; }
+};
+template <int PARTS>
+__device__ __forceinline__ LastRound last_round(unsigned n_local, unsigned G8, unsigned l0)
+{
+    const unsigned rounds = n_local / G8, left = n_local - rounds * G8;
+    LastRound r{rounds + (l0 < left ? 1u : 0u), ~0u, 0, 0};
+    if constexpr (PARTS > 1) {
+        if (left * PARTS <= G8) {
+            const bool mine = l0 < left * PARTS;
+            r = LastRound{rounds + (mine ? 1u : 0u), rounds, rounds * G8 + l0 / PARTS, l0 % PARTS * (256 / PARTS)};
+        }
+    }
+    return r;
+}
+
+// The grid of a streaming launch (a work-group a CU) and into how many parts its last round's tiles go: by the XCD with the most.
+struct StreamGrid { unsigned blocks; int parts; };
+inline hipError_t stream_grid(const GemmArgs &g, StreamGrid *out)
+{
+    int cus = 0;
+    const hipError_t e = compute_units(&cus);
+    if (e != hipSuccess) return e;
+    const int64_t ids = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
+    if (ids > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int64_t most = cus / 8 * 8 < 8 ? 8 : cus / 8 * 8, per_xcd = ids / 8, left = per_xcd % (most / 8);
+    out->parts = left == 0 || g.n_tiles > 4 ? 1 : left * 4 <= most / 8 ? 4 : left * 2 <= most / 8 ? 2 : 1;
+    out->blocks = (unsigned)(ids < most && out->parts == 1 ? ids : most);
+    return hipSuccess;
+}
 
 }  // namespace ab
