@@ -398,26 +398,29 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
     const double es = (double)elem_size(dt);
     bool prep_done = false, term_done = false;
     bool grid_done = false;             // a per-scenario grid's rows: in the first launch if all scenarios are one chunk
-    if (desc->tensor_encoder == 2) {
-        {
+    if (desc->tensor_encoder) {
+        // the encoder, and in its launch, where they fit, the scalars' columns and the layer-1 preparation (step 2); every pass
+        // reports the same stages, so those come empty then
+        const EncoderSide side{stats->scalars, params->W[p.base], params->b[p.base], p.F, p.Fs, p.H[0], w1s, grid, b_term, cfg_vec,
+                               params->W[p.base + p.D], params->b[p.base + p.D], p.H[p.D - 1], w_out_f};
+        if (desc->tensor_encoder == 2) {
             // per scenario and layer: two gate products (256 x 96 and 256 x 128) and the K -> 32 embedding
             TraceScope ts("lstm_encoder", (double)S * desc->n_layers * 2.0 * (256.0 * 224.0 + 32.0 * desc->n_stats), 0, st);
             AB_HIP(launch_lstm_encoder(desc, stats->dyn, params->W[0], params->b[0], params->W[1], params->b[1],
-                                       params->W[2], params->b[2], xs, p.Kp, S, stats->layers_of, st));
-        }
-        TraceScope ts("encode_stats", (double)S * (desc->n_scalars * 4.0 + (p.Kp - desc->enc_hidden[1]) * es), 1, st);
-        AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp,
-                                   desc->enc_hidden[1], 0, st));
-    } else if (desc->tensor_encoder) {
-        {
+                                       params->W[2], params->b[2], xs, p.Kp, S, stats->layers_of, side, &prep_done, st));
+        } else {
             TraceScope ts("tensor_encoder", (double)S * desc->n_layers * 2.0 * (desc->n_stats * 128.0 + 128.0 * 128.0),
                           0, st);
             AB_HIP(launch_tensor_encoder(desc, stats->dyn, params->W[0], params->b[0], params->W[1],
-                                         params->b[1], xs, p.Kp, S, stats->layers_of, st));
+                                         params->b[1], xs, p.Kp, S, stats->layers_of, side, &prep_done, st));
         }
-        TraceScope ts("encode_stats", (double)S * (desc->n_scalars * 4.0 + (p.Kp - desc->enc_hidden[1]) * es), 1, st);
-        AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp,
-                                   desc->enc_hidden[1], 0, st));
+        if (prep_done) {
+            { TraceScope ts("encode_stats", 0.0, 1, st); }
+            { TraceScope ts("prep_layer1", 0.0, 1, st); }
+        } else {
+            TraceScope ts("encode_stats", (double)S * (desc->n_scalars * 4.0 + (p.Kp - desc->enc_hidden[1]) * es), 1, st);
+            AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp, desc->enc_hidden[1], 0, st));
+        }
     } else if (joined_opening(desc, p, S, C, per_scenario)) {
         // few scenarios: transform, preparation (step 2) and scenario term (step 3) in one launch, reported as the product that
         // it is; every pass reports the same stages, so the transform's comes empty

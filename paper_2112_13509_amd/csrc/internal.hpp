@@ -125,11 +125,18 @@ hipError_t launch_score_tiny(int dtype, const ab_model_desc *d, const ab_params 
                              const float *scal, const float *part, const float *cred, int32_t P, int32_t Q,
                              int per_scenario, int64_t S, float *scores, int32_t *best_idx, float *best_score,
                              hipStream_t st);
+// What the encoders' launches take along where *side_done says so: the scalars' columns of the scenario rows (launch_encode_stats
+// without statistics) and the layer-1 preparation (launch_prep_layer1).
+struct EncoderSide {
+    const float *scal;
+    const void *W1; const float *b1; int F, Fs, H1; void *w1s; const ab_grid *grid; float *b_term, *cfg_vec;
+    const void *Wout; const float *b_out; int H_last; float *w_out_f;
+};
 hipError_t launch_lstm_encoder(const ab_model_desc *d, const float *dyn, const void *We, const float *be,
                                const void *W1, const float *b1, const void *W2, const float *b2, void *xs,
-                               int ld, int64_t S, const int32_t *layers_of, hipStream_t st);
+                               int ld, int64_t S, const int32_t *layers_of, const EncoderSide &o, bool *side_done, hipStream_t st);
 hipError_t launch_tensor_encoder(const ab_model_desc *d, const float *dyn, const void *Wa, const float *ba,
                                  const void *Wb, const float *bb, void *xs, int ld,
-                                 int64_t S, const int32_t *layers_of, hipStream_t st);
+                                 int64_t S, const int32_t *layers_of, const EncoderSide &o, bool *side_done, hipStream_t st);
 
 }  // namespace ab

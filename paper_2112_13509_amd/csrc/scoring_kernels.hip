@@ -76,7 +76,7 @@ __device__ __forceinline__ void store_quad(void *xs, int64_t o, const float (&v)
 
 struct QuadSplit { int q4s, q4t; uint32_t magic_q4s, magic_q4t, magic_k; int rpb; };
 
-template <typename T>
+template <typename T, int NT = 256>                        // NT threads
 __device__ __forceinline__ void encode_stats_quad_block(const EncodeArgs &a, const QuadSplit &g, unsigned block)
 {
     __shared__ f32x4 tab[AB_MAX_STATS + AB_MAX_SCALARS];     // statistics first, then the scalars
@@ -91,20 +91,20 @@ __device__ __forceinline__ void encode_stats_quad_block(const EncodeArgs &a, con
 
     // the statistics columns: q4s quads a row, a thread's four loads issued before the first value is used
     const uint32_t n_a = (uint32_t)rows * (uint32_t)g.q4s;
-    for (uint32_t base = 0; base < n_a; base += 1024) {
+    for (uint32_t base = 0; base < n_a; base += 4 * NT) {
         f32x4 x[4];
         uint32_t r[4];
         int col[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint32_t i = base + u * 256 + threadIdx.x;
+            const uint32_t i = base + u * NT + threadIdx.x;
             r[u] = __umulhi(i, g.magic_q4s);
             col[u] = (int)(i - r[u] * (uint32_t)g.q4s) * 4;
             if (i < n_a) x[u] = __builtin_nontemporal_load((const f32x4 *)(a.dyn + (row0 + r[u]) * a.n_stat + col[u]));
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (base + u * 256 + threadIdx.x >= n_a) break;
+            if (base + u * NT + threadIdx.x >= n_a) break;
             int k = a.n_stats_per_layer == 1
                         ? 0 : col[u] - (int)__umulhi((uint32_t)col[u], g.magic_k) * a.n_stats_per_layer;
             float v[4];
@@ -119,7 +119,7 @@ __device__ __forceinline__ void encode_stats_quad_block(const EncodeArgs &a, con
 
     // the scalars and the zero padding behind them: q4t quads a row
     const uint32_t n_b = (uint32_t)rows * (uint32_t)g.q4t;
-    for (uint32_t i = threadIdx.x; i < n_b; i += 256) {
+    for (uint32_t i = threadIdx.x; i < n_b; i += NT) {
         const uint32_t r = __umulhi(i, g.magic_q4t);
         const int q0 = (int)(i - r * (uint32_t)g.q4t) * 4;
         float v[4];
@@ -211,6 +211,17 @@ template <typename T>
 __global__ __launch_bounds__(256) void prep_layer1_kernel(const PrepArgs a)
 {
     prep_layer1_item<T>(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
+}
+
+// What an encoder's launch takes along: the scalars' columns of the scenario rows and the layer-1 preparation, both independent of
+// the encoder, in work-groups behind its own (they fill in where the encoder leaves CUs idle, or as it ends).  As two launches of
+// their own / so, us a call, per-tensor encoder, 512-512 x 256 candidates: 200 scenarios 47.3 / 40.8, 512 75.1 / 71.0, 8192 898 / 887.
+struct SideArgs { EncodeArgs e; QuadSplit g; PrepArgs p; unsigned enc_blocks, blocks; };
+template <int NT>
+__device__ __forceinline__ void side_block(const SideArgs &a, unsigned id)
+{
+    if (id < a.enc_blocks) encode_stats_quad_block<bf16_t, NT>(a.e, a.g, id);
+    else prep_layer1_item<bf16_t>(a.p, (int64_t)(id - a.enc_blocks) * NT + threadIdx.x);
 }
 
 // Per-scenario candidate grids: the transformed pair (phi(S_p), phi(S_c)) of every (scenario, candidate) row
@@ -1097,7 +1108,7 @@ __global__ __launch_bounds__(256) void score_single_hidden_kernel(const ScoreD1A
 // ------------------------------------------------------------------------------------------------
 // Shared per-tensor encoder (Section 3.1 "Meta network architecture": the layer-wise statistics are
 // embedded into a fixed-dimension feature space so that models with different layer counts can be
-// handled).  A work-group takes scenarios blockIdx.x, blockIdx.x + gridDim.x, ... (two work-groups per CU):
+// handled).  A work-group takes scenarios blockIdx.x, blockIdx.x + grid, ... (two work-groups per CU):
 //   e[l] = relu(W_b relu(W_a phi(stat[l]) + b_a) + b_b)   (K -> 128 -> 128), pooled[s] = mean_l e[l], written as the
 //   first 128 columns of the scenario row.
 // The four wavefronts work on their own 32-tensor blocks without meeting, each block's raw statistics fetched while the
@@ -1121,8 +1132,12 @@ struct TensorEncArgs {
 };
 
 template <int KS>                                          // KS: pairs of statistics (K <= 2 KS); weights and rows are bf16
-__global__ __launch_bounds__(256, 2) void tensor_encoder_kernel(const TensorEncArgs a)
+__global__ __launch_bounds__(256, 2) void tensor_encoder_kernel(const TensorEncArgs a, const SideArgs side, const unsigned grid)
 {
+    if (blockIdx.x >= grid) {
+        side_block<256>(side, blockIdx.x - grid);
+        return;
+    }
     constexpr int H = 128;
     __shared__ __attribute__((aligned(16))) unsigned char wb_s[H * 256];
     __shared__ float red[4][H];
@@ -1174,7 +1189,7 @@ __global__ __launch_bounds__(256, 2) void tensor_encoder_kernel(const TensorEncA
         // the block after this one (of this scenario, or the first of this wavefront in the next scenario)
         int64_t sc_n = sc;
         int Ls_n = Ls, l0_n = l0 + 128;
-        if (l0_n >= Ls) { sc_n = sc + gridDim.x; Ls_n = sc_n < a.S ? layers(sc_n) : 0; l0_n = wave * 32; }
+        if (l0_n >= Ls) { sc_n = sc + grid; Ls_n = sc_n < a.S ? layers(sc_n) : 0; l0_n = wave * 32; }
         float raw_n[KS], x[KS];
         fetch_raw(sc_n, Ls_n, l0_n, raw_n);
         // transformed statistics (zero past the end)
@@ -1244,7 +1259,7 @@ __global__ __launch_bounds__(256, 2) void tensor_encoder_kernel(const TensorEncA
           ((uint16_t *)a.xs)[sc * a.ld + t] = (uint16_t)(pack_bf16x2(pooled, 0.f) & 0xffffu);
       }
       __syncthreads();                                       // `red` may be written again
-      sc += gridDim.x;
+      sc += grid;
       Ls = sc < a.S ? layers(sc) : 0;
       l0 = wave * 32;
       if (!has_block) fetch_raw(sc, Ls, l0, raw);
@@ -1842,8 +1857,12 @@ __device__ __forceinline__ void lstm_layer(const LstmEncArgs &a, LstmLds<G, NG, 
 }
 
 template <int G, int NG, int KQ>
-__global__ __launch_bounds__(512) void lstm_encoder_kernel(const LstmEncArgs a)
+__global__ __launch_bounds__(512) void lstm_encoder_kernel(const LstmEncArgs a, const SideArgs side, const unsigned grid)
 {
+    if (blockIdx.x >= grid) {
+        side_block<512>(side, blockIdx.x - grid);
+        return;
+    }
     __shared__ LstmLds<G, NG, KQ> lds;
     // Of the two wavefronts of a SIMD the one of the second layer has more to do per step (four k steps against three,
     // and the next step's embedding) and, being the younger one, would be served last: it gets the higher priority.
@@ -1857,37 +1876,59 @@ __global__ __launch_bounds__(512) void lstm_encoder_kernel(const LstmEncArgs a)
 // and 1.49 us with 4, 8, 16 and 32 of them.  A call of 200 steps, us, with 4 / 8 / 16 / 32 a work-group: 16 scenarios 125 / 140 / 186 /
 // 325, 1024 153 / 167 / 213 / 353, 2048 287 / 196 / 242 / 380, 4096 557 / 374 / 298 / 436.  Beyond 16 a CU: 32.
 template <int KQ>
-static hipError_t launch_lstm(const LstmEncArgs &a, hipStream_t st)
+static hipError_t launch_lstm(const LstmEncArgs &a, const SideArgs &side, hipStream_t st)
 {
     int cus = 0;
     const hipError_t e = compute_units(&cus);
     if (e != hipSuccess) return e;
-    auto blocks = [&](int r) { return (unsigned)((a.S + r - 1) / r); };
-    if (a.S <= 4 * (int64_t)cus)       lstm_encoder_kernel<4, 1, KQ><<<blocks(4), 512, 0, st>>>(a);
-    else if (a.S <= 8 * (int64_t)cus)  lstm_encoder_kernel<8, 1, KQ><<<blocks(8), 512, 0, st>>>(a);
-    else if (a.S <= 16 * (int64_t)cus) lstm_encoder_kernel<16, 1, KQ><<<blocks(16), 512, 0, st>>>(a);
-    else if ((a.S + 31) / 32 > 0x7fffffffLL) return hipErrorInvalidValue;
-    else                               lstm_encoder_kernel<16, 2, KQ><<<blocks(32), 512, 0, st>>>(a);
+    const int r = a.S <= 4 * (int64_t)cus ? 4 : a.S <= 8 * (int64_t)cus ? 8 : a.S <= 16 * (int64_t)cus ? 16 : 32;
+    const int64_t grid = (a.S + r - 1) / r;
+    if (grid + side.blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    auto launch = [&](auto kern) { kern<<<(unsigned)grid + side.blocks, 512, 0, st>>>(a, side, (unsigned)grid); };
+    if (r == 4)       launch(lstm_encoder_kernel<4, 1, KQ>);
+    else if (r == 8)  launch(lstm_encoder_kernel<8, 1, KQ>);
+    else if (r == 16) launch(lstm_encoder_kernel<16, 1, KQ>);
+    else              launch(lstm_encoder_kernel<16, 2, KQ>);
     return hipGetLastError();
+}
+
+// The work beside an encoder, for work-groups of `threads`; none, and o.done false, where the scalars' layout needs the general
+// transform or the candidate table is large (its blocks run slower beside an encoder's, of which few fit a CU).
+static SideArgs encoder_side(const ab_model_desc *d, const float *dyn, void *xs, int ld, int64_t S, const EncoderSide &o, int threads, bool *done)
+{
+    SideArgs a;
+    memset(&a, 0, sizeof(a));
+    fill_encode_args(a.e, d, dyn, o.scal, xs, S, ld, d->enc_hidden[1], 0);
+    *done = quad_split(AB_BF16, d, a.e, a.g) && !(o.b_term && (int64_t)o.grid->P * o.grid->Q * o.H1 > 1 << 19);
+    if (!*done) return a;
+    const int64_t n = fill_prep_args(a.p, d, o.W1, o.b1, o.F, o.Fs, o.H1, ld, o.w1s, o.grid, o.b_term, o.cfg_vec, o.Wout, o.b_out, o.H_last, o.w_out_f);
+    const int64_t enc_blocks = (S + a.g.rpb - 1) / a.g.rpb, blocks = enc_blocks + (n + threads - 1) / threads;
+    if (blocks > 0x3fffffffLL) { *done = false; return a; }
+    a.enc_blocks = (unsigned)enc_blocks;
+    a.blocks = (unsigned)blocks;
+    return a;
 }
 
 hipError_t launch_lstm_encoder(const ab_model_desc *d, const float *dyn, const void *We, const float *be,
                                const void *W1, const float *b1, const void *W2, const float *b2, void *xs,
-                               int ld, int64_t S, const int32_t *layers_of, hipStream_t st)
+                               int ld, int64_t S, const int32_t *layers_of, const EncoderSide &o, bool *side_done, hipStream_t st)
 {
+    *side_done = false;
     if (S == 0) return hipSuccess;
     LstmEncArgs a;
     a.layers_of = layers_of;
     a.dyn = dyn; a.L = d->n_layers; a.K = d->n_stats; a.S = S;
     a.We = We; a.be = be; a.W1 = W1; a.b1 = b1; a.W2 = W2; a.b2 = b2; a.xs = xs; a.ld = ld;
     for (int i = 0; i < AB_MAX_ENCODER_STATS; ++i) a.enc_stat[i] = d->enc_stat[i];
-    return a.K <= 4 ? launch_lstm<1>(a, st) : launch_lstm<2>(a, st);
+    const SideArgs side = encoder_side(d, dyn, xs, ld, S, o, 512, side_done);
+    return a.K <= 4 ? launch_lstm<1>(a, side, st) : launch_lstm<2>(a, side, st);
 }
 
 hipError_t launch_tensor_encoder(const ab_model_desc *d, const float *dyn, const void *Wa, const float *ba,
                                  const void *Wb, const float *bb, void *xs, int ld,
-                                 int64_t S, const int32_t *layers_of, hipStream_t st)
+                                 int64_t S, const int32_t *layers_of, const EncoderSide &o, bool *side_done, hipStream_t st)
 {
+    *side_done = false;
     if (S == 0) return hipSuccess;
     TensorEncArgs a;
     a.layers_of = layers_of;
@@ -1897,10 +1938,10 @@ hipError_t launch_tensor_encoder(const ab_model_desc *d, const float *dyn, const
     int cus = 0;
     hipError_t e;
     if ((e = compute_units(&cus)) != hipSuccess) return e;
-    const int64_t grid = S < 2 * (int64_t)cus ? S : 2 * (int64_t)cus;      // two work-groups a CU (their registers)
-    const unsigned blocks = (unsigned)grid;
-    if (a.K <= 4) tensor_encoder_kernel<2><<<blocks, 256, 0, st>>>(a);
-    else          tensor_encoder_kernel<4><<<blocks, 256, 0, st>>>(a);
+    const unsigned grid = (unsigned)(S < 2 * (int64_t)cus ? S : 2 * (int64_t)cus);      // two work-groups a CU (their registers)
+    const SideArgs side = encoder_side(d, dyn, xs, ld, S, o, 256, side_done);
+    if (a.K <= 4) tensor_encoder_kernel<2><<<grid + side.blocks, 256, 0, st>>>(a, side, grid);
+    else          tensor_encoder_kernel<4><<<grid + side.blocks, 256, 0, st>>>(a, side, grid);
     return hipGetLastError();
 }
 
