@@ -1129,14 +1129,14 @@ __device__ __forceinline__ void stream_gen_tiles(const GemmArgs &g)
 }
 
 template <int EPI, bool COL_REGS, bool SHARE>
-__global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g) { stream_gen_tiles<EPI, COL_REGS, SHARE, 1>(g); }
+__global__ __launch_bounds__(512) void gemm_stream_gen_kernel(const GemmArgs g) { touch_arguments<sizeof(GemmArgs)>(); stream_gen_tiles<EPI, COL_REGS, SHARE, 1>(g); }
 template <int EPI, bool COL_REGS>
-__global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g) { stream_tiles<EPI, COL_REGS, 1>(g); }
+__global__ __launch_bounds__(512) void gemm_stream_kernel(const GemmArgs g) { touch_arguments<sizeof(GemmArgs)>(); stream_tiles<EPI, COL_REGS, 1>(g); }
 // those whose last round's tiles go in parts
 template <int EPI, bool SHARE, int PARTS>
-__global__ __launch_bounds__(512) void gemm_parts_gen_kernel(const GemmArgs g) { stream_gen_tiles<EPI, true, SHARE, PARTS>(g); }
+__global__ __launch_bounds__(512) void gemm_parts_gen_kernel(const GemmArgs g) { touch_arguments<sizeof(GemmArgs)>(); stream_gen_tiles<EPI, true, SHARE, PARTS>(g); }
 template <int EPI, int PARTS>
-__global__ __launch_bounds__(512) void gemm_parts_kernel(const GemmArgs g) { stream_tiles<EPI, EPI == EPI_SCORE, PARTS>(g); }
+__global__ __launch_bounds__(512) void gemm_parts_kernel(const GemmArgs g) { touch_arguments<sizeof(GemmArgs)>(); stream_tiles<EPI, EPI == EPI_SCORE, PARTS>(g); }
 
 static hipError_t launch_stream_as(void (*kern)(GemmArgs), int smem, DeviceOnce &once, const GemmArgs &g, unsigned blocks, hipStream_t st)
 {

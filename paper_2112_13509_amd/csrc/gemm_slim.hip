@@ -43,6 +43,7 @@ __global__ __launch_bounds__(256) void gemm_slim_kernel(const GemmArgs g, int st
 {
     typedef SlimShape<T, GEN> Z;
     constexpr int ES = sizeof(T), BK = Z::BK;
+    touch_arguments<sizeof(GemmArgs) + 4>();
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, l31 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);

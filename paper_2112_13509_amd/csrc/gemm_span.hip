@@ -462,9 +462,9 @@ __device__ __forceinline__ void stream_span_tiles(const GemmArgs &g, const DivC 
 }
 
 template <int EPI, int ROWS4>
-__global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g, const DivC dc) { stream_span_tiles<EPI, ROWS4, 1>(g, dc); }
+__global__ __launch_bounds__(512) void gemm_stream_span_kernel(const GemmArgs g, const DivC dc) { touch_arguments<sizeof(GemmArgs) + sizeof(DivC)>(); stream_span_tiles<EPI, ROWS4, 1>(g, dc); }
 template <int EPI, int ROWS4, int PARTS>
-__global__ __launch_bounds__(512) void gemm_parts_span_kernel(const GemmArgs g, const DivC dc) { stream_span_tiles<EPI, ROWS4, PARTS>(g, dc); }
+__global__ __launch_bounds__(512) void gemm_parts_span_kernel(const GemmArgs g, const DivC dc) { touch_arguments<sizeof(GemmArgs) + sizeof(DivC)>(); stream_span_tiles<EPI, ROWS4, PARTS>(g, dc); }
 
 template <int EPI, int ROWS4>
 static hipError_t launch_span_one(const GemmArgs &g, hipStream_t st)

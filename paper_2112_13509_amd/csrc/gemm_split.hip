@@ -55,6 +55,7 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3])
 template <int AMODE, int EPI, int BN>
 __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
 {
+    touch_arguments<sizeof(GemmArgs)>();
     constexpr int BM = 128, BK = 16, JN = BN / 64;
     constexpr int WE = BN / 16;                            // weights a thread splits per slab (8 or 4)
     constexpr int A_PLANE = BM * 16, W_PLANE = BN * 16;    // one part, one half of the slab's k

@@ -480,6 +480,7 @@ struct OutputVArgs { const float *h_last; const float *a_term, *wp, *wc, *xp_sel
 template <typename T>
 __global__ __launch_bounds__(256) void output_v_kernel(const OutputVArgs a)
 {
+    touch_arguments<sizeof(OutputVArgs)>();
     const int lane = threadIdx.x & 63;
     const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (s >= a.S) return;
@@ -593,6 +594,7 @@ struct FinishArgs {
 template <bool EIGHTS, bool PAIR>
 __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
 {
+    touch_arguments<sizeof(FinishArgs)>();
     const int64_t s = blockIdx.x;
     const float *p = a.partial + s * a.row_stride * a.nt;
     const float b = a.b_out ? a.b_out[0] : 0.f;
@@ -659,6 +661,7 @@ __global__ __launch_bounds__(256) void finish_select_kernel(const FinishArgs a)
 template <int NT>
 __global__ __launch_bounds__(256) void finish_select_wave_kernel(const FinishArgs a, int64_t S)
 {
+    touch_arguments<sizeof(FinishArgs)>();
     const int lane = threadIdx.x & 63;
     const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (s >= S) return;

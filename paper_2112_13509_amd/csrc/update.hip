@@ -762,6 +762,7 @@ __device__ __forceinline__ void adam_elems(const AdamArgs &a, const AdamArgs::Tn
 template <typename T, bool MANY>
 __global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a)
 {
+    touch_arguments<sizeof(AdamArgs)>();
     const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;       // one thread per group of tn.vw elements
     if (gid >= a.total) return;
     int j = 0;

@@ -98,15 +98,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
     const int t = threadIdx.x, lane = t & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t row0 = (int64_t)blockIdx.x * R;
-    // the arguments' cache lines, all requested at once (each would be a miss of its own at its first use)
-    {
-        typedef __attribute__((address_space(4))) const uint32_t karg;
-        karg *ka = (karg *)__builtin_amdgcn_kernarg_segment_ptr();
-        uint32_t sink = 0;
-#pragma unroll
-        for (int i = 0; i < (int)sizeof(RowsArgs); i += 64) sink ^= ka[i / 4];
-        asm volatile("" ::"s"(sink));
-    }
+    touch_arguments<sizeof(RowsArgs)>();
     const int D = a.D, k0 = a.k0, n_out = a.n_out;
     unsigned char *ring = smem + wave * (NU * UNIT);
     auto buf = [&](int k) { return smem + (k & 1 ? a.o_odd : a.o_even); };         // holds h_k, then delta_k (x: k = -1)
@@ -614,6 +606,7 @@ __device__ __forceinline__ void output_gradient(const GradsArgs &a, unsigned id,
 template <typename T, int W>
 __global__ __launch_bounds__(256, W == 128 ? 2 : 3) void update_grads_kernel(const GradsArgs a)
 {
+    touch_arguments<sizeof(GradsArgs)>();
     constexpr int ES = sizeof(T), ROWB = W * ES, BK = 8192 / ROWB, ST = W == 128 ? 4 : 3, STAGE = 16384, MB = W / 64;
     __shared__ __attribute__((aligned(16))) unsigned char smem[ST * STAGE];
     const int t = threadIdx.x, lane = t & 63;
@@ -939,15 +932,7 @@ __global__ __launch_bounds__(512) void update_step_kernel(const StepArgs a)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, l31 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    // the arguments' cache lines, all requested at once (each would be a miss of its own at its first use)
-    {
-        typedef __attribute__((address_space(4))) const uint32_t karg;
-        karg *ka = (karg *)__builtin_amdgcn_kernarg_segment_ptr();
-        uint32_t sink = 0;
-#pragma unroll
-        for (int i = 0; i < (int)sizeof(StepArgs); i += 64) sink ^= ka[i / 4];
-        asm volatile("" ::"s"(sink));
-    }
+    touch_arguments<sizeof(StepArgs)>();
     const AdamRates rt{a.lr, a.beta1, a.beta2, a.eps, a.scal[0], a.scal[1]};
     unsigned id = blockIdx.x;
     if (id < a.n_out_blocks) {
