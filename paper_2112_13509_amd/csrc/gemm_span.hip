@@ -237,22 +237,17 @@ __device__ __forceinline__ void stream_span_tiles(const GemmArgs &g, const DivC 
                     acc[jn][0], 0, 0, 0);
     };
 
-    // bias and output weights of all columns -> LDS, once, before any transfer is in flight
+    // bias and output weights of all columns -> LDS, once, by DMA in front of everything else
     int64_t m0 = 0;
     int n0 = 0;
     unsigned tn = 0;
     {
-        const float *src = t < 256 ? g.bias : g.w_out;
-        const bool mine = t < 256 || EPI == EPI_SCORE;
-        float tv[4] = {0.f, 0.f, 0.f, 0.f};
+        const int ln = opaque_lane();
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
-            if (mine && (unsigned)tt < n_tiles) tv[tt] = src[tt * 256 + (t & 255)];
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            asm volatile("" : "+v"(tv[tt]));
-            if (mine) lds_write4(smem + (t < 256 ? V_BIAS : V_WOUT) + (tt * 256 + (t & 255)) * 4, tv[tt]);
+        for (int h = 0; h < 2; ++h) {                       // pieces of 64 columns (past the last one: that one again)
+            const int i = min(wave + 8 * h, (int)n_tiles * 4 - 1);
+            dma4(g.bias + i * 64 + ln, smem + V_BIAS + i * 256);
+            if constexpr (EPI == EPI_SCORE) dma4(g.w_out + i * 64 + ln, smem + V_WOUT + i * 256);
         }
     }
     auto load_bias = [&]() {
