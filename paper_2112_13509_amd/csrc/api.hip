@@ -243,6 +243,47 @@ static bool joined_opening(const ab_model_desc *d, const ScorePlan &p, int64_t S
     return term_in_first_launch(d, S) && !(needs_table(p, per_scenario) && (int64_t)C * p.H[0] > most);
 }
 
+// The weights of the products on gemm_split.hip in their parts (6 bytes each), laid out by the pass's first launch where the workspace has room that
+// the pass does not use by then: the candidate table's, the candidate rows' where the grid is shared, the second pass's.  at[k]: offset
+// in the workspace, or 0; tile[k]: columns of the tiles that they are laid out for.  Whole calls, split in each work-group / so, us: 256-256
+// 38400 rows 43.9 / 41.3, 614400 392 / 366; 128-128 32768 19.2 / 17.5, 2.4 M 435 / 402; 64-64 38400 18.1 / 17.4, 2.4 M 172 / 161.
+// Tiles of 256 columns (eight wavefronts, half the splitting of activations): where the product is the last one (as it stores, the larger
+// work-group is slower: 256 three times, 38400 rows 82.8 -> 93.2 us), its groups allow them and a tile has 16 slabs or more.  128 columns / 256, us: 256-256
+// 139200 rows 104.4 / 101.6, 1.7 M 1010 / 985; 512-512 204800 473 / 455; 128-128-256 139200 112.4 / 113.0, 204800 141.8 / 144.0; 64-256
+// 139200 41.2 / 44.3, 1.7 M 316 / 357.
+struct PartsPlan { size_t at[AB_MAX_HIDDEN]; int tile[AB_MAX_HIDDEN]; };
+static void plan_parts(const ScorePlan &p, int32_t C, int per_scenario, PartsPlan *out)
+{
+    memset(out, 0, sizeof(*out));
+    struct { size_t at, left; } room[3] = {{p.off_bterm, needs_table(p, per_scenario) ? 0 : (size_t)C * p.H[0] * 4},
+                                           {p.off_xrow, per_scenario ? 0 : (size_t)p.chunk_rows * 8}, {p.off_vx, p.total - p.off_vx}};
+    int n = 0;
+    for (int k = 1; k < p.D && n < kMostSplitWeights; ++k) {
+        if (!p.split[k]) continue;
+        const size_t bytes = (size_t)p.H[k] * p.H[k - 1] * 6;               // (a multiple of 256)
+        for (auto &r : room) {
+            if (r.left < bytes) continue;
+            const bool wide = k == p.D - 1 && p.H[k - 1] >= 256 && p.H[k] % 256 == 0 && p.H[k] / 256 % p.split[k] == 0;
+            out->tile[k] = wide ? 256 : p.H[k] % 128 == 0 ? 128 : 64;
+            out->at[k] = r.at;
+            r.at += bytes;
+            r.left -= bytes;
+            ++n;
+            break;
+        }
+    }
+}
+
+// For which column tiles hidden product k's weights lie in their parts (for tests); 0: they do not.
+int scoring_parts_tile(const ab_model_desc *d, int64_t S, int32_t C, int per_scenario, int k)
+{
+    ScorePlan p;
+    PartsPlan parts;
+    if (plan_scoring(d, S, C, &p) != AB_OK) return -1;
+    plan_parts(p, C, per_scenario, &parts);
+    return parts.tile[k];
+}
+
 // Whether a pass opens with the joined launch (for tests).
 bool scoring_joined_opening(const ab_model_desc *d, int64_t S, int32_t C, int per_scenario)
 {
@@ -391,6 +432,13 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
     float *cfg_vec = (float *)(ws + p.off_cfgv);
     float *xp_row = (float *)(ws + p.off_xrow), *xc_row = xp_row + p.chunk_rows;
     const int per_scenario = grid->per_scenario;
+    PartsPlan parts;
+    plan_parts(p, C, per_scenario, &parts);
+    SplitWeightsArgs split_weights{};
+    for (int k = 1; k < p.D; ++k)
+        if (parts.at[k])
+            split_weights.w[split_weights.n++] = SplitWeights{(const float *)params->W[p.base + k], (i32x4 *)(ws + parts.at[k]), p.H[k], p.H[k - 1], parts.tile[k]};
+    const double parts_bytes = 80.0 * split_weights_items(split_weights);
     void *act[2] = {ws + p.off_act0, ws + p.off_act1};
     const int dt = p.dtype;
 
@@ -428,27 +476,27 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
         TraceScope ts("gemm_scenario_term", 2.0 * S * p.H[0] * p.Kp, 0, st);
         AB_HIP(launch_scenario_term(dt, desc, stats->dyn, stats->scalars, S, params->W[p.base], params->b[p.base], p.F, p.Fs, p.H[0], p.Kp,
                                     a_term, grid, b_term, cfg_vec, params->W[p.base + p.D], params->b[p.base + p.D], p.H[p.D - 1],
-                                    w_out_f, per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, st));
+                                    w_out_f, per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, split_weights, st));
         prep_done = term_done = true;
         grid_done = p.chunk_scen >= S;
     } else {
         // flat statistics: transform and layer-1 preparation (step 2) share one launch where the layout allows
         const double prep_bytes = (double)p.H[0] * (p.F * es + p.Kp * es) + (table ? (double)C * p.H[0] * 4.0 : 0.0) +
-                                  (per_scenario && p.chunk_scen >= S ? (double)S * C * 8.0 : 0.0);
+                                  (per_scenario && p.chunk_scen >= S ? (double)S * C * 8.0 : 0.0) + parts_bytes;
         TraceScope ts("encode_and_prep", (double)S * (p.Fs * 4.0 + p.Kp * es) + prep_bytes, 1, st);
         AB_HIP(launch_encode_and_prep(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp, params->W[p.base],
                                       params->b[p.base], p.F, p.Fs, p.H[0], w1s, grid, b_term, cfg_vec,
                                       params->W[p.base + p.D], params->b[p.base + p.D], p.H[p.D - 1], w_out_f,
-                                      per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, &prep_done, st));
+                                      per_scenario && p.chunk_scen >= S ? xp_row : nullptr, xc_row, split_weights, &prep_done, st));
         grid_done = prep_done && p.chunk_scen >= S;
         if (!prep_done) AB_HIP(launch_encode_stats(dt, desc, stats->dyn, stats->scalars, xs, S, p.Kp, 0, 1, st));
     }
     // 2. layer-1 split: packed statistics columns of W1, candidate term B[c], fp32 output weights
     if (!prep_done) {
-        TraceScope ts("prep_layer1", (double)p.H[0] * (p.F * es + p.Kp * es) + (table ? (double)C * p.H[0] * 4.0 : 0.0), 1, st);
+        TraceScope ts("prep_layer1", (double)p.H[0] * (p.F * es + p.Kp * es) + (table ? (double)C * p.H[0] * 4.0 : 0.0) + parts_bytes, 1, st);
         AB_HIP(launch_prep_layer1(dt, desc, params->W[p.base], params->b[p.base], p.F, p.Fs, p.H[0], p.Kp, w1s,
                                   grid, b_term, cfg_vec, params->W[p.base + p.D], params->b[p.base + p.D],
-                                  p.H[p.D - 1], w_out_f, st));
+                                  p.H[p.D - 1], w_out_f, split_weights, st));
     }
     // 3. scenario term A[s] = x_s W1_s^T + b1 (fp32 out)
     if (!term_done) {
@@ -507,8 +555,9 @@ static ab_status score_candidates_in(const ab_model_desc *desc, const ab_params 
                                      : (last ? "gemm_hidden_last" : "gemm_hidden_mid"),
                               2.0 * rows * p.H[k] * p.H[k - 1], 0, st);
                 const int amode = k == 1 ? AMODE_GEN : AMODE_LOAD, epi = last ? EPI_SCORE : EPI_STORE;
+                if (parts.at[k]) g.B_parts = ws + parts.at[k];
                 if (p.split[k])
-                    AB_HIP(launch_gemm_split(amode, epi, g, p.split[k], st));
+                    AB_HIP(launch_gemm_split(amode, epi, g, p.split[k], parts.tile[k], st));
                 else if (p.big[k] == BIG_SPAN)
                     AB_HIP(launch_gemm_span(epi, g, st));
                 else if (p.big[k] && gemm_big_supported(dt, amode, epi, g))

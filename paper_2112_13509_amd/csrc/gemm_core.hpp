@@ -84,6 +84,7 @@ struct GemmArgs {
                                               // ldo_t a multiple of 4 and out_t 16-byte aligned
     const float *w_out; float *partial;       // EPI_SCORE: partial[row*n_tiles + tile_n] = sum_col relu(acc+bias)*w_out
     const void *mask; int64_t ldmask;         // EPI_DRELU: out = acc * (mask[row, col] > 0)
+    const void *B_parts;                      // gemm_split.hip: B in its three parts, laid out for its column tiles (or NULL)
     int32_t n_loop;                           // gemm_split.hip: column tiles that a work-group walks
     int32_t k_splits; int64_t split_stride;   // EPI_SPLITK: fp32 out + split*split_stride, K range split evenly
 };

@@ -10,14 +10,21 @@
 // Relative error against fp64 (2-norm, ReLU'd normal activations, 256 columns): K = 64 / 256 / 1024 4.1e-8 / 7.1e-8 /
 // 1.4e-7, the fp32 instruction 1.06e-7 / 2.1e-7 / 4.1e-7; with one accumulator for all six 1.3e-7 / 2.5e-7 / 4.7e-7.
 //
-// What bounds it: the matrix pipe at a power-limited clock.  Six bf16 instructions of 32 cycles do the work of eight fp32
-// ones of 64 cycles.  4.2 M rows x 256 x 256 with generated operand and fused output unit, in four launches: 1.15 ms a
-// launch on the fp32 instruction (76 % of its peak), 0.63 - 0.66 ms here (0.70 under the profiler); matrix pipe busy 61 % of the
-// cycles, clock 1.95 GHz.
+// What bounds it: the matrix pipe at a power-limited clock, and beside it the vector work of splitting.  Six bf16 instructions of 32
+// cycles do the work of eight fp32 ones of 64 cycles.  4.2 M rows x 256 x 256 with generated operand and fused output unit, in four
+// launches: 1.15 ms a launch on the fp32 instruction (76 % of its peak); the whole call 2.60 ms with the weights split in each
+// work-group, 2.42 with weights that lie split (PARTS), 2.38 so on tiles of 256 columns; six bf16 products of that size 2.23 at the
+// rate of the large bf16 kernels.
 //
 // Shape: a work-group of 256 threads (2 x 2 wavefronts) owns 128 rows and walks its column tiles of BN columns, K in
 // slabs of 16.  A wavefront's 64 x BN/2 outputs take 128 accumulator registers with both sets, so two wavefronts fit a
 // SIMD: two work-groups share a CU, and one's LDS latencies, barriers and epilogues run under the other's matrix work.
+//
+// Split weights (PARTS, where the pass has room for them: split_parts.hpp, made once a pass by its first launch) come by DMA, a slab
+// ahead, in the order in which LDS holds them.  All of a wavefront's requests are waited for at the end of the slab that makes
+// them, which is where the next slab wants them; waiting for the DMA alone would leave the compiler to wait for the activations in
+// the next slab, which it does for everything in flight.  2 x 4 wavefronts on 256 columns split each activation once where 2 x 2 on two
+// tiles of 128 do it twice; on 64 x 256 (1 x 4, two work-groups a CU) the weights' traffic into LDS doubles: 2.53 ms.
 // The vector work of a slab (operand generation, splitting) is spread over its matrix instructions, five between two
 // (1.30 M cycles a launch; in one piece a fifth more).  LDS: two stages; a stage holds, per operand, part and half of the
 // slab's sixteen k, 16 bytes per row one row after the other: a thread writes the eight k it has split and a fragment
@@ -34,30 +41,19 @@
 // of a value below 2^-109 has bits below bf16's smallest (activations of 1e-36: error 2e-5 without this).  1024 scenarios x 4096 candidates, 256-256, every
 // scenario with a NaN or an infinity: 2.53 -> 2.30 ms a call (7.15 with all such tiles computed again, one scenario in 64 like that 2.62).
 #include "stream_util.hpp"
+#include "split_parts.hpp"
 #include <type_traits>
 
 namespace ab {
 
-// The three parts of two fp32 values, packed: p[i] = part i of a (low half) and b.
-__device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3])
-{
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        p[i] = pack_bf16x2(a, b);                          // round to nearest even
-        asm("" : "+v"(p[i]));                              // (one conversion of the pair: not once more for each half)
-        if (i < 2) {
-            a -= __uint_as_float(p[i] << 16);              // exact; what is left after two parts fits bf16
-            b -= __uint_as_float(p[i] & 0xffff0000u);
-        }
-    }
-}
-
-template <int AMODE, int EPI, int BN>
-__global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
+template <int AMODE, int EPI, int WM, int WN, int JN, bool PARTS>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_split_kernel(const GemmArgs g)
 {
     touch_arguments<sizeof(GemmArgs)>();
-    constexpr int BM = 128, BK = 16, JN = BN / 64;
-    constexpr int WE = BN / 16;                            // weights a thread splits per slab (8 or 4)
+    constexpr int NW = WM * WN, NT = 64 * NW, BM = 64 * WM, BN = 32 * JN * WN, BK = 16;
+    constexpr int AE = BM * BK / NT;                       // activations a thread splits per slab (8 or 4)
+    constexpr int WE = PARTS ? 4 : BN * BK / NT;           // weights a thread splits per slab (8 or 4), unless they lie split
+    constexpr int W_REQ = 6 * BN / 64, W_MINE = (W_REQ + NW - 1) / NW;     // a slab's KB of split weights, a wavefront's
     constexpr int A_PLANE = BM * 16, W_PLANE = BN * 16;    // one part, one half of the slab's k
     constexpr int W_BASE = 6 * A_PLANE, STAGE = 6 * (A_PLANE + W_PLANE);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -68,49 +64,62 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
     const int64_t tm = (local / g.n_tiles) * 8 + (blockIdx.x & 7);
     if (tm >= g.m_tiles) return;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int wave_m = wave >> 1, wave_n = wave & 1, half = lane >> 5, l31 = lane & 31;
+    const int wave_m = wave / WN, wave_n = wave % WN, half = lane >> 5, l31 = lane & 31;
     const int64_t m0 = tm * BM;
     const int KT = g.K / BK, n_first = tn * g.n_loop * BN;
 
-    // ---- this thread's share of a slab: eight k of one activation row, WE k of one weight row
-    const int a_row = t & (BM - 1), a_kh = wave >> 1;
-    const int w_row = t & (BN - 1), w_part = BN == 128 ? wave >> 1 : wave;     // which WE of the sixteen k
+    // ---- this thread's share of a slab: AE k of one activation row, WE k of one weight row
+    const int a_row = t & (BM - 1), a_part = wave * 64 / BM;                   // which AE of the sixteen k
+    const int w_row = t & (BN - 1), w_part = wave * 64 / BN;                   // which WE of the sixteen k
     const int64_t gr = min(m0 + a_row, g.M - 1);
     const float *a_src;
     float xp = 0.f, xc = 0.f;
     if constexpr (AMODE == AMODE_LOAD) {
-        a_src = (const float *)g.A + gr * g.lda + a_kh * 8;
+        a_src = (const float *)g.A + gr * g.lda + a_part * AE;
     } else {
         const int64_t s = gr / g.C, x = g.x_per_row ? gr : gr - s * g.C;
-        a_src = g.a_term + s * g.ldt + a_kh * 8;
+        a_src = g.a_term + s * g.ldt + a_part * AE;
         xp = g.xp[x];
         xc = g.xc[x];
     }
     const float *w_src = (const float *)g.B + (int64_t)(n_first + w_row) * g.ldb + w_part * WE;
-    f32x4 ra[2][2], rw[2][WE / 4];                         // two sets: requested a slab ahead
-    f32x8_unaligned rp[2], rc[2];                          // wp, wc of the slab: the same for the whole wavefront
+    f32x4 ra[2][AE / 4], rw[2][WE / 4];                    // two sets: requested a slab ahead (rw, w_src: not with PARTS)
+    typedef float vec_u __attribute__((ext_vector_type(AE), aligned(4)));
+    typedef __attribute__((address_space(4))) vec_u const_vec;
+    vec_u rp[2], rc[2];                                    // wp, wc of the slab: the same for the whole wavefront
+    const unsigned char *w_img = nullptr;                  // PARTS: the slab that is requested next,
+    if constexpr (PARTS) w_img = (const unsigned char *)g.B_parts + (int64_t)(n_first / BN) * KT * (6 * W_PLANE) + lane * 16;
+    int w_left = g.n_loop * KT;                            // slabs from there on
+    auto request_parts = [&](unsigned char *stage) {
+#pragma unroll
+        for (int i = 0; i < W_MINE; ++i) {
+            const int r = W_REQ % NW == 0 || i < W_REQ / NW ? i * NW + wave : i * NW + wave % (W_REQ % NW);   // (a remainder: some twice)
+            dma16<false>(w_img + r * 1024, stage + W_BASE + r * 1024);
+        }
+        if (--w_left > 0) w_img += 6 * W_PLANE;            // (behind the last slab: that one again, not used)
+    };
     int ld_k = 0, ld_n = 0;                                // the slab that is requested next: its k, its column tile
     auto request = [&](int set) {
-        ra[set][0] = *(const f32x4 *)(a_src + ld_k);
-        ra[set][1] = *(const f32x4 *)(a_src + ld_k + 4);
 #pragma unroll
-        for (int i = 0; i < WE / 4; ++i) rw[set][i] = *(const f32x4 *)(w_src + ld_k + 4 * i);
+        for (int i = 0; i < AE / 4; ++i) ra[set][i] = *(const f32x4 *)(a_src + ld_k + 4 * i);
+#pragma unroll
+        for (int i = 0; i < (PARTS ? 0 : WE / 4); ++i) rw[set][i] = *(const f32x4 *)(w_src + ld_k + 4 * i);
     };
     auto request_vectors = [&](int set) {                  // ... and wp, wc by scalar loads; then on to the slab after it
         if constexpr (AMODE != AMODE_LOAD) {
-            rp[set] = *(const const_f32x8 *)(uintptr_t)(g.wp + ld_k + a_kh * 8);
-            rc[set] = *(const const_f32x8 *)(uintptr_t)(g.wc + ld_k + a_kh * 8);
+            rp[set] = *(const const_vec *)(uintptr_t)(g.wp + ld_k + a_part * AE);
+            rc[set] = *(const const_vec *)(uintptr_t)(g.wc + ld_k + a_part * AE);
         }
         ld_k += BK;
         if (ld_k == g.K) {                                 // (behind the last column tile: that one again, not used)
             ld_k = 0;
-            if (++ld_n < g.n_loop) w_src += (int64_t)BN * g.ldb;
+            if (!PARTS && ++ld_n < g.n_loop) w_src += (int64_t)BN * g.ldb;
         }
     };
     uint32_t pa[4][3], pw[4][3];                           // the split pairs of this thread's shares
     auto split_half = [&](int set, int h) {
 #pragma unroll
-        for (int e = 2 * h; e < 2 * h + 2; ++e) {
+        for (int e = AE / 4 * h; e < AE / 4 * (h + 1); ++e) {
             float v[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -119,13 +128,19 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
                     v[i] = relu_keep_nan(fmaf(rc[set][2 * e + i], xc, fmaf(rp[set][2 * e + i], xp, v[i])));
             }
             split3(v[0], v[1], pa[e]);
-            if (e < WE / 2) split3(rw[set][e >> 1][2 * (e & 1)], rw[set][e >> 1][2 * (e & 1) + 1], pw[e]);
+            if (!PARTS && e < WE / 2) split3(rw[set][e >> 1][2 * (e & 1)], rw[set][e >> 1][2 * (e & 1) + 1], pw[e]);
         }
     };
     auto write_parts = [&](unsigned char *stage) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            *(i32x4 *)(stage + (i * 2 + a_kh) * A_PLANE + a_row * 16) = i32x4{(int)pa[0][i], (int)pa[1][i], (int)pa[2][i], (int)pa[3][i]};
+            if constexpr (PARTS && AE == 8)
+                lds_write16(stage + (i * 2 + a_part) * A_PLANE + a_row * 16, i32x4{(int)pa[0][i], (int)pa[1][i], (int)pa[2][i], (int)pa[3][i]});
+            else if constexpr (PARTS)
+                lds_write8(stage + (i * 2 + (a_part >> 1)) * A_PLANE + a_row * 16 + (a_part & 1) * 8, uint2{pa[0][i], pa[1][i]});
+            else
+                *(i32x4 *)(stage + (i * 2 + a_part) * A_PLANE + a_row * 16) = i32x4{(int)pa[0][i], (int)pa[1][i], (int)pa[2][i], (int)pa[3][i]};
+            if constexpr (PARTS) continue;
             if constexpr (WE == 8)
                 *(i32x4 *)(stage + W_BASE + (i * 2 + w_part) * W_PLANE + w_row * 16) = i32x4{(int)pw[0][i], (int)pw[1][i], (int)pw[2][i], (int)pw[3][i]};
             else
@@ -134,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
     };
 
     const int a_rd = half * A_PLANE + (wave_m * 64 + l31) * 16;
-    const int w_rd = W_BASE + half * W_PLANE + (wave_n * (BN / 2) + l31) * 16;
+    const int w_rd = W_BASE + half * W_PLANE + (wave_n * (32 * JN) + l31) * 16;
     f32x16 big[JN][2], small[JN][2];
     float row_sum[2] = {0.f, 0.f};                         // EPI_SCORE: over this wavefront's columns of all column tiles
 
@@ -234,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
         }
     };
     auto epilogue = [&](int n0) {
-        const int nw = n0 + wave_n * (BN / 2);
+        const int nw = n0 + wave_n * (32 * JN);
         float worst[2] = {0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < JN; ++j)
@@ -253,6 +268,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
         emit(nw);
     };
 
+    if constexpr (PARTS) request_parts(smem);
     request(0);
     request_vectors(0);
     request(1);
@@ -260,7 +276,14 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
     split_half(0, 0);
     split_half(0, 1);
     write_parts(smem);
-    __syncthreads();
+    if constexpr (PARTS) {
+        AB_FENCE();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x70);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        AB_FENCE();
+    } else __syncthreads();
     auto slab = [&](auto first_tag, int par) {             // slab j, par = j & 1; a column tile's first one starts the sums
         constexpr bool FIRST = decltype(first_tag)::value;
         const unsigned char *stage = smem + par * STAGE;
@@ -280,6 +303,8 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
         const std::integral_constant<bool, FIRST> first{};
         const std::false_type on{};
         AB_FENCE();
+        if constexpr (PARTS) request_parts(next);          // slab j + 1
+        AB_FENCE();
         request(par);                                      // slab j + 2
         AB_FENCE();
 #pragma unroll
@@ -290,10 +315,11 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
             for (int i = 0; i < JN; ++i) fw[p][i] = *(const bf16x8 *)(stage + w_rd + p * 2 * W_PLANE + i * 512);
         }
         // the vector work goes into the shadows of the matrix instructions
+        constexpr int VPM = PARTS ? (AE == 8 ? 3 : 2) : 5;
         auto interleave = [&]() {
 #pragma unroll
             for (int i = 0; i < 6 * JN; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             }
         };
@@ -313,7 +339,11 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
         interleave();
         AB_FENCE();
         if constexpr (AMODE != AMODE_LOAD) asm volatile("" ::"s"(rp[par]), "s"(rc[par]));
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (PARTS) {                             // all but slab j + 2's activations
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0x70);
+            asm volatile("" ::: "memory");
+        } else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         AB_FENCE();
     };
@@ -332,36 +362,51 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmArgs g)
             if (half == 0) red[wave_n * BM + wave_m * 64 + i * 32 + l31] = v;
         }
         __syncthreads();
-        if (t < BM && m0 + t < g.M) g.partial[(m0 + t) * g.n_tiles + tn] = red[t] + red[BM + t];
+        if (t < BM && m0 + t < g.M) {
+            float sum = red[t];
+#pragma unroll
+            for (int w = 1; w < WN; ++w) sum += red[w * BM + t];
+            g.partial[(m0 + t) * g.n_tiles + tn] = sum;
+        }
     }
 }
 
-template <int AMODE, int EPI, int BN>
+template <int AMODE, int EPI, int WM, int WN, int JN, bool PARTS>
 static hipError_t launch_one(const GemmArgs &g, hipStream_t st)
 {
-    constexpr int smem = 2 * 6 * (128 + BN) * 16;
+    constexpr int smem = 2 * 6 * (64 * WM + 32 * JN * WN) * 16;
     const int64_t blocks = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    gemm_split_kernel<AMODE, EPI, BN><<<(unsigned)blocks, 256, smem, st>>>(g);
+    auto kern = gemm_split_kernel<AMODE, EPI, WM, WN, JN, PARTS>;
+    static DeviceOnce once;
+    if (smem > 64 * 1024) { const hipError_t e = ensure_dynamic_lds((const void *)kern, smem, once); if (e != hipSuccess) return e; }
+    kern<<<(unsigned)blocks, 64 * WM * WN, smem, st>>>(g);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, hipStream_t st)
+template <int WM, int WN, int JN, bool PARTS>
+static hipError_t launch_shape(int amode, int epi, GemmArgs &g, int n_groups, hipStream_t st)
 {
-    const int bn = g.N % 128 == 0 ? 128 : 64;
-    if (g.M <= 0) return hipSuccess;
-    if (g.N % bn != 0 || g.K <= 0 || g.K % 32 != 0 || !g.bias || g.N / bn % n_groups != 0) return hipErrorInvalidValue;
-    g.m_tiles = (g.M + 127) / 128;
+    constexpr int bn = 32 * JN * WN;
+    if (g.N % bn != 0 || g.N / bn % n_groups != 0) return hipErrorInvalidValue;
+    g.m_tiles = (g.M + 64 * WM - 1) / (64 * WM);
     g.n_tiles = n_groups;
     g.n_loop = g.N / bn / n_groups;
-    if (bn == 128) {
-        if (amode == AMODE_LOAD)
-            return epi == EPI_STORE ? launch_one<AMODE_LOAD, EPI_STORE, 128>(g, st) : launch_one<AMODE_LOAD, EPI_SCORE, 128>(g, st);
-        return epi == EPI_STORE ? launch_one<AMODE_GENV, EPI_STORE, 128>(g, st) : launch_one<AMODE_GENV, EPI_SCORE, 128>(g, st);
-    }
-    if (amode == AMODE_LOAD)
-        return epi == EPI_STORE ? launch_one<AMODE_LOAD, EPI_STORE, 64>(g, st) : launch_one<AMODE_LOAD, EPI_SCORE, 64>(g, st);
-    return epi == EPI_STORE ? launch_one<AMODE_GENV, EPI_STORE, 64>(g, st) : launch_one<AMODE_GENV, EPI_SCORE, 64>(g, st);
+    if constexpr (WM * WN == 4) {
+        if (epi == EPI_STORE)
+            return amode == AMODE_LOAD ? launch_one<AMODE_LOAD, EPI_STORE, WM, WN, JN, PARTS>(g, st) : launch_one<AMODE_GENV, EPI_STORE, WM, WN, JN, PARTS>(g, st);
+    } else if (epi == EPI_STORE) return hipErrorInvalidValue;
+    return amode == AMODE_LOAD ? launch_one<AMODE_LOAD, EPI_SCORE, WM, WN, JN, PARTS>(g, st) : launch_one<AMODE_GENV, EPI_SCORE, WM, WN, JN, PARTS>(g, st);
+}
+
+hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, int tile, hipStream_t st)
+{
+    if (g.M <= 0) return hipSuccess;
+    if (g.N % 64 != 0 || g.K <= 0 || g.K % 32 != 0 || !g.bias) return hipErrorInvalidValue;
+    if (!g.B_parts)
+        return g.N % 128 == 0 ? launch_shape<2, 2, 2, false>(amode, epi, g, n_groups, st) : launch_shape<2, 2, 1, false>(amode, epi, g, n_groups, st);
+    return tile == 256 ? launch_shape<2, 4, 2, true>(amode, epi, g, n_groups, st)
+         : tile == 128 ? launch_shape<2, 2, 2, true>(amode, epi, g, n_groups, st) : launch_shape<2, 2, 1, true>(amode, epi, g, n_groups, st);
 }
 
 }  // namespace ab

@@ -5,6 +5,7 @@
 #include <atomic>
 #include "../../include/autobyte.h"
 #include "gemm_core.hpp"
+#include "split_parts.hpp"
 
 namespace ab {
 
@@ -70,7 +71,8 @@ hipError_t launch_gemm_slim(int dtype, int amode, int epi, const GemmArgs &g, hi
 
 // fp32 products on the bf16 matrix cores (gemm_split.hip): EPI_STORE (with ReLU) or EPI_SCORE, with a bias; the column tiles
 // are shared out among `n_groups` work-groups a row panel, which is also the row stride of the partial sums.
-hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, hipStream_t st);
+// g.B_parts: the weights already in their parts, for column tiles of `tile` (256: EPI_SCORE only).
+hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, int tile, hipStream_t st);
 
 // The 256x256 bf16 kernel (gemm_big.hip): EPI_STORE (bf16 out) or EPI_SCORE, AMODE_LOAD or AMODE_GEN.
 bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g);
@@ -89,17 +91,17 @@ hipError_t launch_encode_stats(int dtype, const ab_model_desc *d, const float *d
                                void *xs, int64_t S, int ld, int col0, int with_stats, hipStream_t st);
 hipError_t launch_prep_layer1(int dtype, const ab_model_desc *d, const void *W1, const float *b1, int F, int Fs,
                               int H1, int ld, void *w1s, const ab_grid *grid, float *b_term, float *cfg_vec,
-                              const void *Wout, const float *b_out, int H_last, float *w_out_f, hipStream_t st);
+                              const void *Wout, const float *b_out, int H_last, float *w_out_f, SplitWeightsArgs parts, hipStream_t st);
 hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, void *xs,
                                   int64_t S, int ld, const void *W1, const float *b1, int F, int Fs, int H1, void *w1s,
                                   const ab_grid *grid, float *b_term, float *cfg_vec, const void *Wout,
                                   const float *b_out, int H_last, float *w_out_f, float *xp_row, float *xc_row,
-                                  bool *done, hipStream_t st);     // xp_row: also the rows of a per-scenario grid
+                                  SplitWeightsArgs parts, bool *done, hipStream_t st);     // xp_row: also the rows of a per-scenario grid
 // Transform, layer-1 preparation and the scenario term's product in one launch, for few scenarios.
 hipError_t launch_scenario_term(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, int64_t S, const void *W1,
                                 const float *b1, int F, int Fs, int H1, int Kp, float *a_term, const ab_grid *grid, float *b_term,
                                 float *cfg_vec, const void *Wout, const float *b_out, int H_last, float *w_out_f, float *xp_row,
-                                float *xc_row, hipStream_t st);
+                                float *xc_row, SplitWeightsArgs parts, hipStream_t st);
 // Where the chosen candidate's transformed pair goes, and the grid that it comes from.
 struct ChosenArgs { const float *part, *cred; int32_t P, Q, per_scenario; ab_enc enc_part, enc_cred; float *xp_sel, *xc_sel; };
 hipError_t launch_finish_select(const float *partial, int nt, int64_t row_stride, const float *b_out,

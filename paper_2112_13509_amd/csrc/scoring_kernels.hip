@@ -207,9 +207,27 @@ __device__ __forceinline__ void prep_layer1_item(const PrepArgs &a, int64_t gid)
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void prep_layer1_kernel(const PrepArgs a)
+// The fp32 preparation also lays out the hidden weights in their parts for gemm_split.hip, in the work-groups from parts.from on, the last.
+struct NoParts {};
+template <typename T> using PartsOf = std::conditional_t<sizeof(T) == 4, SplitWeightsArgs, NoParts>;
+template <int NT> __device__ __forceinline__ bool parts_block(const SplitWeightsArgs &a)
 {
+    if (blockIdx.x < a.from) return false;
+    split_weights_item(a, (int64_t)(blockIdx.x - a.from) * NT + threadIdx.x);
+    return true;
+}
+template <int NT> __device__ __forceinline__ bool parts_block(const NoParts &) { return false; }
+template <typename T> static PartsOf<T> parts_of(SplitWeightsArgs a, int64_t from)
+{
+    a.from = (uint32_t)from;
+    if constexpr (sizeof(T) == 4) return a;
+    else return NoParts{};
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void prep_layer1_kernel(const PrepArgs a, const PartsOf<T> parts)
+{
+    if (parts_block<256>(parts)) return;
     prep_layer1_item<T>(a, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
@@ -245,11 +263,11 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const GridRowsArgs a) { 
 // 4.6 us), where all scenarios are one chunk.
 template <typename T>
 __global__ __launch_bounds__(256) void encode_and_prep_kernel(const EncodeArgs a, const QuadSplit g, const PrepArgs p,
-                                                              const GridRowsArgs r, unsigned enc_blocks, unsigned grid_from)
+                                                              const GridRowsArgs r, unsigned enc_blocks, unsigned grid_from, const PartsOf<T> parts)
 {
     if (blockIdx.x < enc_blocks) encode_stats_quad_block<T>(a, g, blockIdx.x);
     else if (blockIdx.x < grid_from) prep_layer1_item<T>(p, (int64_t)(blockIdx.x - enc_blocks) * 256 + threadIdx.x);
-    else grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 256 + threadIdx.x);
+    else if (!parts_block<256>(parts)) grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 256 + threadIdx.x);
 }
 
 // The same opening for few scenarios, with the scenario term's product in it: A[s] = W1_s phi(x_s) + b1 straight from the raw
@@ -264,12 +282,15 @@ struct TermArgs { const float *b1; float *a_term; uint32_t magic_k; int32_t n_ti
 
 template <typename T, int R>
 __global__ __launch_bounds__(512) void scenario_term_kernel(const EncodeArgs a, const TermArgs q, const PrepArgs p, const GridRowsArgs r,
-                                                            unsigned term_blocks, unsigned grid_from)
+                                                            unsigned term_blocks, unsigned grid_from, const PartsOf<T> parts)
 {
     constexpr int ES = sizeof(T), E = 16 / ES, KS = 4 * E, U = 2, EDGE = 16 * R;
     __shared__ __attribute__((aligned(16))) float part[8][R * R * 256];
     __shared__ f32x4 tab[AB_MAX_STATS + AB_MAX_SCALARS];     // statistics first, then the scalars
-    if (blockIdx.x >= grid_from) { grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 512 + threadIdx.x); return; }
+    if (blockIdx.x >= grid_from) {
+        if (!parts_block<512>(parts)) grid_rows_item(r, (int64_t)(blockIdx.x - grid_from) * 512 + threadIdx.x);
+        return;
+    }
     if (blockIdx.x >= term_blocks) { prep_layer1_item<T>(p, (int64_t)(blockIdx.x - term_blocks) * 512 + threadIdx.x); return; }
     const int t = threadIdx.x, lane = t & 63, l15 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -1326,12 +1347,14 @@ static int64_t fill_prep_args(PrepArgs &a, const ab_model_desc *d, const void *W
 
 hipError_t launch_prep_layer1(int dtype, const ab_model_desc *d, const void *W1, const float *b1, int F, int Fs,
                               int H1, int ld, void *w1s, const ab_grid *grid, float *b_term, float *cfg_vec,
-                              const void *Wout, const float *b_out, int H_last, float *w_out_f, hipStream_t st)
+                              const void *Wout, const float *b_out, int H_last, float *w_out_f, SplitWeightsArgs parts, hipStream_t st)
 {
     PrepArgs a;
     const int64_t n = fill_prep_args(a, d, W1, b1, F, Fs, H1, ld, w1s, grid, b_term, cfg_vec, Wout, b_out, H_last, w_out_f);
-    if (dtype == AB_BF16) prep_layer1_kernel<bf16_t><<<blocks_for(n), 256, 0, st>>>(a);
-    else prep_layer1_kernel<float><<<blocks_for(n), 256, 0, st>>>(a);
+    const int64_t own = (n + 255) / 256, blocks = own + (split_weights_items(parts) + 255) / 256;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (dtype == AB_BF16) prep_layer1_kernel<bf16_t><<<(unsigned)blocks, 256, 0, st>>>(a, parts_of<bf16_t>(parts, own));
+    else prep_layer1_kernel<float><<<(unsigned)blocks, 256, 0, st>>>(a, parts_of<float>(parts, own));
     return hipGetLastError();
 }
 
@@ -1341,7 +1364,7 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
                                   int64_t S, int ld, const void *W1, const float *b1, int F, int Fs, int H1, void *w1s,
                                   const ab_grid *grid, float *b_term, float *cfg_vec, const void *Wout,
                                   const float *b_out, int H_last, float *w_out_f, float *xp_row, float *xc_row,
-                                  bool *done, hipStream_t st)
+                                  SplitWeightsArgs parts, bool *done, hipStream_t st)
 {
     *done = false;
     if (S == 0) return hipSuccess;
@@ -1354,20 +1377,19 @@ hipError_t launch_encode_and_prep(int dtype, const ab_model_desc *d, const float
     const int64_t enc_blocks = (S + g.rpb - 1) / g.rpb, prep_blocks = (n + 255) / 256;
     const GridRowsArgs r{grid->partition_bytes, grid->credit_mult, grid->P, grid->Q, d->enc_partition, d->enc_credit, xp_row, xc_row,
                          xp_row ? S * grid->P * grid->Q : 0};
-    const int64_t blocks = enc_blocks + prep_blocks + (r.rows + 255) / 256;
+    const int64_t parts_from = enc_blocks + prep_blocks + (r.rows + 255) / 256, blocks = parts_from + (split_weights_items(parts) + 255) / 256;
     if (blocks > 0x7fffffffLL) return hipSuccess;
     *done = true;
-    if (dtype == AB_BF16)
-        encode_and_prep_kernel<bf16_t><<<(unsigned)blocks, 256, 0, st>>>(a, g, p, r, (unsigned)enc_blocks, (unsigned)(enc_blocks + prep_blocks));
-    else
-        encode_and_prep_kernel<float><<<(unsigned)blocks, 256, 0, st>>>(a, g, p, r, (unsigned)enc_blocks, (unsigned)(enc_blocks + prep_blocks));
+    auto launch = [&](auto kern, auto q) { kern<<<(unsigned)blocks, 256, 0, st>>>(a, g, p, r, (unsigned)enc_blocks, (unsigned)(enc_blocks + prep_blocks), q); };
+    if (dtype == AB_BF16) launch(encode_and_prep_kernel<bf16_t>, parts_of<bf16_t>(parts, parts_from));
+    else                  launch(encode_and_prep_kernel<float>, parts_of<float>(parts, parts_from));
     return hipGetLastError();
 }
 
 hipError_t launch_scenario_term(int dtype, const ab_model_desc *d, const float *dyn, const float *scal, int64_t S, const void *W1,
                                 const float *b1, int F, int Fs, int H1, int Kp, float *a_term, const ab_grid *grid, float *b_term,
                                 float *cfg_vec, const void *Wout, const float *b_out, int H_last, float *w_out_f, float *xp_row,
-                                float *xc_row, hipStream_t st)
+                                float *xc_row, SplitWeightsArgs parts, hipStream_t st)
 {
     if (S == 0) return hipSuccess;
     EncodeArgs a;
@@ -1380,12 +1402,13 @@ hipError_t launch_scenario_term(int dtype, const ab_model_desc *d, const float *
                      quad_split(dtype, d, a, g)};            // (the transform's two forms take the logarithm differently in bf16)
     const GridRowsArgs r{grid->partition_bytes, grid->credit_mult, grid->P, grid->Q, d->enc_partition, d->enc_credit, xp_row, xc_row,
                          xp_row ? S * grid->P * grid->Q : 0};
-    const int64_t term_blocks = (S + edge - 1) / edge * q.n_tiles, grid_from = term_blocks + (n + 511) / 512, blocks = grid_from + (r.rows + 511) / 512;
+    const int64_t term_blocks = (S + edge - 1) / edge * q.n_tiles, grid_from = term_blocks + (n + 511) / 512, parts_from = grid_from + (r.rows + 511) / 512,
+                  blocks = parts_from + (split_weights_items(parts) + 511) / 512;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    auto launch = [&](auto kern) { kern<<<(unsigned)blocks, 512, 0, st>>>(a, q, p, r, (unsigned)term_blocks, (unsigned)grid_from); };
-    if (dtype == AB_BF16) launch(scenario_term_kernel<bf16_t, 1>);
-    else if (edge == 16)  launch(scenario_term_kernel<float, 1>);
-    else                  launch(scenario_term_kernel<float, 2>);
+    auto launch = [&](auto kern, auto w) { kern<<<(unsigned)blocks, 512, 0, st>>>(a, q, p, r, (unsigned)term_blocks, (unsigned)grid_from, w); };
+    if (dtype == AB_BF16) launch(scenario_term_kernel<bf16_t, 1>, parts_of<bf16_t>(parts, parts_from));
+    else if (edge == 16)  launch(scenario_term_kernel<float, 1>, parts_of<float>(parts, parts_from));
+    else                  launch(scenario_term_kernel<float, 2>, parts_of<float>(parts, parts_from));
     return hipGetLastError();
 }
 
