@@ -190,6 +190,15 @@ static void plan_layers(UpdatePlan *p)
     p->total = off;
 }
 
+static RowsArgs rows_shape(const UpdatePlan &p)
+{
+    RowsArgs shape;
+    memset(&shape, 0, sizeof(shape));
+    shape.D = p.D; shape.n_out = p.n_out;
+    for (int k = 0; k < p.D; ++k) { shape.l[k].in = p.in_w[k]; shape.l[k].out = p.H[k]; }
+    return shape;
+}
+
 static void plan_update(const ab_model_desc *d, int64_t B, int first, UpdatePlan *p)
 {
     memset(p, 0, sizeof(*p));
@@ -200,14 +209,11 @@ static void plan_update(const ab_model_desc *d, int64_t B, int first, UpdatePlan
     p->n_out = d->n_outputs > 1 ? d->n_outputs : 1;
     p->B = B;
     p->Bp = (B + 63) / 64 * 64;
-    RowsArgs shape;
-    memset(&shape, 0, sizeof(shape));
-    shape.D = p->D; shape.n_out = p->n_out;
     for (int k = 0; k < p->D; ++k) {
         p->H[k] = d->hidden[k];
         p->in_w[k] = (k == 0) ? p->Kp : d->hidden[k - 1];
-        shape.l[k].in = p->in_w[k]; shape.l[k].out = p->H[k];
     }
+    const RowsArgs shape = rows_shape(*p);
     p->rows = update_rows_supported(shape, p->dtype) && rows_form(shape, p->dtype, B, first, &p->by_batch);
     if (p->rows) plan_rows(p, first);
     else plan_layers(p);
@@ -243,6 +249,16 @@ bool update_one_step(const ab_model_desc *d, int64_t B, int first)
     UpdatePlan p;
     plan_update(d, B, first, &p);
     return p.rows && p.one_step;
+}
+
+// What its blocks of 32 rows look like (for tests): see update_rows32_fold.
+int update_rows32(const ab_model_desc *d, int first)
+{
+    UpdatePlan p;
+    plan_update(d, 8192, first, &p);
+    RowsArgs shape = rows_shape(p);
+    shape.k0 = first;
+    return update_rows32_fold(shape, p.dtype);
 }
 
 // The form that a step takes (for tests).

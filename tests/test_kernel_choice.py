@@ -98,6 +98,10 @@ def takes_rows(d, B, first=0):
     return _fn("_ZN2ab17update_takes_rowsEPK13ab_model_descli", C.c_bool, C.c_void_p, C.c_int64, C.c_int)(C.byref(d), B, first)
 
 
+def rows32(d, first=0):
+    return _fn("_ZN2ab13update_rows32EPK13ab_model_desci", C.c_int, C.c_void_p, C.c_int)(C.byref(d), first)
+
+
 @pytest.mark.parametrize("dtype,L,hidden,first,rows,layers", [
     # light: the row-block form at every batch
     ("bf16", 128, (512, 512, 512), 0, (1, 4096, 5000, 1 << 20), ()), ("bf16", 128, (1024, 512, 256), 0, (1, 4097), ()),
