@@ -244,8 +244,8 @@ static bool joined_opening(const ab_model_desc *d, const ScorePlan &p, int64_t S
 }
 
 // The weights of the products on gemm_split.hip in their parts (6 bytes each), laid out by the pass's first launch where the workspace has room that
-// the pass does not use by then: the candidate table's, the candidate rows' where the grid is shared, the second pass's.  at[k]: offset
-// in the workspace, or 0; tile[k]: columns of the tiles that they are laid out for.  Whole calls, split in each work-group / so, us: 256-256
+// the pass does not use by then: the candidate table's, the candidate rows' where the grid is shared, the second pass's (not the chosen
+// pairs', which the selection of each chunk writes).  at[k]: offset in the workspace, or 0; tile[k]: columns of the tiles that they are laid out for.  Whole calls, split in each work-group / so, us: 256-256
 // 38400 rows 43.9 / 41.3, 614400 392 / 366; 128-128 32768 19.2 / 17.5, 2.4 M 435 / 402; 64-64 38400 18.1 / 17.4, 2.4 M 172 / 161.
 // Tiles of 256 columns (eight wavefronts, half the splitting of activations): where the product is the last one (as it stores, the larger
 // work-group is slower: 256 three times, 38400 rows 82.8 -> 93.2 us), its groups allow them and a tile has 16 slabs or more.  128 columns / 256, us: 256-256
@@ -256,7 +256,7 @@ static void plan_parts(const ScorePlan &p, int32_t C, int per_scenario, PartsPla
 {
     memset(out, 0, sizeof(*out));
     struct { size_t at, left; } room[3] = {{p.off_bterm, needs_table(p, per_scenario) ? 0 : (size_t)C * p.H[0] * 4},
-                                           {p.off_xrow, per_scenario ? 0 : (size_t)p.chunk_rows * 8}, {p.off_vx, p.total - p.off_vx}};
+                                           {p.off_xrow, per_scenario ? 0 : (size_t)p.chunk_rows * 8}, {p.off_vlast, p.total - p.off_vlast}};
     int n = 0;
     for (int k = 1; k < p.D && n < kMostSplitWeights; ++k) {
         if (!p.split[k]) continue;

@@ -28,6 +28,7 @@ pytestmark = pytest.mark.gpu
     (130, 6, 36, 32, [320, 768], False, [256]),                # just enough room, three groups
     (300, 6, 32, 32, [256, 512], False, [256]),                # one group, two tiles
     (1100, 6, 16, 8, [128, 256], False, [128]),                # short sums: tiles of 128, two in a group
+    (3600, 3, 20, 15, [64, 256], True, [128]),                 # second pass's room and two chunks: the first one's choice must leave it alone
 ])
 def test_split_weights(S, L, P, Q, hidden, own_grids, want):
     w = wl.make_scoring("split-parts", S, L, hidden, P, Q, 16 * wl.KIB, 64 * wl.MIB, 1.0, 64.0, False, "f32", 21000 + S)
