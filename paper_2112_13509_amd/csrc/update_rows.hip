@@ -90,15 +90,25 @@ __device__ __forceinline__ void lds_read_tr_4x4(uint2 (&v)[4][4], const unsigned
 }
 __device__ __forceinline__ i32x4 join(const uint2 &lo, const uint2 &hi) { return i32x4{(int)lo.x, (int)lo.y, (int)hi.x, (int)hi.y}; }
 
+template <int R16> using RowsArgsOf = std::conditional_t<R16 == 1, RowsArgs, Rows32Args>;
+
 template <typename T, int R16, bool FOLD>
-__global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
+__global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgsOf<R16> a)
 {
     constexpr int R = 16 * R16, ES = sizeof(T);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t row0 = (int64_t)blockIdx.x * R;
-    touch_arguments<sizeof(RowsArgs)>();
+    // touch_arguments, written out: through the function the compiler orders this opening otherwise (the figures are at Rows32Args)
+    {
+        typedef __attribute__((address_space(4))) const uint32_t karg;
+        karg *ka = (karg *)__builtin_amdgcn_kernarg_segment_ptr();
+        uint32_t sink = 0;
+#pragma unroll
+        for (int i = 0; i < (int)sizeof(a); i += 64) sink ^= ka[i / 4];
+        asm volatile("" ::"s"(sink));
+    }
     const int D = a.D, k0 = a.k0, n_out = a.n_out;
     unsigned char *ring = smem + wave * (NU * UNIT);
     auto buf = [&](int k) { return smem + (k & 1 ? a.o_odd : a.o_even); };         // holds h_k, then delta_k (x: k = -1)
@@ -201,14 +211,16 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
     // FOLD: shares of the inputs that a wavefront takes one after the other (32-row blocks, where the LDS does not hold the sums of
     // more wavefronts): each share's sums begin at zero, as they do in a wavefront of its own.  (In all kernels of 32 rows: 0.6 % of a step.)
     f32x4 whole[R16][4];
-    int cut = 0, share = 0;
-    auto first_cut = [&](const RowsJob &j) {
-        if constexpr (!FOLD) return;
-        if (!j.fold) { cut = -1; return; }
-        share = ((wave * j.recip) >> 5) << j.fold;
-        cut = (j.n_blk * (share + 1)) >> (j.ks_shift + j.fold);
+    int cut = 0, share = 0, fold = 0;
+    auto first_cut = [&](const RowsJob &j, int job) {
+        if constexpr (FOLD) {
+            fold = a.folds >> (2 * job) & 3;
+            if (!fold) { cut = -1; return; }
+            share = ((wave * j.recip) >> 5) << fold;
+            cut = (j.n_blk * (share + 1)) >> (j.ks_shift + fold);
 #pragma unroll
-        for (int q = 0; q < R16 * 4; ++q) whole[q >> 2][q & 3] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int q = 0; q < R16 * 4; ++q) whole[q >> 2][q & 3] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
     };
     auto end_of_block = [&](const RowsJob &j, int b, int b1) {
         if constexpr (!FOLD) return;
@@ -221,7 +233,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
             return;
         }
         clear();
-        cut = (j.n_blk * (++share + 1)) >> (j.ks_shift + j.fold);        // (every share has a block)
+        cut = (j.n_blk * (++share + 1)) >> (j.ks_shift + fold);        // (every share has a block)
     };
     // sums of the wavefronts that split a slice's inputs; true in the wavefront that goes on with the slice
     auto combine = [&](const RowsJob &j) {
@@ -276,7 +288,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
             int slice, b0, b1;
             range(j, pass, slice, b0, b1);
             clear();
-            first_cut(j);
+            first_cut(j, k);
             for (int b = b0; b < b1; ++b) {
                 i32x4 x[R16][2];
 #pragma unroll
@@ -326,7 +338,8 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
     }
 
     // ---- output unit: sixteen output rows (the last one again past n_out), the inputs split over the wavefronts
-    const int H = a.l[D - 1].out, o_sums = R16 == 1 ? a.o_scratch : a.o_sums;
+    const int H = a.l[D - 1].out;
+    auto sums = [&]() { if constexpr (R16 == 1) return smem + a.o_scratch; else return smem + a.o_sums; };
     {
 #pragma unroll
         for (int rr = 0; rr < R16; ++rr) acc[rr][0] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -338,7 +351,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
         }
 #pragma unroll
         for (int rr = 0; rr < R16; ++rr)
-            lds_write16(smem + o_sums + ((wave * R16 + rr) * 64 + lane) * 16, __builtin_bit_cast(i32x4, acc[rr][0]));
+            lds_write16(sums() + ((wave * R16 + rr) * 64 + lane) * 16, __builtin_bit_cast(i32x4, acc[rr][0]));
         meet();
     }
     float *dout_s = (float *)(smem + a.o_dout);             // [R][16]
@@ -347,7 +360,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
         float yh = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-            yh += ((const float *)(smem + o_sums))[((q * R16 + (row >> 4)) * 64 + (row & 15) + 16 * (w >> 2)) * 4 + (w & 3)];
+            yh += ((const float *)sums())[((q * R16 + (row >> 4)) * 64 + (row & 15) + 16 * (w >> 2)) * 4 + (w & 3)];
         const bool live = row0 + row < a.B && w < n_out;
         float e = 0.f;
         if (live) e = (yh + ((const float *)(smem + a.o_bout))[w]) - ((const float *)(smem + a.o_tgt))[row * n_out + w];
@@ -417,7 +430,7 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
             int slice, b0, b1;
             range(j, pass, slice, b0, b1);
             clear();
-            first_cut(j);
+            first_cut(j, 2 * D - 1 - k);
             for (int b = b0; b < b1; ++b) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -463,9 +476,11 @@ __global__ __launch_bounds__(512) void update_rows_kernel(const RowsArgs a)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // no transfer may still target LDS when the group ends
 }
 
-// The jobs and the LDS of a rows launch; false where it does not fit.  At most 1 << most_shift wavefronts share a slice.
-static bool rows_layout(RowsArgs &a, int es, int r16, int most_shift, int *bytes)
+// The jobs and the LDS of a rows launch, of blocks of 32 rows where `wide` says what they have beyond `a`; false where it does not fit.
+// At most 1 << most_shift wavefronts share a slice (16 rows: eight, as many as there are).
+static bool rows_layout(RowsArgs &a, int es, Rows32Args *wide, int most_shift, int *bytes)
 {
+    const int r16 = wide ? 2 : 1;
     auto fill = [&](RowsJob &j, int k, bool back) {
         const int n = (back ? a.l[k].in : a.l[k].out) / 64;
         j.W = (const unsigned char *)a.l[k].W; j.ld = (uint32_t)(a.l[k].in * es);
@@ -476,12 +491,14 @@ static bool rows_layout(RowsArgs &a, int es, int r16, int most_shift, int *bytes
         // 54-64-64-1 bf16 500 rows 24.1 / 22.0, 126-256-128-64-1 fp32 500 rows 35.0 / 33.3; two blocks each at least: 22.7, 22.0, 34.6
         j.ks_shift = n >= 5 ? 0 : n >= 3 ? 1 : n == 2 ? 2 : 3;
         while (j.ks_shift && (1 << j.ks_shift) > j.n_blk) --j.ks_shift;
-        j.fold = (uint8_t)(j.ks_shift > most_shift ? j.ks_shift - most_shift : 0);
-        j.ks_shift -= j.fold;
+        const int fold = j.ks_shift > most_shift ? j.ks_shift - most_shift : 0;
+        if (wide) wide->folds |= (uint32_t)fold << 2 * (int)(&j - a.job);
+        j.ks_shift -= fold;
         j.passes = (uint16_t)((n + 7) / 8);
         j.recip = (uint16_t)((31 + n) / n);
     };
     int even = 0, odd = a.l[0].in * es, bias = 0, masks = 0, part = 0;
+    if (wide) wide->folds = 0;
     a.n_jobs = 0;
     for (int k = 0; k < a.D; ++k) {
         int &side = k & 1 ? odd : even;
@@ -507,15 +524,15 @@ static bool rows_layout(RowsArgs &a, int es, int r16, int most_shift, int *bytes
     a.o_mask = take(masks);
     a.o_dout = take(16 * r16 * 64);
     // the output unit's partial sums: in 32-row blocks where the last layer's inputs were, done with by then
-    const bool free = r16 > 1 && 16 * r16 * (a.D & 1 ? odd : even) >= r16 * 8192;
+    const bool free = wide && 16 * r16 * (a.D & 1 ? odd : even) >= r16 * 8192;
     a.o_scratch = take(r16 * (part * 4096 > 8192 || free ? part * 4096 : 8192));
-    a.o_sums = !free ? a.o_scratch : a.D & 1 ? a.o_odd : a.o_even;
+    if (wide) wide->o_sums = !free ? a.o_scratch : a.D & 1 ? a.o_odd : a.o_even;
     *bytes = o;
     return o <= 160 * 1024;
 }
 
 template <typename T, int R16, bool FOLD>
-static hipError_t launch_rows_one(const RowsArgs &a, int bytes, hipStream_t st)
+static hipError_t launch_rows_one(const RowsArgsOf<R16> &a, int bytes, hipStream_t st)
 {
     auto kern = update_rows_kernel<T, R16, FOLD>;
     static DeviceOnce once;
@@ -539,30 +556,32 @@ bool update_rows_supported(const RowsArgs &shape, int dtype)
     }
     RowsArgs a = shape;
     int bytes;
-    return weights <= (int64_t)7 << 19 && rows_layout(a, es, 1, 3, &bytes);
+    return weights <= (int64_t)7 << 19 && rows_layout(a, es, nullptr, 3, &bytes);
 }
 
 // How many shares (1 << n) a wavefront takes at most one after the other in blocks of 32 rows; -1: such blocks do not fit the LDS, or
 // only with one wavefront on a slice that four share in blocks of 16 (in those / so, fp32, us a step: 256-128-64 and 194 columns, 6000
 // rows 80.6 / 82.1; 128-256 and 362, 4200 rows 67.5 / 72.9; two on a slice that eight share, 64-64 and 394 with eight outputs 57.3 / 54.0).
 // The layout is left in `a`.
-static int rows32_fold(RowsArgs &a, int es, int *bytes)
+static int rows32_fold(Rows32Args &a, int es, int *bytes)
 {
     for (int most = 3; most >= 0; --most) {
-        const bool fits = rows_layout(a, es, 2, most, bytes);
+        const bool fits = rows_layout(a, es, &a, most, bytes);
         int fold = 0;
         for (int i = 0; i < a.n_jobs; ++i) {
-            if (a.job[i].fold > 1 && a.job[i].ks_shift == 0) return -1;
-            if (a.job[i].fold > fold) fold = a.job[i].fold;
+            const int f = a.folds >> (2 * i) & 3;
+            if (f > 1 && a.job[i].ks_shift == 0) return -1;
+            if (f > fold) fold = f;
         }
         if (fits) return fold;
     }
     return -1;
 }
-int update_rows32_fold(RowsArgs shape, int dtype)
+int update_rows32_fold(const RowsArgs &shape, int dtype)
 {
+    Rows32Args a{shape};
     int bytes;
-    return rows32_fold(shape, dtype == AB_BF16 ? 2 : 4, &bytes);
+    return rows32_fold(a, dtype == AB_BF16 ? 2 : 4, &bytes);
 }
 
 // A work-group streams all weights whether it has 16 or 32 rows: 32 once there are more blocks of 16 than CUs, with fewer
@@ -573,9 +592,12 @@ template <typename T>
 static hipError_t launch_rows(RowsArgs &a, int cus, hipStream_t st)
 {
     int bytes = 0;
-    const int fold = (a.B + 15) / 16 > cus ? rows32_fold(a, sizeof(T), &bytes) : -1;
-    if (fold >= 0) return fold ? launch_rows_one<T, 2, true>(a, bytes, st) : launch_rows_one<T, 2, false>(a, bytes, st);
-    return rows_layout(a, sizeof(T), 1, 3, &bytes) ? launch_rows_one<T, 1, false>(a, bytes, st) : hipErrorInvalidValue;
+    Rows32Args w{a};
+    const int fold = (a.B + 15) / 16 > cus ? rows32_fold(w, sizeof(T), &bytes) : -1;
+    // (the kernel of 16 rows is named first, which is where the code object has it then: behind the others' 100 KB a step of 1000 or
+    // 4096 rows took 0.1 us more)
+    if (fold < 0) return rows_layout(a, sizeof(T), nullptr, 3, &bytes) ? launch_rows_one<T, 1, false>(a, bytes, st) : hipErrorInvalidValue;
+    return fold ? launch_rows_one<T, 2, true>(w, bytes, st) : launch_rows_one<T, 2, false>(w, bytes, st);
 }
 
 hipError_t launch_update_rows(int dtype, RowsArgs a, hipStream_t st)
