@@ -42,10 +42,14 @@ static const int64_t kSplitTiles = 192;
 //     (28.0 / 23.7); 256-256 24 15.4 / 14.6 (15.5 / 15.4), 48 16.5 / 14.7 (16.6 / 15.6); 128-1024 32 13.5 / 13.2 (13.6 / 14.0), 56 14.8 / 13.7
 //   several: 512-512-512 32 26.0 / 26.2 (26.1 / 27.4), 40 29.7 / 26.4; 768-768-768 30 32.4 / 31.4 (32.3 / 33.2), 36 37.3 / 31.5; 1024 four
 //     times 32 49.7 / 58.0, 40 57.5 / 58.0 (57.5 / 59.5), 48 60.4 / 58.1; 256-256-256 32 21.0 / 22.4, 48 23.2 / 22.8 (23.3 / 23.4)
+// Not the generating kernel for inputs that the streaming one does not take (K = 64 or above 1024): it has no parts, a work-group takes a
+// whole tile and generates before it multiplies.  One product: 2048-256 12 tiles 47.7 / 62.4, 60 58.8 / 66.6, 64 67.1 / 66.7; 1280-512 12 33.7 /
+// 43.7, 60 40.0 / 44.0; 2048-1024 12 51.6 / 63.1; 4096-256 30 85.7 / 117.7; 64-256 40 12.7 / 14.0, 60 13.2 / 14.0, 64 14.3 / 14.0; several:
+// 1280-512-256 44 43.0 / 55.1, 2048-1024-1024 44 63.4 / 81.1.
 static const int64_t kBigTiles = 64;
-static int64_t big_tiles_least(int K, int N, bool alone)
+static int64_t big_tiles_least(int K, int N, bool alone, bool generated)
 {
-    if (N > 1024) return kBigTiles;
+    if (N > 1024 || (generated && !gemm_big_streams_gen(K))) return kBigTiles;
     if (alone) return K >= 512 ? 12 : 40;
     return K < 512 ? kBigTiles : K < 1024 ? 36 : 44;
 }
@@ -125,7 +129,7 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
     auto big_tiles = [&](int k) { return (p->chunk_rows + 255) / 256 * (p->H[k] / 256); };
     for (int k = 1; k < p->D; ++k) {
         p->tile[k] = pick_tile(p->chunk_rows, p->H[k]);
-        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 || big_tiles(k) < big_tiles_least(p->H[k - 1], p->H[k], p->D == 2)) continue;
+        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 || big_tiles(k) < big_tiles_least(p->H[k - 1], p->H[k], p->D == 2, k == 1)) continue;
         if (k > 1 || C % 256 == 0) p->big[k] = BIG_TILE;       // (its generating kernel has one scenario per row tile)
         else if (gemm_span_shape(C, p->H[0], p->H[k])) p->big[k] = BIG_SPAN;
     }

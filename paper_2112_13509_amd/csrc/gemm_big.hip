@@ -1209,6 +1209,8 @@ bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g)
     return g.ldb % 8 == 0 && g.ldb <= (1 << 22);
 }
 
+bool gemm_big_streams_gen(int K) { return K >= 128 && K <= 1024; }
+
 hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st)
 {
     g.m_tiles = (g.M + 255) / 256;
@@ -1221,7 +1223,7 @@ hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st)
     }
     // generated operand: the streaming kernel needs the bias, the vector area bounds K, two slabs at least,
     // 32-bit row arithmetic and 4-byte DMA sources
-    if (g.bias && g.K <= 1024 && g.K >= 128 && g.M < (1LL << 31))
+    if (g.bias && gemm_big_streams_gen(g.K) && g.M < (1LL << 31))
         return epi == EPI_STORE ? (g.xp_runs4 ? launch_stream_gen<EPI_STORE, true>(g, st) : launch_stream_gen<EPI_STORE, false>(g, st))
                                 : (g.xp_runs4 ? launch_stream_gen<EPI_SCORE, true>(g, st) : launch_stream_gen<EPI_SCORE, false>(g, st));
     return epi == EPI_STORE ? launch_big_one<AMODE_GEN, EPI_STORE>(g, st)

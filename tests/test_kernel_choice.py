@@ -36,7 +36,10 @@ def test_kernel_of_the_first_hidden_product(hidden, S, Cn, kernel):
 @pytest.mark.parametrize("hidden,Cn,k,first", [
     ((512, 512), 256, 1, 6), ((1024, 1024), 256, 1, 3), ((1024, 256), 255, 1, 12), ((256, 256), 256, 1, 40), ((128, 1024), 256, 1, 10),
     ((512, 512, 512), 256, 1, 18), ((512, 512, 512), 256, 2, 18), ((1024,) * 4, 256, 2, 11), ((1024,) * 4, 255, 1, 11), ((256, 256, 256), 256, 1, 64),
-    ((512, 1280), 256, 1, 13), ((1024, 512, 256), 256, 2, 36)])
+    ((512, 1280), 256, 1, 13), ((1024, 512, 256), 256, 2, 36),
+    # inputs that the streaming generating kernel does not take (2048-256, 12 scenarios on whole tiles: 47.7 -> 62.4 us a call)
+    ((2048, 256), 256, 1, 64), ((1280, 512), 256, 1, 32), ((2048, 1024), 256, 1, 16), ((64, 256), 256, 1, 64), ((64, 1024), 256, 1, 16),
+    ((1280, 512, 256), 256, 1, 32), ((2048, 1024, 1024), 256, 1, 16), ((2048, 1024, 1024), 256, 2, 11)])
 def test_fewest_tiles_of_the_large_kernels(hidden, Cn, k, first):
     """From so many scenarios on (parts of tiles fill the chip; 1024-1024, 14 scenarios on generic tiles: 23.1 -> 32.9 us a call), and a
     workspace that holds the other kernels' partial sums below."""
