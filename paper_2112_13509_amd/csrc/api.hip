@@ -39,20 +39,20 @@ static const int64_t kSplitTiles = 192;
 // more CUs but have one slab requested ahead.  Up to 1024 columns a product of less than a round goes in parts of its tiles, so
 // the line lies low; where a pass has this product alone, lowest.  Whole calls, 50 layers of statistics, generic / 256 x 256, us, by tiles:
 //   one product: 1024-1024 16 tiles 28.6 / 22.1, 56 32.9 / 23.1; 768-768 12 24.7 / 19.1 (with 255 candidates 24.5 / 20.7); 1024-256 12 28.2 / 21.9
-//     (28.0 / 23.7); 256-256 24 15.4 / 14.6 (15.5 / 15.4), 48 16.5 / 14.7 (16.6 / 15.6); 128-1024 32 13.5 / 13.2 (13.6 / 14.0), 56 14.8 / 13.7
+//     (28.0 / 23.7); 256-256 24 15.4 / 14.6 (15.5 / 15.4), 48 16.5 / 14.7 (16.6 / 15.6); 128-1024 32 13.5 / 13.2 (13.6 / 14.0), 56 14.8 / 13.7; 128-256 42 (13.7 / 14.0), 55 (14.7 / 14.0)
 //   several: 512-512-512 32 26.0 / 26.2 (26.1 / 27.4), 40 29.7 / 26.4; 768-768-768 30 32.4 / 31.4 (32.3 / 33.2), 36 37.3 / 31.5; 1024 four
 //     times 32 49.7 / 58.0, 40 57.5 / 58.0 (57.5 / 59.5), 48 60.4 / 58.1; 256-256-256 32 21.0 / 22.4, 48 23.2 / 22.8 (23.3 / 23.4)
 // Not the generating kernel for inputs that the streaming one does not take (K = 64 or above 1024): it has no parts, a work-group takes a
 // whole tile and generates before it multiplies.  One product: 2048-256 12 tiles 47.7 / 62.4, 60 58.8 / 66.6, 64 67.1 / 66.7; 1280-512 12 33.7 /
 // 43.7, 60 40.0 / 44.0; 2048-1024 12 51.6 / 63.1; 4096-256 30 85.7 / 117.7; 64-256 40 12.7 / 14.0, 60 13.2 / 14.0, 64 14.3 / 14.0; several:
 // 1280-512-256 44 43.0 / 55.1, 2048-1024-1024 44 63.4 / 81.1.
+// Nor low for a product behind one on generic tiles: that one takes longer then, outside the time of its wavefronts (256-640-256, 40
+// scenarios, 17.7 -> 20.6 us with the same wave cycles, L2 misses and bytes written; the cause is not known).  256-512-512 (the first product on
+// generic tiles) 36 tiles 24.7 / 26.4, 62 28.0 / 30.3; 256-640-256 36 32.0 / 37.8; 256-1024-1024 44 30.2 / 32.9; with the first product on large
+// ones 256-768-256 36 35.1 / 29.4, 256-1024-512 44 36.6 / 30.8.  Where generic tiles of more than 64 columns come behind a product of more than 512, the line lies
+// higher: 512-768-192 36 28.4 / 30.3, 60 31.4 / 32.6; 576-1024-256 36 30.4 / 33.0; 768-768-192 36 32.6 / 32.3, 52 36.5 / 35.0; 768-1024-1024-192 the second
+// 44 50.9 / 53.2, 52 57.5 / 53.7; 768-1280-1024-192 52 62.7 / 64.6; but 512-512-192 36 27.0 / 27.1, 52 30.9 / 28.7, 1024-512-192 44 37.7 / 32.4.
 static const int64_t kBigTiles = 64;
-static int64_t big_tiles_least(int K, int N, bool alone, bool generated)
-{
-    if (N > 1024 || (generated && !gemm_big_streams_gen(K))) return kBigTiles;
-    if (alone) return K >= 512 ? 12 : 40;
-    return K < 512 ? kBigTiles : K < 1024 ? 36 : 44;
-}
 
 static ab_status check_desc(const ab_model_desc *d)
 {
@@ -106,6 +106,25 @@ struct ScorePlan {
 static const int64_t kTargetChunkRows = 1 << 20;
 static const int64_t kVChunk = 4096;
 
+static int64_t big_tiles(const ScorePlan &p, int k) { return (p.chunk_rows + 255) / 256 * (p.H[k] / 256); }
+
+// The 256 x 256 kernel of hidden product k, or 0; `after`: product k - 1 goes to one.
+static int big_kernel(const ScorePlan &p, int32_t C, int k, bool after)
+{
+    const int K = p.H[k - 1], N = p.H[k];
+    if (p.dtype != AB_BF16 || N % 256 != 0) return 0;
+    int64_t least = kBigTiles;
+    if (N <= 1024 && (k == 1 ? gemm_big_streams_gen(K) : after)) {
+        if (p.D == 2) least = K >= 512 ? 12 : K < 192 && C % 4 ? 48 : 40;
+        else least = K < 512 ? kBigTiles : K < 1024 ? 36 : K == 1024 ? 44 : 52;
+        if (N > 512 && least < kBigTiles && k + 1 < p.D && p.H[k + 1] > 64 && !big_kernel(p, C, k + 1, true))
+            least = K >= 768 && K <= 1024 ? 52 : kBigTiles;
+    }
+    if (big_tiles(p, k) < least) return 0;
+    if (k > 1 || C % 256 == 0) return BIG_TILE;              // (its generating kernel has one scenario per row tile)
+    return gemm_span_shape(C, K, N) ? BIG_SPAN : 0;
+}
+
 static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, ScorePlan *p)
 {
     memset(p, 0, sizeof(*p));
@@ -126,19 +145,16 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
     p->chunk_scen = cs;
     p->chunk_rows = cs * C;
     p->tile_a = slim(S, p->H[0]) ? TILE_SLIM : pick_tile(S, p->H[0]);
-    auto big_tiles = [&](int k) { return (p->chunk_rows + 255) / 256 * (p->H[k] / 256); };
     for (int k = 1; k < p->D; ++k) {
         p->tile[k] = pick_tile(p->chunk_rows, p->H[k]);
-        if (p->dtype != AB_BF16 || p->H[k] % 256 != 0 || big_tiles(k) < big_tiles_least(p->H[k - 1], p->H[k], p->D == 2, k == 1)) continue;
-        if (k > 1 || C % 256 == 0) p->big[k] = BIG_TILE;       // (its generating kernel has one scenario per row tile)
-        else if (gemm_span_shape(C, p->H[0], p->H[k])) p->big[k] = BIG_SPAN;
+        p->big[k] = big_kernel(*p, C, k, p->big[k - 1] != 0);
     }
     p->nt_last = 1;
     int nt_room = 1;              // (the generic tiles' below kBigTiles, so that a workspace serves fewer scenarios as well)
     if (p->D >= 2) {
         const int kl = p->D - 1, generic = p->H[kl] / tile_edge(p->tile[kl]);
         p->nt_last = p->big[kl] ? p->H[kl] / 256 : generic;
-        nt_room = p->big[kl] && big_tiles(kl) >= kBigTiles ? p->nt_last : generic;
+        nt_room = p->big[kl] && big_tiles(*p, kl) >= kBigTiles ? p->nt_last : generic;
     }
     const size_t es = elem_size(p->dtype);
     size_t off = 0;

@@ -39,7 +39,12 @@ def test_kernel_of_the_first_hidden_product(hidden, S, Cn, kernel):
     ((512, 1280), 256, 1, 13), ((1024, 512, 256), 256, 2, 36),
     # inputs that the streaming generating kernel does not take (2048-256, 12 scenarios on whole tiles: 47.7 -> 62.4 us a call)
     ((2048, 256), 256, 1, 64), ((1280, 512), 256, 1, 32), ((2048, 1024), 256, 1, 16), ((64, 256), 256, 1, 64), ((64, 1024), 256, 1, 16),
-    ((1280, 512, 256), 256, 1, 32), ((2048, 1024, 1024), 256, 1, 16), ((2048, 1024, 1024), 256, 2, 11)])
+    ((1280, 512, 256), 256, 1, 32), ((2048, 1024, 1024), 256, 1, 16), ((2048, 1024, 1024), 256, 2, 16),
+    # behind generic tiles (256-512-512, 18 scenarios 24.7 -> 26.4 us a call), and wide ones in front of them (512-768-192, 12 scenarios 28.4 -> 30.3)
+    ((256, 512, 512), 256, 2, 32), ((256, 640, 256), 256, 2, 64), ((256, 768, 256), 256, 2, 36), ((256, 1024, 1024), 256, 2, 16), ((256, 768, 512), 256, 2, 22),
+    ((1024, 1280, 256), 260, 2, 63), ((768, 2048, 512), 256, 2, 26), ((512, 768, 192), 256, 1, 22), ((512, 768, 64), 256, 1, 12), ((512, 768, 256), 256, 1, 22), ((768, 1024, 256), 256, 1, 13),
+    ((1024, 1024, 192), 256, 1, 13), ((512, 512, 192), 256, 1, 18), ((768, 1024, 1024, 192), 256, 2, 13), ((1280, 1280, 1024, 192), 256, 2, 16),
+    ((512, 768, 512), 256, 1, 18), ((128, 512), 255, 1, 24), ((128, 512), 260, 1, 19)])
 def test_fewest_tiles_of_the_large_kernels(hidden, Cn, k, first):
     """From so many scenarios on (parts of tiles fill the chip; 1024-1024, 14 scenarios on generic tiles: 23.1 -> 32.9 us a call), and a
     workspace that holds the other kernels' partial sums below."""
