@@ -319,6 +319,14 @@ int scoring_big_kernel(const ab_model_desc *d, int64_t S, int32_t C, int k)
 }
 
 // How many column groups hidden product k takes on gemm_split.hip (for tests); 0: not there.
+// Into how many parts the tiles of the last round of hidden product k go on so many CUs (for tests); 0: not on a streaming kernel.
+int scoring_parts_of_tiles(const ab_model_desc *d, int64_t S, int32_t C, int k, int cus)
+{
+    ScorePlan p;
+    if (plan_scoring(d, S, C, &p) != AB_OK) return -1;
+    return !p.big[k] || (k == 1 && !gemm_big_streams_gen(p.H[0])) ? 0 : stream_parts(p.chunk_rows, p.H[k], cus);
+}
+
 int scoring_split_groups(const ab_model_desc *d, int64_t S, int32_t C, int k)
 {
     ScorePlan p;

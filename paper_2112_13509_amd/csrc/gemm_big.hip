@@ -1210,6 +1210,7 @@ bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g)
 }
 
 bool gemm_big_streams_gen(int K) { return K >= 128 && K <= 1024; }
+int stream_parts(int64_t M, int N, int cus) { return stream_grid_on(cus, (M + 255) / 256, N / 256).parts; }
 
 hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st)
 {

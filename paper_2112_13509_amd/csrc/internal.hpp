@@ -77,6 +77,7 @@ hipError_t launch_gemm_split(int amode, int epi, GemmArgs g, int n_groups, int t
 // The 256x256 bf16 kernel (gemm_big.hip): EPI_STORE (bf16 out) or EPI_SCORE, AMODE_LOAD or AMODE_GEN.
 bool gemm_big_supported(int dtype, int amode, int epi, const GemmArgs &g);
 bool gemm_big_streams_gen(int K);          // whether K generated inputs go to its streaming kernel
+int stream_parts(int64_t M, int N, int cus);          // into how many parts the streaming kernels' last round of tiles goes (for tests)
 hipError_t launch_gemm_big(int amode, int epi, GemmArgs g, hipStream_t st);
 
 // The same product with a generated operand whose row tiles span scenarios (gemm_span.hip).

@@ -101,16 +101,20 @@ __device__ __forceinline__ LastRound last_round(unsigned n_local, unsigned G8, u
 
 // The grid of a streaming launch (a work-group a CU) and into how many parts its last round's tiles go: by the XCD with the most.
 struct StreamGrid { unsigned blocks; int parts; };
+inline StreamGrid stream_grid_on(int cus, int64_t m_tiles, int n_tiles)
+{
+    const int64_t ids = (m_tiles + 7) / 8 * 8 * n_tiles;
+    const int64_t most = cus / 8 * 8 < 8 ? 8 : cus / 8 * 8, per_xcd = ids / 8, left = per_xcd % (most / 8);
+    const int parts = left == 0 || n_tiles > 4 ? 1 : left * 4 <= most / 8 ? 4 : left * 2 <= most / 8 ? 2 : 1;
+    return StreamGrid{(unsigned)(ids < most && parts == 1 ? ids : most), parts};
+}
 inline hipError_t stream_grid(const GemmArgs &g, StreamGrid *out)
 {
     int cus = 0;
     const hipError_t e = compute_units(&cus);
     if (e != hipSuccess) return e;
-    const int64_t ids = (g.m_tiles + 7) / 8 * 8 * g.n_tiles;
-    if (ids > 0x7fffffffLL) return hipErrorInvalidValue;
-    const int64_t most = cus / 8 * 8 < 8 ? 8 : cus / 8 * 8, per_xcd = ids / 8, left = per_xcd % (most / 8);
-    out->parts = left == 0 || g.n_tiles > 4 ? 1 : left * 4 <= most / 8 ? 4 : left * 2 <= most / 8 ? 2 : 1;
-    out->blocks = (unsigned)(ids < most && out->parts == 1 ? ids : most);
+    if ((g.m_tiles + 7) / 8 * 8 * g.n_tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+    *out = stream_grid_on(cus, g.m_tiles, g.n_tiles);
     return hipSuccess;
 }
 

@@ -56,6 +56,19 @@ def test_fewest_tiles_of_the_large_kernels(hidden, Cn, k, first):
         assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("hidden,S,Cn,k,parts", [
+    # on 256 and on 304 CUs: 8 of an XCD's 32 or 38 work-groups hold quarters, 16 (19) halves
+    ((512, 1024), 13, 256, 1, (4, 4)), ((512, 1024), 17, 256, 1, (2, 2)), ((512, 1024), 33, 256, 1, (1, 1)), ((1024, 1024, 1024), 64, 256, 2, (1, 1)),
+    ((1024, 1024, 1024), 72, 256, 2, (4, 1)), ((1024, 1024, 1024), 80, 256, 1, (4, 4)), ((1024, 1024, 1024), 96, 255, 1, (2, 2)), ((1024, 1024, 1024), 300, 256, 2, (1, 1)),
+    # not a streaming kernel; more than four column tiles
+    ((2048, 256), 100, 256, 1, (0, 0)), ((512, 256), 4, 256, 1, (0, 0)), ((128, 1280), 512, 256, 1, (1, 1))])
+def test_parts_of_the_last_round_of_tiles(hidden, S, Cn, k, parts):
+    """Whole tiles leave work-groups idle there (1024 four times, 16 scenarios: 59 -> 76 us a call)."""
+    f = _fn("_ZN2ab22scoring_parts_of_tilesEPK13ab_model_descliii", C.c_int, C.c_void_p, C.c_int64, C.c_int32, C.c_int, C.c_int)
+    d = ab.desc_from_workload(wl.make_scoring("kernel-choice", 1, 4, list(hidden), 4, 4, 16e3, 64e6, 1.0, 16.0, False, "bf16", 1))
+    assert tuple(f(C.byref(d), S, Cn, k, cus) for cus in (256, 304)) == parts
+
+
 @pytest.mark.parametrize("hidden,S,Cn,groups", [
     ((256, 256), 1024, 4096, [1]), ((256, 256), 96, 128, [2]), ((256, 256), 95, 128, [0]), ((64, 64), 192, 128, [1]), ((64, 64), 191, 128, [0]),
     ((256, 128, 64), 192, 128, [1, 1]), ((256, 128, 64), 191, 128, [0, 0]), ((64, 512, 64), 48, 128, [4, 0]), ((256, 256), 4, 4096, [2]), ((256, 256), 4, 512, [0]),
