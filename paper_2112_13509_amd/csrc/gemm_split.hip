@@ -25,11 +25,12 @@
 // them, which is where the next slab wants them; waiting for the DMA alone would leave the compiler to wait for the activations in
 // the next slab, which it does for everything in flight.  2 x 4 wavefronts on 256 columns split each activation once where 2 x 2 on two
 // tiles of 128 do it twice; on 64 x 256 (1 x 4, two work-groups a CU) the weights' traffic into LDS doubles: 2.53 ms.
-// The vector work of a slab (operand generation, splitting) is spread over its matrix instructions, five between two
-// (1.30 M cycles a launch; in one piece a fifth more).  LDS: two stages; a stage holds, per operand, part and half of the
+// The vector work of a slab (operand generation, splitting) is spread over its matrix instructions, five between two (1.30 M cycles
+// a launch; in one piece a fifth more); with PARTS, where the activations alone are split, three, in the larger work-group two.  LDS: two stages; a stage holds, per operand, part and half of the
 // slab's sixteen k, 16 bytes per row one row after the other: a thread writes the eight k it has split and a fragment
 // is one 16-byte read, both over consecutive addresses (no bank conflicts, no swizzle).  Slab j + 1's raw values are in
-// registers while slab j is multiplied, and slab j + 2's are on their way (requested only half a slab ahead: 5 % slower).
+// registers while slab j is multiplied; where the work-group splits its weights, slab j + 2's are on their way across the barrier
+// (requested only half a slab ahead: 5 % slower).
 // A third stage, with the next slab's first fragments read in front of the barrier, was 5 % slower again.
 //
 // Infinities: inf splits into (inf, NaN, NaN), so a row that holds one has a NaN in the second accumulator where fp32 arithmetic
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_split_kernel(const GemmA
         interleave();
         AB_FENCE();
         if constexpr (AMODE != AMODE_LOAD) asm volatile("" ::"s"(rp[par]), "s"(rc[par]));
-        if constexpr (PARTS) {                             // all but slab j + 2's activations
+        if constexpr (PARTS) {                             // everything: slab j + 1's weights, and slab j + 2's activations with them
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_waitcnt(0x70);
             asm volatile("" ::: "memory");
