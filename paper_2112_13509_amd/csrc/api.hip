@@ -150,7 +150,8 @@ static ab_status plan_scoring(const ab_model_desc *d, int64_t S, int32_t C, Scor
         p->big[k] = big_kernel(*p, C, k, p->big[k - 1] != 0);
     }
     p->nt_last = 1;
-    int nt_room = 1;              // (the generic tiles' below kBigTiles, so that a workspace serves fewer scenarios as well)
+    int nt_room = 1;              // (the generic tiles' below kBigTiles, so that the size does not fall where the large kernels begin; from
+                                  //  kBigTiles on it does, as at the lines between the generic tiles: ab_workspace_bytes says so)
     if (p->D >= 2) {
         const int kl = p->D - 1, generic = p->H[kl] / tile_edge(p->tile[kl]);
         p->nt_last = p->big[kl] ? p->H[kl] / 256 : generic;
@@ -318,7 +319,6 @@ int scoring_big_kernel(const ab_model_desc *d, int64_t S, int32_t C, int k)
     return plan_scoring(d, S, C, &p) == AB_OK ? p.big[k] : -1;
 }
 
-// How many column groups hidden product k takes on gemm_split.hip (for tests); 0: not there.
 // Into how many parts the tiles of the last round of hidden product k go on so many CUs (for tests); 0: not on a streaming kernel.
 int scoring_parts_of_tiles(const ab_model_desc *d, int64_t S, int32_t C, int k, int cus)
 {
@@ -327,6 +327,7 @@ int scoring_parts_of_tiles(const ab_model_desc *d, int64_t S, int32_t C, int k, 
     return !p.big[k] || (k == 1 && !gemm_big_streams_gen(p.H[0])) ? 0 : stream_parts(p.chunk_rows, p.H[k], cus);
 }
 
+// How many column groups hidden product k takes on gemm_split.hip (for tests); 0: not there.
 int scoring_split_groups(const ab_model_desc *d, int64_t S, int32_t C, int k)
 {
     ScorePlan p;

@@ -225,6 +225,19 @@ def test_binding_takes_counts_as_int_does(lib, count):
         ab.ab_select_best(sc, idx, C_="four")
 
 
+@pytest.mark.parametrize("hidden,C_,border", [((1024, 1024), 256, 16), ((512, 512), 256, 32), ((256, 256), 256, 64), ((512, 1280), 256, 13)])
+def test_scoring_workspace_falls_where_larger_tiles_begin(lib, hidden, C_, border):
+    """As autobyte.h says: the size for S is not enough for every smaller S, and such a call is refused rather than let run over."""
+    d = ab.make_desc(4, 3, [(1, 0.7, 2.0)] * 3, [(0, 0.0, 1.0)] * 4, (1, 12.0, 0.5), (1, 2.0, 0.5), hidden, "bf16")
+    sizes = [ab.ab_workspace_bytes(d, S, C_) for S in range(2 * border)]
+    assert sizes[border - 1] > sizes[border]
+    for part in (sizes[border // 4 + 1:border], sizes[border:]):     # (below, slim products leave their sums where the rows were)
+        assert part == sorted(part)
+    p = _fake_params(len(hidden) + 1)
+    grid = ab.ab_grid(0x5000, 16, 0x6000, C_ // 16)
+    assert _call_score(lib, d, p, grid=grid, stats=ab.ab_stats(0x3000, 0x4000, border - 1), ws_bytes=sizes[border]) == -5
+
+
 def test_static_scratch_form_checks_its_arguments_on_the_host(lib):
     """The allocation-free scoring entry point refuses bad arguments and oversized problems before any
     device call is made (so these run without a GPU)."""
